@@ -30,12 +30,20 @@ METRIC = "DM-trial×samples/s & real-time factor (4096 ch); batched+CNN vs plain
 PEAK_INT32_OPS = 256 * 4 * 16 * 2.4e9  # CUs x SIMDs x lanes x clock: int32 VALU ops/s
 # Sample additions per 32-bit VALU lane operation: the 16-bit tile adds two
 # 16-bit sample sums per packed add; the byte-quad tile adds four bytes per
-# v_sad_u8.  Their ALU ceilings in sample additions:
-PEAK_SAMPLE_ADDS = {"dedisperse": 2 * PEAK_INT32_OPS, "dedisperse_quad": 4 * PEAK_INT32_OPS}
+# v_sad_u8; the pattern tile adds two dwords of two 8-channel sums per
+# v_add3_u32 (the sums themselves run on the matrix cores, once per delay
+# pattern).  Their ALU ceilings in sample additions:
+PEAK_SAMPLE_ADDS = {"dedisperse": 2 * PEAK_INT32_OPS, "dedisperse_quad": 4 * PEAK_INT32_OPS,
+                    "dedisperse_pattern": 32 * PEAK_INT32_OPS}
+PEAK_NOTE = {"dedisperse": "two 16-bit sample additions per packed 32-bit VALU add: 2 x 256 CUs x 64 lanes x 2.4 GHz",
+             "dedisperse_quad": "four 8-bit sample additions per v_sad_u8 lane operation: 4 x 256 CUs x 64 lanes x "
+                                "2.4 GHz",
+             "dedisperse_pattern": "two dwords of two 8-channel sums per v_add3_u32: 32 x 256 CUs x 64 lanes x "
+                                   "2.4 GHz"}
 # LDS bytes the kernels read per sample addition (a dword holds two 16-bit
-# samples, or four channels' bytes)
-LDS_BYTES_PER_ADD = {"dedisperse": 2.0, "dedisperse_quad": 1.0}
-KERNEL_NAME = {"dedisperse": "k_dedisp", "dedisperse_quad": "k_dedisp_quad"}
+# samples, four channels' bytes, or two outputs' 8-channel sums)
+LDS_BYTES_PER_ADD = {"dedisperse": 2.0, "dedisperse_quad": 1.0, "dedisperse_pattern": 0.25}
+KERNEL_NAME = {"dedisperse": "k_dedisp", "dedisperse_quad": "k_dedisp_quad", "dedisperse_pattern": "k_dedisp_pat"}
 QUAD_KERNEL_BY_KIND = {1: "k_dedisp_quad", 2: "k_dedisp_quad_pc", 3: "k_dedisp_quad_pc"}  # byte-quad kernels by shape kind
 # LDS read rates measured on the MI355X for the kernels' access pattern, B/clk/CU
 LDS_READ2ST64 = 110.2  # ds_read2st64_b32, offsets from registers (the kernels' form)
@@ -66,7 +74,8 @@ def describe(w, desc):
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_dedisp_realistic_traffic.md")
 # the device code of each dedispersion tile, by its profile key
 KERNEL_SOURCES = {"k_dedisp_quad": [os.path.join(ROOT, "paper_2110_12749_amd", "csrc", "dedisp_quad.hip")],
-                  "k_dedisp": [os.path.join(ROOT, "paper_2110_12749_amd", "csrc", "dedisp_tile.h")]}
+                  "k_dedisp": [os.path.join(ROOT, "paper_2110_12749_amd", "csrc", "dedisp_tile.h")],
+                  "k_dedisp_pat": [os.path.join(ROOT, "paper_2110_12749_amd", "csrc", "dedisp_pat.hip")]}
 
 
 def kernel_source_hash(key: str) -> str:
@@ -79,8 +88,8 @@ def kernel_source_hash(key: str) -> str:
 
 
 def measured_traffic(workload_name: str, key: str):
-    """HBM bytes per launch of a dedispersion tile (key "k_dedisp_quad" or
-    "k_dedisp") from the committed rocprofv3 counter summary (FETCH_SIZE +
+    """HBM bytes per launch of a dedispersion tile (key "k_dedisp_pat",
+    "k_dedisp_quad" or "k_dedisp") from the committed rocprofv3 counter summary (FETCH_SIZE +
     WRITE_SIZE, scaled by a plain copy kernel), or None when there is none for
     this workload or the kernel's source changed since."""
     if workload_name != "realistic" or not os.path.exists(TRAFFIC_FILE):
@@ -310,7 +319,9 @@ SWEEP_SHAPES = [(4, 4, 8, 32), (4, 4, 8, 16), (4, 4, 8, 8), (4, 4, 4, 32), (4, 8
                 (4, 8, 4, 64, 2),
                 # split rows: kind 2 over the channels whose copies fit, the 16-bit tile over the rest
                 (4, 8, 8, 64, 3), (4, 8, 12, 64, 3), (8, 4, 8, 64, 3),
-                (8, 4, 4, 64, 2)]
+                (8, 4, 4, 64, 2),
+                # pattern tile
+                (4, 12, 8, 16, 4), (4, 8, 8, 16, 4)]
 
 
 def shape_sweep(w):
@@ -343,7 +354,7 @@ def shape_sweep(w):
                 ctx.dedisperse(fb, w.freqs, d1, out=out)
             p = ctx.profile_read()
             ctx.profile_enable(False)
-            ms = sum(p[k][1] for k in ("dedisperse", "dedisperse_quad") if k in p) / 2
+            ms = sum(p[k][1] for k in PEAK_SAMPLE_ADDS if k in p) / 2
             used = tuple(ctx.row_shape(w.freqs, d1, 0))
             print(f"| {s} | {seg[3]} | {seg[2]} | {c} | {used} | {ms:.2f} | {adds / ms / 1e9:.2f} |", flush=True)
         del out
@@ -507,7 +518,7 @@ def main():
                for k, v in prof.items()}
     kname = KERNEL_NAME[dom]
     if dom == "dedisperse_quad":  # the byte-quad kernel of the rows' shapes (the D = 1 rows share one)
-        kinds = {sh[4] for sh in cfg["tile_shapes"] if sh[4] != 0}
+        kinds = {sh[4] for sh in cfg["tile_shapes"] if sh[4] in QUAD_KERNEL_BY_KIND}
         kname = "/".join(QUAD_KERNEL_BY_KIND[k] for k in sorted(kinds))
     all_adds = sum(prof[k][2] for k in PEAK_SAMPLE_ADDS if k in prof)
     all_ms = sum(prof[k][1] for k in PEAK_SAMPLE_ADDS if k in prof)
@@ -518,18 +529,14 @@ def main():
         "rtf": rtf,
         "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": peak / 1e12, "unit": "TOP/s",
                      "frac": achieved / peak,
-                     "traffic": measured_traffic(w.name, "k_dedisp_quad" if dom == "dedisperse_quad" else "k_dedisp"),
+                     "traffic": measured_traffic(w.name, KERNEL_NAME[dom]),
                      "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-scaled)",
                      "kernel": kname, "launches_per_step": n / args.steps,
                      "work": "integer sample additions (n_dm * n_out * nchan per launch)",
-                     "peak_note": ("four 8-bit sample additions per v_sad_u8 lane operation: 4 x 256 CUs x 64 "
-                                   "lanes x 2.4 GHz" if dom == "dedisperse_quad" else
-                                   "two 16-bit sample additions per packed 32-bit VALU add: 2 x 256 CUs x 64 "
-                                   "lanes x 2.4 GHz") +
-                                  "; the kernel is bound by its LDS reads (see 'lds') and the VALU work of "
-                                  "staging them",
+                     "peak_note": PEAK_NOTE[dom] + "; the kernel is bound by its LDS reads (see 'lds') and the VALU "
+                                                   "work of staging them",
                      "all_dedispersion": {"adds_per_s": all_adds / (all_ms / 1e3), "ms_per_step": all_ms / args.steps,
-                                          "what": "every dedispersion launch of the step (both tiles)"},
+                                          "what": "every dedispersion launch of the step (all tiles)"},
                      "int32_reference": {"peak": PEAK_INT32_OPS / 1e12, "frac": achieved / PEAK_INT32_OPS,
                                          "all_dedispersion_frac": all_adds / (all_ms / 1e3) / PEAK_INT32_OPS,
                                          "what": "against one 32-bit add per VALU lane and clock (256 CUs x 64 "

@@ -75,34 +75,45 @@ RowTables &row_tables(gsp_ctx *ctx, const gsp_dmt_desc *desc, const double *freq
                had.chunk != want.chunk))
     slot.reset();  // the tuned shape changed since the tables were built
   if (!slot) {
-    auto rt = std::make_unique<RowTables>();
-    try {
-      build_row_tables(ctx, desc, freqs, s, want, *rt);
-    } catch (const Error &e) {
-      // the byte-quad default does not suit every row (delay spreads wider
-      // than its LDS copies): such rows split their band between the two
-      // tiles where the quads that do not fit lie at one end of it, else
-      // keep the 16-bit tile
-      const bool tuned = ctx->tuned.count(row_signature(desc, s)) > 0;
-      if (e.status != GSP_EINVAL || want.kind != 2 || tuned) throw;
-      std::vector<int32_t> delays = std::move(rt->delays_host);
-      rt = std::make_unique<RowTables>();
-      rt->delays_host = delays;
-      DedispShape split = want;
-      split.kind = 3;
-      try {
-        build_row_tables(ctx, desc, freqs, s, split, *rt);
-      } catch (const Error &e2) {
-        if (e2.status != GSP_EINVAL) throw;
+    // a default does not suit every row: the pattern tile's partial sums may
+    // not fit the LDS (next: its smaller tile) or not pay (then plain_shape); the byte-quad
+    // tile's copies may not (such rows split their band between two tiles
+    // where the quads that do not fit lie at one end of it, else keep the
+    // 16-bit tile).  A tuned shape is not replaced.
+    std::vector<DedispShape> order{want};
+    const bool tuned = ctx->tuned.count(row_signature(desc, s)) > 0;
+    if (!tuned) {
+      if (want.kind == 4) {
+        if (want.tpw != 8) {  // fewer trials per tile, fewer patterns per group
+          order.push_back(want);
+          order.back().tpw = 8;
+        }
+        order.push_back(plain_shape(desc->seg[s].downsamp, desc->nchan));
+      }
+      if (order.back().kind == 2) {
+        DedispShape split = order.back();
+        split.kind = 3;
+        order.push_back(split);
         DedispShape pair;  // the 16-bit tile's default (4, 4, 8, 32)
         pair.kind = 0;
         pair.groups = 4;
         pair.tpw = 4;
         pair.waves = 8;
         pair.chunk = 32;
-        rt = std::make_unique<RowTables>();
-        rt->delays_host = std::move(delays);
-        build_row_tables(ctx, desc, freqs, s, pair, *rt);
+        order.push_back(pair);
+      }
+    }
+    std::unique_ptr<RowTables> rt;
+    std::vector<int32_t> delays;
+    for (size_t k = 0; k < order.size(); ++k) {
+      rt = std::make_unique<RowTables>();
+      rt->delays_host = std::move(delays);
+      try {
+        build_row_tables(ctx, desc, freqs, s, order[k], *rt, 0, tuned);
+        break;
+      } catch (const Error &e) {
+        if (e.status != GSP_EINVAL || k + 1 == order.size()) throw;
+        delays = std::move(rt->delays_host);
       }
     }
     rt->req = want;

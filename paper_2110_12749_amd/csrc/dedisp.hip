@@ -45,7 +45,8 @@ static constexpr int kStagePitch = kStageT + 1;  // odd u16 pitch spreads LDS ba
 // MODE: 2 = 16-byte loads, 1 = dword loads, 0 = byte loads.
 template <typename OutT, int MODE>
 __global__ __launch_bounds__(256) void k_stage(const uint8_t *__restrict__ X, int64_t nsamp, int32_t nchan,
-                                               int32_t D, int64_t N, OutT *__restrict__ Y, int64_t pitch) {
+                                               int32_t D, int64_t N, OutT *__restrict__ Y, int64_t pitch,
+                                               int32_t split) {
   __shared__ uint16_t tile[kStageC * kStagePitch];
   const int tid = threadIdx.x;
   const int64_t j0 = (int64_t)blockIdx.x * kStageT;
@@ -148,8 +149,11 @@ __global__ __launch_bounds__(256) void k_stage(const uint8_t *__restrict__ X, in
       if constexpr (sizeof(OutT) == 1)
         v[q] = (uint32_t)t[4 * q] | ((uint32_t)t[4 * q + 1] << 8) | ((uint32_t)t[4 * q + 2] << 16) |
                ((uint32_t)t[4 * q + 3] << 24);
-      else
+      else {
         v[q] = (uint32_t)t[2 * q] | ((uint32_t)t[2 * q + 1] << 16);
+        // split form (the pattern tile's, sums below 2048): x >> 4 in the high byte, x & 15 in the low one
+        if (split) v[q] = ((v[q] & 0x07F007F0u) << 4) | (v[q] & 0x000F000Fu);
+      }
     }
     *reinterpret_cast<uint4 *>(Y + (int64_t)c * pitch + j) = make_uint4(v[0], v[1], v[2], v[3]);
   }
@@ -164,7 +168,7 @@ namespace gsp {
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-DedispShape default_shape(int32_t D, int32_t nchan) {
+DedispShape plain_shape(int32_t D, int32_t nchan) {
   DedispShape s;
   s.tpw = 4;
   s.waves = 8;
@@ -180,7 +184,25 @@ DedispShape default_shape(int32_t D, int32_t nchan) {
   return s;
 }
 
+DedispShape default_shape(const gsp_dmt_desc *desc, int32_t s) {
+  const int32_t D = desc->seg[s].downsamp, n_dm = desc->seg[s].n_dm;
+  if (D > 8) return plain_shape(D, desc->nchan);  // the pattern tile's samples have 11 bits
+  DedispShape p;
+  p.kind = 4;
+  p.groups = 4;
+  p.waves = 8;
+  p.chunk = 16;
+  // 96 or 64 trials per tile.  Downsampled rows: 64 (their building is most of
+  // the time and grows with the trials: 13.5 ms for the survey's D = 4 row
+  // with 96, 12.8 with 64; D = 2 the same).  D = 1: a tile's building costs
+  // about 24 trials' sums (49.7 ms for 16 tiles of 96, 54.9 for 24 of 64).
+  auto cost = [&](int t) { return (n_dm + 8 * t - 1) / (8 * t) * (8 * t + 24); };
+  p.tpw = D == 1 && cost(12) <= cost(8) ? 12 : 8;
+  return p;
+}
+
 bool shape_supported(const DedispShape &s) {
+  if (s.kind == 4) return pat_shape_supported(s);
   if (s.kind >= 1 && s.kind <= 3) return quad_shape_supported(s);
   if (s.kind != 0) return false;
   const int kt = s.groups * 16 + s.tpw;
@@ -198,7 +220,7 @@ std::string row_signature(const gsp_dmt_desc *desc, int32_t s) {
 
 DedispShape shape_for_row(gsp_ctx *ctx, const gsp_dmt_desc *desc, int32_t s) {
   auto it = ctx->tuned.find(row_signature(desc, s));
-  return it != ctx->tuned.end() ? it->second : default_shape(desc->seg[s].downsamp, desc->nchan);
+  return it != ctx->tuned.end() ? it->second : default_shape(desc, s);
 }
 
 static constexpr int64_t kLdsBudget = 80 * 1024;  // two workgroups per CU
@@ -222,7 +244,7 @@ int64_t staged_pitch(const RowTables &rt) {
 }
 
 void build_row_tables(gsp_ctx *ctx, const gsp_dmt_desc *desc, const double *freqs, int32_t s,
-                      const DedispShape &shape, RowTables &rt, int units_per_thread) {
+                      const DedispShape &shape, RowTables &rt, int units_per_thread, bool must) {
   if (!shape_supported(shape)) fail(GSP_EINVAL, "unsupported dedispersion shape");
   const gsp_segment &g = desc->seg[s];
   if (rt.delays_host.empty()) {
@@ -237,7 +259,10 @@ void build_row_tables(gsp_ctx *ctx, const gsp_dmt_desc *desc, const double *freq
     rt.n_out = desc->n_out[s];
     rt.max_delay = desc->max_delay[s];
     rt.shape = shape;
-    build_quad_tables(ctx, rt);
+    if (shape.kind == 4)
+      build_pat_tables(ctx, rt, must);
+    else
+      build_quad_tables(ctx, rt);
     return;
   }
   build_tables_from_delays(ctx, g.n_dm, desc->nchan, g.downsamp, desc->nsamp / g.downsamp, desc->n_out[s],
@@ -371,11 +396,11 @@ void stage_row(gsp_ctx *ctx, const uint8_t *fb, const gsp_dmt_desc *desc, const 
   if (rt.D == 1) {
     auto k = mode == 2 ? k_stage<uint8_t, 2> : (mode == 1 ? k_stage<uint8_t, 1> : k_stage<uint8_t, 0>);
     hipLaunchKernelGGL(k, grid, dim3(256), 0, st, fb, desc->nsamp, rt.nchan, rt.D, rt.N, ctx->staged.as<uint8_t>(),
-                       pitch);
+                       pitch, 0);
   } else {
     auto k = mode == 2 ? k_stage<uint16_t, 2> : (mode == 1 ? k_stage<uint16_t, 1> : k_stage<uint16_t, 0>);
     hipLaunchKernelGGL(k, grid, dim3(256), 0, st, fb, desc->nsamp, rt.nchan, rt.D, rt.N, ctx->staged.as<uint16_t>(),
-                       pitch);
+                       pitch, rt.shape.kind == 4 ? 1 : 0);
   }
   check_hip(hipGetLastError(), "launch staging kernel");
   ctx->staged_tag = {fb, desc->nsamp, pitch, rt.nchan, rt.D, nullptr};
@@ -390,7 +415,8 @@ void stage_raw(gsp_ctx *ctx, const uint8_t *fb, int64_t nsamp, int32_t nchan, in
   const uintptr_t fa = reinterpret_cast<uintptr_t>(fb);
   const int mode = (nchan % 16 == 0 && fa % 16 == 0) ? 2 : ((nchan % 4 == 0 && fa % 4 == 0) ? 1 : 0);
   auto k = mode == 2 ? k_stage<uint8_t, 2> : (mode == 1 ? k_stage<uint8_t, 1> : k_stage<uint8_t, 0>);
-  hipLaunchKernelGGL(k, grid, dim3(256), 0, st, fb, nsamp, nchan, 1, nsamp, ctx->staged.as<uint8_t>(), pitch);
+  hipLaunchKernelGGL(k, grid, dim3(256), 0, st, fb, nsamp, nchan, 1, nsamp, ctx->staged.as<uint8_t>(), pitch,
+                     0);
   check_hip(hipGetLastError(), "launch staging kernel");
   ctx->staged_tag = {fb, nsamp, pitch, nchan, 1, nullptr};
 }
@@ -412,6 +438,10 @@ static void launch_k(const DedispArgs &a, int waves, int64_t lds, int D, hipStre
 }
 
 void launch_dedisp(gsp_ctx *ctx, const RowTables &rt, int32_t *out_row, hipStream_t st) {
+  if (rt.shape.kind == 4) {
+    launch_dedisp_pat(ctx, rt, out_row, st);
+    return;
+  }
   if (rt.shape.kind != 0) {
     // a split row: the 16-bit tile's channels first, the byte-quad tile adds
     if (rt.shape.kind == 3) launch_dedisp(ctx, *rt.low, out_row, st);

@@ -245,12 +245,6 @@ __global__ __launch_bounds__(1024) void k_dedisp_quad(QuadArgs a) {
 // waves meet at one barrier per pass).  The summing waves never wait for a
 // global load; the staging waves keep R chunks per thread in flight, their
 // copy records one batch ahead.
-__device__ __forceinline__ void wg_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
 template <int K, int TPW, int NP>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void k_dedisp_quad_pc(QuadArgs a) {
   static_assert(TPW % 2 == 0 && TPW <= 8, "trials are read in pairs");

@@ -42,6 +42,13 @@ __device__ __forceinline__ int xcd_remap(int b, int G) {
   return x < r ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
 }
 
+// Workgroup barrier that also orders LDS accesses across it
+__device__ __forceinline__ void wg_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
 // Staging unit: 16 consecutive samples of one channel, i.e. 8 dwords of each
 // LDS copy.  Per pass each thread stages at most unit_max units (uint8
 // sources: 3; uint16 sources, 9 registers a unit: 2, which keeps 4 waves per

@@ -44,10 +44,11 @@ struct DedispShape {
   int kind = 0;      // 0: 16-bit pair tile (any row); 1: byte-quad tile (D = 1, nchan % 4 == 0);
                      // 2: byte-quad tile with 4 staging waves besides `waves` summing waves;
                      // 3: kind 2 over the channels whose copies fit, the 16-bit tile (default
-                     //    shape) over a run of channels at one end of the band whose copies do not
+                     //    shape) over a run of channels at one end of the band whose copies do not;
+                     // 4: pattern tile (D <= 8): partial sums of 8 channels shared between trials
   int trials_per_block() const { return tpw * waves; }
-  // kind 0: a lane sums `groups` dwords of two samples; kinds 1, 2: `groups` dwords of one sample
-  int samples_per_block() const { return (kind != 0 ? 64 : 128) * groups; }
+  // kinds 0, 4: a lane sums `groups` dwords of two samples; kinds 1, 2: `groups` dwords of one sample
+  int samples_per_block() const { return (kind == 0 || kind == 4 ? 128 : 64) * groups; }
 };
 
 // Per-row device tables for one plan (cached by plan key).
@@ -70,7 +71,9 @@ struct RowTables {
   DevBuf q_tile_pass;        // int32 [n_tiles + 1]: first pass record of each DM tile
   DevBuf q_passes;           // int4 per pass {first quad, first copy, chunks per copy, magic} + a sentinel per tile
   DevBuf q_copies;           // int4 per staged copy: source byte offset of each of its 4 channels
-  int64_t q_pitch = 0;       // staged pitch the quad tile needs
+  DevBuf q_items;            // pattern tile: PatUnit per building unit (q_copies then holds its patterns)
+  DevBuf q_chan;             // pattern tile: int32 [subgroup][8] source byte offsets of a group's channels
+  int64_t q_pitch = 0;       // staged pitch the quad or pattern tile needs
   int32_t y_ch0 = 0;         // first staged channel row the tables read (the row's own channels from here)
   int64_t pitch_override = 0;  // staged pitch shared with the other part of a split row (0: own)
   std::unique_ptr<RowTables> low;  // kind 3: the 16-bit tile's part of the row
@@ -198,15 +201,19 @@ void compute_delays(const gsp_dmt_desc *desc, const double *freqs, int32_t s, in
 std::string plan_key(const gsp_dmt_desc *desc, const double *freqs);
 
 // Dedispersion (dedisp.hip)
-// default: the byte-quad tile where it applies (D = 1, nchan % 4 == 0), else the 16-bit tile
-DedispShape default_shape(int32_t D, int32_t nchan);
+// default: the pattern tile (D <= 8) where its tables fit and pay, else
+// plain_shape: the byte-quad tile where it applies (D = 1, nchan % 4 == 0),
+// else the 16-bit tile
+DedispShape default_shape(const gsp_dmt_desc *desc, int32_t s);
+DedispShape plain_shape(int32_t D, int32_t nchan);
 bool shape_supported(const DedispShape &s);
 std::string row_signature(const gsp_dmt_desc *desc, int32_t s);
 DedispShape shape_for_row(gsp_ctx *ctx, const gsp_dmt_desc *desc, int32_t s);
 // units_per_thread: staging units each thread holds (the kernel's
-// unit_max for its source type); 0 = the batch kernel's for the row's D
+// unit_max for its source type); 0 = the batch kernel's for the row's D.
+// must: build the pattern tile's tables also where another tile is faster
 void build_row_tables(gsp_ctx *ctx, const gsp_dmt_desc *desc, const double *freqs, int32_t s,
-                      const DedispShape &shape, RowTables &rt, int units_per_thread = 0);
+                      const DedispShape &shape, RowTables &rt, int units_per_thread = 0, bool must = true);
 // The same tables from an explicit delay table rt.delays_host [n_dm][nchan]
 // (delays of D*tsamp samples, max_delay their largest; n_out outputs).
 // lds_budget > 0: LDS bytes per workgroup the staging passes may use (default
@@ -248,6 +255,29 @@ void quad_tables_host(const RowTables &rt, QuadHost &H, int64_t min_pitch = 0);
 void quad_split(const RowTables &rt, int32_t *c0, int32_t *c1);
 void build_quad_tables(gsp_ctx *ctx, RowTables &rt);
 void launch_dedisp_quad(gsp_ctx *ctx, const RowTables &rt, int32_t *out_row, hipStream_t st);
+// Pattern tile (dedisp_pat.hip): tables from rt.delays_host for rt.shape
+// (kind 4); GSP_EINVAL when the row does not suit it (D > 8, a group's
+// partial sums wider than the LDS)
+bool pat_shape_supported(const DedispShape &s);
+struct PatUnit {                   // building work: 64 positions x 16 patterns
+  int64_t base;                    // byte offset of the group's first channel row
+  int32_t x;                       // first position
+  int32_t rel;                     // ... less the subgroup's first one
+  int32_t chan, rec;               // subgroup, pattern block
+  int32_t group, pad;
+};
+static_assert(sizeof(PatUnit) == 32, "read with one scalar load");
+struct PatHost {                   // the pattern tile's tables on the host (PatArgs in dedisp_pat.hip)
+  std::vector<int32_t> tile_pass, passes, chan;
+  std::vector<PatUnit> units;
+  std::vector<uint32_t> pats, addr;
+  int64_t pitch = 0;               // staged pitch needed, samples
+  double built = 0;                // LDS dwords built per time tile, all DM tiles
+};
+void pat_tables_host(const RowTables &rt, PatHost &H);
+bool pat_tables_pay(const RowTables &rt, const PatHost &H);
+void build_pat_tables(gsp_ctx *ctx, RowTables &rt, bool must);  // must: also where another tile is faster
+void launch_dedisp_pat(gsp_ctx *ctx, const RowTables &rt, int32_t *out_row, hipStream_t st);
 
 // Search (search.hip)
 SearchTiling search_tiling(int32_t max_width);

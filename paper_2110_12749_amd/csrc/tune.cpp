@@ -33,6 +33,8 @@ const DedispShape kCandidates[] = {
     mk(2, 8, 4, 32), mk(4, 4, 4, 16), mk(8, 4, 8, 16),
     mk(4, 8, 8, 64, 2), mk(4, 8, 12, 64, 2), mk(8, 4, 8, 64, 2), mk(4, 8, 4, 64, 2), mk(4, 8, 8, 64, 3), mk(4, 8, 12, 64, 3),
     mk(4, 8, 8, 64, 1), mk(8, 4, 16, 64, 1),
+    // pattern tile (D <= 8)
+    mk(4, 12, 8, 16, 4), mk(4, 8, 8, 16, 4),
 };
 
 DedispShape from_abi(const gsp_shape &s) {
@@ -104,7 +106,7 @@ int gsp_autotune(gsp_ctx *ctx, const uint8_t *fb, const double *freqs, const gsp
       for (int32_t s = 0; s < desc->n_seg; ++s) {
         const std::string sig = row_signature(desc, s);
         float best_ms = 1e30f;
-        DedispShape best = default_shape(desc->seg[s].downsamp, desc->nchan);
+        DedispShape best = default_shape(desc, s);
         for (const DedispShape &cand : kCandidates) {
           ctx->tuned[sig] = cand;
           RowTables *rt = nullptr;
