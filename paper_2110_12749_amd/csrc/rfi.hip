@@ -14,8 +14,9 @@
 // Design: four HBM-bound passes.  One wave per spectrum forms s_j (16-byte
 // loads, byte sums by v_sad_u8, DPP reduction); one workgroup per block
 // takes the moments (int64 / 128-bit sums) and flags; channel means are
-// read only for blocks that replace something; a last pass writes the
-// replaced spectra and applies the filter, in place if out == in.
+// read only for blocks that replace something, each block's spectra split over
+// many workgroups; a last pass writes the replaced spectra and applies the
+// filter, in place if out == in.
 #include <algorithm>
 #include <cmath>
 
@@ -68,7 +69,8 @@ __global__ __launch_bounds__(kRfiThreads) void k_rfi_rowsum(const uint8_t *__res
 __global__ __launch_bounds__(kRfiThreads) void k_rfi_flags(const int32_t *__restrict__ s, int64_t nsamp,
                                                           int64_t block, double clip, uint8_t *__restrict__ flag,
                                                           int32_t *__restrict__ n_u,
-                                                          unsigned long long *__restrict__ n_flagged) {
+                                                          unsigned long long *__restrict__ n_flagged,
+                                                          uint32_t *__restrict__ csum, int32_t nchan) {
   __shared__ int64_t r1[kRfiThreads];
   __shared__ unsigned __int128 r2[kRfiThreads];
   __shared__ int32_t rc[kRfiThreads];
@@ -121,18 +123,84 @@ __global__ __launch_bounds__(kRfiThreads) void k_rfi_flags(const int32_t *__rest
   const bool replace = nu > 0 && nu < n;
   if (!replace)
     for (int64_t k = tid; k < n; k += kRfiThreads) flag[j0 + k] = 0;
+  if (replace && csum)  // the block's channel sums start from zero
+    for (int32_t c = tid; c < nchan; c += kRfiThreads) csum[b * (int64_t)nchan + c] = 0;
   if (tid == 0) {
     n_u[b] = replace ? nu : (int32_t)n;
     if (replace) atomicAdd(n_flagged, (unsigned long long)(n - nu));
   }
 }
 
+// Channel sums over the unflagged spectra of blocks that replace some.
+// A workgroup takes kRfiSlice spectra of a block (grid: channel tiles x
+// slices y, y + gridDim.y, ... x blocks z, z + gridDim.z, ...), `cw` threads side by side over the
+// channels (16 each with 16-byte loads, else one) and 256 / cw spectra apart;
+// a thread's sums of at most kRfiSlice bytes fit 16 bits, two channels to a
+// dword, and are added to the block's by one atomic per channel.  Bound by
+// reading the blocks and the atomics: one thread per channel over a whole
+// block of 2048 spectra, a serial chain of loads, took 1.55 ms for the blocks
+// 30 spikes fall in (4096 channels); slices of 64 spectra take 0.23 ms, of 128
+// 0.17.
+constexpr int kRfiSlice = 128;
+template <int VEC>
+__global__ __launch_bounds__(kRfiThreads) void k_rfi_sums(const uint8_t *__restrict__ x, int64_t nsamp,
+                                                         int32_t nchan, int64_t block, int64_t n_blocks, int cw,
+                                                         const uint8_t *__restrict__ flag,
+                                                         const int32_t *__restrict__ n_u,
+                                                         uint32_t *__restrict__ csum) {
+  constexpr int C = VEC ? 16 : 1;
+  const int c = (blockIdx.x * cw + (threadIdx.x & (cw - 1))) * C;
+  if (c >= nchan) return;
+  for (int64_t b = blockIdx.z; b < n_blocks; b += gridDim.z) {
+    const int64_t j0 = b * block;
+    const int64_t n = min(block, nsamp - j0);
+    if (n_u[b] == n) continue;  // nothing replaced in this block
+    const uint8_t *p = x + j0 * (int64_t)nchan + c;
+    uint32_t *d = csum + b * (int64_t)nchan + c;
+    for (int64_t k0 = (int64_t)blockIdx.y * kRfiSlice; k0 < n; k0 += (int64_t)gridDim.y * kRfiSlice) {
+      const int64_t end = min(n, k0 + kRfiSlice);
+      if constexpr (VEC) {
+        uint32_t ev[4] = {0, 0, 0, 0}, od[4] = {0, 0, 0, 0};
+#pragma unroll 8
+        for (int64_t k = k0 + threadIdx.x / cw; k < end; k += kRfiThreads / cw) {
+          const uint4 q = *reinterpret_cast<const uint4 *>(p + k * (int64_t)nchan);
+          const uint32_t keep = flag[j0 + k] ? 0u : 0x00FF00FFu;  // the load does not wait for the flag
+          const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            ev[i] += w[i] & keep;
+            od[i] += (w[i] >> 8) & keep;
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          atomicAdd(d + 4 * i, ev[i] & 0xFFFFu);
+          atomicAdd(d + 4 * i + 1, od[i] & 0xFFFFu);
+          atomicAdd(d + 4 * i + 2, ev[i] >> 16);
+          atomicAdd(d + 4 * i + 3, od[i] >> 16);
+        }
+      } else {
+        uint32_t acc = 0;
+#pragma unroll 8
+        for (int64_t k = k0 + threadIdx.x / cw; k < end; k += kRfiThreads / cw) {
+          const uint32_t v = p[k * (int64_t)nchan];
+          acc += flag[j0 + k] ? 0u : v;
+        }
+        atomicAdd(d, acc);
+      }
+    }
+  }
+}
+
 // Channel means over the unflagged spectra of blocks that replace some:
 // thread = channel, workgroup = (channel tile, blocks y, y + gridDim.y, ...).
+// csum: the sums (k_rfi_sums); null for blocks of at most kRfiSlice spectra,
+// which are summed here (their sums would take more memory than their bytes).
 __global__ __launch_bounds__(kRfiThreads) void k_rfi_means(const uint8_t *__restrict__ x, int64_t nsamp,
                                                           int32_t nchan, int64_t block, int64_t n_blocks,
                                                           const uint8_t *__restrict__ flag,
                                                           const int32_t *__restrict__ n_u,
+                                                          const uint32_t *__restrict__ csum,
                                                           uint8_t *__restrict__ mean,
                                                           unsigned long long *__restrict__ msum) {
   const int c = blockIdx.x * kRfiThreads + threadIdx.x;
@@ -142,7 +210,9 @@ __global__ __launch_bounds__(kRfiThreads) void k_rfi_means(const uint8_t *__rest
     const int32_t nu = n_u[b];
     if (nu == n) continue;  // nothing replaced in this block
     uint32_t acc = 0;
-    if (c < nchan)
+    if (csum) {
+      if (c < nchan) acc = csum[b * (int64_t)nchan + c];
+    } else if (c < nchan)
       for (int64_t k = 0; k < n; ++k)
         if (!flag[j0 + k]) acc += x[(j0 + k) * (int64_t)nchan + c];
     const uint32_t m = c < nchan ? (uint32_t)((2 * (uint64_t)acc + (uint64_t)nu) / (2 * (uint64_t)nu)) : 0u;
@@ -237,7 +307,9 @@ extern "C" int gsp_rfi_clean(gsp_ctx *ctx, const uint8_t *fb_dev, int64_t nsamp,
     const size_t o_mean = (o_nu + (size_t)nb * 4 + 255) / 256 * 256;
     const size_t o_msum = (o_mean + (size_t)nb * nchan + 255) / 256 * 256;
     const size_t o_cnt = (o_msum + (size_t)nb * 8 + 255) / 256 * 256;
-    const size_t bytes = o_cnt + 256;
+    const bool split = clip && block > kRfiSlice && nsamp > kRfiSlice;  // channel sums of their own
+    const size_t o_csum = o_cnt + 256;
+    const size_t bytes = o_csum + (split ? (size_t)nb * nchan * 4 : 0);
     ctx->rfi.device = ctx->device;
     ctx->rfi.reserve(bytes);
     unsigned char *base = ctx->rfi.as<unsigned char>();
@@ -247,6 +319,7 @@ extern "C" int gsp_rfi_clean(gsp_ctx *ctx, const uint8_t *fb_dev, int64_t nsamp,
     uint8_t *mean = base + o_mean;
     auto *msum = reinterpret_cast<unsigned long long *>(base + o_msum);
     auto *cnt = reinterpret_cast<unsigned long long *>(base + o_cnt);
+    uint32_t *csum = split ? reinterpret_cast<uint32_t *>(base + o_csum) : nullptr;
     const unsigned grid = (unsigned)std::min<int64_t>((nsamp + 3) / 4, 256 * 16);  // 4 waves per workgroup
     ProfScope prof(ctx, "rfi", st, 2.0 * (double)nsamp * nchan);
     hipLaunchKernelGGL(k_rfi_zero, dim3(1), dim3(64), 0, st, cnt, (int64_t)1);
@@ -256,10 +329,21 @@ extern "C" int gsp_rfi_clean(gsp_ctx *ctx, const uint8_t *fb_dev, int64_t nsamp,
       hipLaunchKernelGGL(k_rfi_zero, dim3((unsigned)std::min<int64_t>((nb + 255) / 256, 1024)), dim3(256), 0, st,
                          msum, nb);
       hipLaunchKernelGGL(k_rfi_flags, dim3((unsigned)nb), dim3(kRfiThreads), 0, st, s, nsamp, block, clip_sigma,
-                         flag, n_u, cnt);
+                         flag, n_u, cnt, csum, nchan);
+      if (split) {
+        const int v16 = (nchan % 16 == 0 && reinterpret_cast<uintptr_t>(fb_dev) % 16 == 0) ? 1 : 0;
+        const int cols = v16 ? nchan / 16 : nchan;
+        int cw = 1;  // threads side by side: a power of two that covers the channels, at most a workgroup
+        while (cw < cols && cw < kRfiThreads) cw *= 2;
+        const int64_t slices = (std::min(block, nsamp) + kRfiSlice - 1) / kRfiSlice;
+        const dim3 g((unsigned)((cols + cw - 1) / cw), (unsigned)std::min<int64_t>(slices, 65535),
+                     (unsigned)std::min<int64_t>(nb, 65535));
+        auto k = v16 ? k_rfi_sums<1> : k_rfi_sums<0>;
+        hipLaunchKernelGGL(k, g, dim3(kRfiThreads), 0, st, fb_dev, nsamp, nchan, block, nb, cw, flag, n_u, csum);
+      }
       hipLaunchKernelGGL(k_rfi_means,
                          dim3((unsigned)((nchan + kRfiThreads - 1) / kRfiThreads), (unsigned)std::min<int64_t>(nb, 65535)),
-                         dim3(kRfiThreads), 0, st, fb_dev, nsamp, nchan, block, nb, flag, n_u, mean, msum);
+                         dim3(kRfiThreads), 0, st, fb_dev, nsamp, nchan, block, nb, flag, n_u, csum, mean, msum);
     }
     hipLaunchKernelGGL(k_rfi_apply, dim3(grid), dim3(kRfiThreads), 0, st, fb_dev, nsamp, nchan, clip ? block : 0,
                        vec, s, flag, mean, msum, clip ? 1 : 0, zero_dm ? 1 : 0, same ? 0 : 1, out_dev);

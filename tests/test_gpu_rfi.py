@@ -80,3 +80,17 @@ def test_wideband_full_size(env):
     n = _check(env, X, 6.0, 2048, True, True)
     say(f"  {n} spectra replaced")
     assert n >= 1
+
+
+@pytest.mark.parametrize("nchan", [16, 48, 272, 65, 4112, 300])
+@pytest.mark.parametrize("nsamp,block", [(128, 128), (129, 129), (257, 4096), (1000, 127), (1100, 330)])
+def test_channel_sum_slices(env, nchan, nsamp, block):
+    """Blocks of one slice, one spectrum more, two and a half, a short last
+    block; channel counts around whole 16-byte loads and workgroups."""
+    rng = np.random.default_rng(nchan * nsamp + block)
+    X = rng.integers(90, 160, (nsamp, nchan), dtype=np.uint8)
+    for j in (3, nsamp // 2, nsamp - 1):
+        X[j] = 255
+    say(f"[case] rfi slices {nchan}x{nsamp} block {block}")
+    assert _check(env, X, 3.0, block, True, False) >= 1
+    assert _check(env, X, 3.0, block, False, True) >= 1
