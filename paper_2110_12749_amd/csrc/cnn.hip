@@ -6,13 +6,17 @@
 //   -> conv3x3(32->64)+ReLU+maxpool2 -> conv3x3(64->128)+ReLU+maxpool2
 //   -> flatten (h, w, c) 2048 -> FC 192 + ReLU -> FC 1 -> logit
 //   loss: binary cross-entropy with logits (mean over the batch); Adam.
-// Every convolution and fully connected product, forward and backward
-// (activation and weight gradients), runs on one hand-written GEMM kernel
-// built on the gfx950 BF16 matrix cores (v_mfma_f32_32x32x16_bf16), fed by
-// im2col / col2im gathers; the epilogue fuses bias, ReLU and gradient masks.
+// Every convolution and fully connected product but the first, forward and
+// backward, runs on the gfx950 BF16 matrix cores (v_mfma_f32_32x32x16_bf16):
+// k_gemm for the forward passes and the gradients of the inputs (a
+// convolution of the output gradients with the flipped kernel), its operands
+// gathered from the activations (implicit im2col), bias and ReLU in the
+// epilogue; k_wgrad for the gradients of the weights, whose operands run along
+// their rows.  The first convolution (2 channels) has kernels of its own.
 #include <cmath>
 #include <cstring>
 #include <fstream>
+#include <stdexcept>
 
 #include "gsp_internal.h"
 
@@ -43,46 +47,48 @@ __host__ __device__ inline float bf2f(uint16_t h) {
 }
 
 // ---------------------------------------------------------------------------
-// GEMM: C[m][n] = sum_k A[m][k] B[k][n] (+ bias[n]) (ReLU) (mask) with
-// arbitrary element strides, BF16 inputs, FP32 accumulation.
-// Workgroup tile 64 x 64, k step 32 (two 32 x 32 x 16 MFMAs per wave); 4 waves, each a 32 x 32 tile.
+// GEMM: C[m][n] = sum_k A[m][k] B[k][n] (+ bias[n]) (ReLU), BF16 inputs, FP32
+// accumulation.  A: rows of a_m elements, unit k stride, or implicit im2col; B
+// and C with arbitrary element strides.  K, a_m, and b_n where b_k is 1, are
+// multiples of 8, the operands' bases 16-byte aligned.
 // ---------------------------------------------------------------------------
 struct GemmArgs {
   const uint16_t *A;
-  int64_t a_m, a_k;  // strides (elements)
+  int64_t a_m;
   const uint16_t *B;
   int64_t b_k, b_n;
   void *C;
   int64_t c_m, c_n;
   int32_t M, N, K;
   const float *bias;       // [N] or null
-  const uint16_t *mask;    // optional: zero the result where mask[m*c_m + n*c_n] <= 0 (bf16)
   int32_t relu;
   int32_t out_bf16;        // 1: store bf16, 0: store fp32
-  int32_t accumulate;      // fp32 output only: C += result
-  int32_t k_chunk;         // split-K: workgroup z covers k in [z*k_chunk, (z+1)*k_chunk); atomic fp32 adds
-  // implicit im2col (3x3, padding 1) for A when im_x is set: A[m][k] =
-  // x(n, c, h + dh, w + dw) with m = (n*H + h)*H + w, k = tap*C + c,
-  // tap = (dh+1)*3 + (dw+1); x addressed with strides (n, c, h, w)
-  const uint16_t *im_x;
-  int64_t im_sn, im_sc, im_sh, im_sw;
+  // implicit im2col (3x3, padding 1) when im_H > 0: A is NHWC activations of
+  // 2^im_H x 2^im_H pixels and 2^im_C channels (at least 8), A[m][k] =
+  // x(n, h + dh, w + dw, c) with m = (n*H + h)*H + w, k = tap*C + c,
+  // tap = (dh+1)*3 + (dw+1)
   int32_t im_C, im_H;
 };
-
 static constexpr int kTM = 64, kTN = 64, kTK = 32;
 static constexpr int kTP = kTK + 8;  // padded LDS row: 80 bytes, 16-byte aligned
 
-static unsigned grid_for(int64_t n) { return (unsigned)std::min<int64_t>((n + 255) / 256, 256 * 64); }
+__device__ __host__ inline int grid_for(int64_t n) {
+  const int64_t b = (n + 255) / 256;
+  return (int)(b < 1 ? 1 : b > 65535 ? 65535 : b);
+}
 
 typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 
-// Workgroup tile 64 x 64, k step 32.  Each thread stages 8 consecutive k of
-// one A row and of one B column: one 16-byte load where the operand is
-// contiguous and aligned along k (plain A with unit k stride, implicit
-// im2col over channel-contiguous activations, B with unit k stride), 8
-// element loads otherwise.  B is kept transposed in LDS ([n][k]) so that
-// both MFMA operands are 8-byte LDS reads.  The next k step's operands are
-// loaded into registers while the current one is multiplied.
+// Workgroup tile 64 x 64, k step 32 (two 32 x 32 x 16 MFMAs per wave); 4 waves,
+// each a 32 x 32 tile.  Each thread stages 8 consecutive k of one A row (IM: by
+// implicit im2col) and of one B column: one 16-byte load, or, where B's k
+// stride is not 1 (BV false: fc1's input gradient), 8 element loads.  B is kept
+// transposed in LDS ([n][k]) so that both MFMA operands are 16-byte LDS reads.
+// The next k step's operands are loaded into registers while the current one
+// is multiplied.  The forms are template arguments: chosen inside one kernel
+// they cost registers (4 to 7 waves per SIMD in place of 8); conv2 to conv4 of
+// 6754 images took 953 us, now 832.
+template <bool IM, bool BV>
 __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
   __shared__ __align__(16) uint16_t As[kTM][kTP];
   __shared__ __align__(16) uint16_t Bt[kTN][kTP];
@@ -92,77 +98,41 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
   const int64_t m0 = (int64_t)blockIdx.x * kTM;
   const int64_t n0 = (int64_t)blockIdx.y * kTN;
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  const bool split = gridDim.z > 1;
-  const int k_begin = split ? (int)blockIdx.z * g.k_chunk : 0;
-  const int k_end = split ? min(g.K, k_begin + g.k_chunk) : g.K;
+  const int k_end = g.K;
   // this thread's A row / B column and k offset inside a step
   const int srow = tid >> 2, skc = (tid & 3) * 8;
   const int64_t am = m0 + srow, bcol = n0 + srow;
   const bool a_in = am < g.M, b_in = bcol < g.N;
   // implicit im2col: the pixel of this thread's A row
-  const uint16_t *im_base = nullptr;
-  int im_h = 0, im_w = 0;
-  if (g.im_x) {
-    const int64_t m = min(am, (int64_t)g.M - 1);
-    const int HH = g.im_H * g.im_H;
-    const int64_t n = m / HH;
-    const int hw = (int)(m - n * HH);
-    im_h = hw / g.im_H;
-    im_w = hw - im_h * g.im_H;
-    im_base = g.im_x + n * g.im_sn;
-  }
-  // vector forms, decided once per launch
-  const bool a_vec = g.im_x ? (g.im_C % 8 == 0 && g.im_sc == 1 && g.im_sh % 8 == 0 && g.im_sw % 8 == 0 &&
-                               g.im_sn % 8 == 0 && (reinterpret_cast<uintptr_t>(g.im_x) & 15) == 0)
-                            : (g.a_k == 1 && g.a_m % 8 == 0 && (reinterpret_cast<uintptr_t>(g.A) & 15) == 0);
-  const bool b_vec = g.b_k == 1 && g.b_n % 8 == 0 && (reinterpret_cast<uintptr_t>(g.B) & 15) == 0;
+  const int H = 1 << g.im_H, im_h = (int)(am >> g.im_H) & (H - 1), im_w = (int)am & (H - 1);
+  const uint16_t *arow = IM ? g.A + (am << g.im_C) : g.A + am * g.a_m, *bptr = g.B + bcol * g.b_n;
 
   auto load_a = [&](int k0) -> u16x8 {
     u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
     const int k = k0 + skc;
-    if (!a_in) return v;
-    if (g.im_x) {
-      if (a_vec && k + 8 <= k_end) {
-        const int tap = k / g.im_C, ch = k - tap * g.im_C;
-        const int hh = im_h + tap / 3 - 1, ww = im_w + tap % 3 - 1;
-        if (hh >= 0 && hh < g.im_H && ww >= 0 && ww < g.im_H)
-          v = *reinterpret_cast<const u16x8 *>(im_base + ch + hh * g.im_sh + ww * g.im_sw);
-        return v;
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int kk = k + i;
-        if (kk < k_end) {
-          const int tap = kk / g.im_C, ch = kk - tap * g.im_C;
-          const int hh = im_h + tap / 3 - 1, ww = im_w + tap % 3 - 1;
-          if (hh >= 0 && hh < g.im_H && ww >= 0 && ww < g.im_H)
-            v[i] = im_base[ch * g.im_sc + hh * g.im_sh + ww * g.im_sw];
-        }
-      }
-      return v;
-    }
-    if (a_vec && k + 8 <= k_end) return *reinterpret_cast<const u16x8 *>(g.A + am * g.a_m + k);
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (k + i < k_end) v[i] = g.A[am * g.a_m + (int64_t)(k + i) * g.a_k];
+    if (!a_in || k >= k_end) return v;
+    if (!IM) return *reinterpret_cast<const u16x8 *>(arow + k);
+    const int tap = k >> g.im_C, ch = k & ((1 << g.im_C) - 1);
+    const int dh = tap / 3 - 1, dw = tap % 3 - 1;
+    if ((unsigned)(im_h + dh) < (unsigned)H && (unsigned)(im_w + dw) < (unsigned)H)
+      v = *reinterpret_cast<const u16x8 *>(arow + ((int64_t)(dh * H + dw) << g.im_C) + ch);
     return v;
   };
   auto load_b = [&](int k0) -> u16x8 {
     u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
     const int k = k0 + skc;
-    if (!b_in) return v;
-    if (b_vec && k + 8 <= k_end) return *reinterpret_cast<const u16x8 *>(g.B + bcol * g.b_n + k);
+    if (!b_in || k >= k_end) return v;
+    if (BV) return *reinterpret_cast<const u16x8 *>(bptr + k);
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (k + i < k_end) v[i] = g.B[(int64_t)(k + i) * g.b_k + bcol * g.b_n];
+    for (int i = 0; i < 8; ++i) v[i] = bptr[(int64_t)(k + i) * g.b_k];
     return v;
   };
 
   f32x16 acc;
 #pragma unroll
   for (int j = 0; j < 16; ++j) acc[j] = 0.f;
-  u16x8 pa = load_a(k_begin), pb = load_b(k_begin);
-  for (int k0 = k_begin; k0 < k_end; k0 += kTK) {
+  u16x8 pa = load_a(0), pb = load_b(0);
+  for (int k0 = 0; k0 < k_end; k0 += kTK) {
     __syncthreads();  // the previous step's operands are read
     *reinterpret_cast<u16x8 *>(&As[srow][skc]) = pa;
     *reinterpret_cast<u16x8 *>(&Bt[srow][skc]) = pb;
@@ -192,15 +162,8 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
     float v = acc[j] + bn;
     if (g.relu) v = v > 0.f ? v : 0.f;
     const int64_t o = m * g.c_m + n * g.c_n;
-    if (split) {  // partial sums over a slice of k (bias, ReLU and masks not allowed)
-      atomicAdd(static_cast<float *>(g.C) + o, acc[j]);
-      continue;
-    }
-    if (g.mask && !(bf2f(g.mask[o]) > 0.f)) v = 0.f;
     if (g.out_bf16)
       static_cast<uint16_t *>(g.C)[o] = f2bf(v);
-    else if (g.accumulate)
-      static_cast<float *>(g.C)[o] += v;
     else
       static_cast<float *>(g.C)[o] = v;
   }
@@ -267,95 +230,225 @@ __global__ void k_zero_f32(float *__restrict__ a, int64_t n) {
     a[i] = 0.f;
 }
 
-// Plain launch, or split-K (fp32 output zeroed first, partial sums added
-// atomically) when the output is small and K long: weight gradients.
-static void gemm(GemmArgs g, hipStream_t st) {
+static void gemm(const GemmArgs &g, hipStream_t st) {
   if (g.M <= 0 || g.N <= 0) return;
-  const int64_t tiles = (int64_t)((g.M + kTM - 1) / kTM) * ((g.N + kTN - 1) / kTN);
-  int splits = 1;
-  if (!g.out_bf16 && !g.bias && !g.relu && !g.mask && !g.accumulate && tiles < 256 && g.K >= 8192)
-    splits = (int)std::min<int64_t>(std::max<int64_t>(1, 1024 / tiles), g.K / 4096);
-  dim3 grid((unsigned)((g.M + kTM - 1) / kTM), (unsigned)((g.N + kTN - 1) / kTN), (unsigned)splits);
-  if (splits > 1) {
-    g.k_chunk = (g.K + splits - 1) / splits;
-    g.k_chunk = (g.k_chunk + kTK - 1) / kTK * kTK;
-    // zero the (strided) fp32 output: M x N with strides c_m, c_n (dense here)
-    const int64_t span = (int64_t)(g.M - 1) * g.c_m + (int64_t)(g.N - 1) * g.c_n + 1;
-    hipLaunchKernelGGL(k_zero_f32, dim3(grid_for(span)), dim3(256), 0, st, static_cast<float *>(g.C), span);
-  } else {
-    g.k_chunk = g.K;
-  }
-  hipLaunchKernelGGL(k_gemm, grid, dim3(256), 0, st, g);
+  const bool bv = g.b_k == 1;
+  if (g.K % 8 || g.a_m % 8 || (bv && g.b_n % 8) || (reinterpret_cast<uintptr_t>(g.A) & 15) ||
+      (bv && (reinterpret_cast<uintptr_t>(g.B) & 15)) || (g.im_H && (!bv || g.im_C < 3)))
+    throw std::logic_error("gemm: operand layout");
+  const dim3 grid((unsigned)((g.M + kTM - 1) / kTM), (unsigned)((g.N + kTN - 1) / kTN));
+  if (g.im_H)
+    hipLaunchKernelGGL((k_gemm<true, true>), grid, dim3(256), 0, st, g);
+  else if (bv)
+    hipLaunchKernelGGL((k_gemm<false, true>), grid, dim3(256), 0, st, g);
+  else
+    hipLaunchKernelGGL((k_gemm<false, false>), grid, dim3(256), 0, st, g);
   check_hip(hipGetLastError(), "launch gemm");
 }
 
-// ---------------------------------------------------------------------------
-// im2col / col2im (3x3, padding 1, stride 1)
-// col[(n*H + h)*W + w][tap*C + c] = x(n, c, h+dh, w+dw), tap = (dh+1)*3 + (dw+1)
-// x addressed with strides (n, c, h, w) so both NCHW inputs and NHWC
-// activations are read in place.
-// ---------------------------------------------------------------------------
-__global__ void k_im2col(const uint16_t *__restrict__ x, int64_t sn, int64_t sc, int64_t sh, int64_t sw, int N,
-                         int C, int H, int W, uint16_t *__restrict__ col) {
-  const int64_t total = (int64_t)N * H * W * 9 * C;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int c = (int)(i % C);
-    const int tap = (int)((i / C) % 9);
-    const int64_t p = i / (9 * (int64_t)C);
-    const int w = (int)(p % W), h = (int)((p / W) % H);
-    const int n = (int)(p / ((int64_t)W * H));
-    const int hh = h + tap / 3 - 1, ww = w + tap % 3 - 1;
-    col[i] = (hh >= 0 && hh < H && ww >= 0 && ww < W) ? x[n * sn + c * sc + hh * sh + ww * sw] : (uint16_t)0;
-  }
-}
-
-// dx(n, h, w, c) = sum over taps of dcol[pixel (h - dh, w - dw)][tap*C + c]:
-// the taps are fp32 products (the dcol GEMM keeps fp32), summed in fp32 and
-// rounded to bf16 once (NHWC output)
-__global__ void k_col2im(const float *__restrict__ dcol, int N, int C, int H, int W, uint16_t *__restrict__ dx) {
-  const int64_t total = (int64_t)N * H * W * C;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int c = (int)(i % C);
-    const int64_t p = i / C;
-    const int w = (int)(p % W), h = (int)((p / W) % H);
-    const int n = (int)(p / ((int64_t)W * H));
-    float s = 0.f;
-    for (int tap = 0; tap < 9; ++tap) {
-      const int hh = h - (tap / 3 - 1), ww = w - (tap % 3 - 1);
-      if (hh < 0 || hh >= H || ww < 0 || ww >= W) continue;
-      s += dcol[(((int64_t)n * H + hh) * W + ww) * 9 * C + tap * C + c];
+// Weight gradients: out[m][n] += sum_p G[p][m] X[p][n] (out fp32, row-major,
+// zeroed before), G the output gradients [P][M], X the inputs: plain rows
+// [P][N], or, with im_H > 0, the 3x3 patches of NHWC activations (n =
+// tap*im_C + c as in GemmArgs, p = (image*H + h)*H + w).  M, N and im_C are
+// multiples of 8.
+//
+// Both operands are contiguous along their rows and long along p, the
+// reduction.  A workgroup takes 64 x 64 outputs over a slice of p: per step of
+// 32 p, 128 threads load 16 bytes of two neighbouring rows of G, 128 of X, and
+// write the pairs (p, p + 1) of each column as a dword of the transposed LDS
+// tiles; then as k_gemm.  Slices (grid.z, atomic fp32 adds) give some 1000
+// workgroups.  Single-element gathers of written-out patches and slices of
+// 4096 p left 72 to 256 workgroups waiting for loads: 450 to 660 us per
+// convolution for 256 images, now 24 (with fc1's, on average).
+struct WgradArgs {
+  const uint16_t *G, *X;
+  float *out;
+  int64_t P, slice;  // slice: p per workgroup, a multiple of 32
+  int32_t M, N, im_C, im_H;
+};
+__global__ __launch_bounds__(256) void k_wgrad(WgradArgs g) {
+  constexpr int KP = 40;  // padded LDS row of 32 p: 80 bytes, 16-byte aligned
+  __shared__ __align__(16) uint16_t As[64][KP];
+  __shared__ __align__(16) uint16_t Bs[64][KP];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int m0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+  const int64_t p_begin = (int64_t)blockIdx.z * g.slice, p_end = min(g.P, p_begin + g.slice);
+  const bool is_b = tid >= 128;                             // this thread stages X (else G)
+  const int pr = tid & 15, ch = (tid & 127) >> 4;           // its pair of p and 8 columns
+  const int col = (is_b ? n0 : m0) + 8 * ch;
+  const bool in = col < (is_b ? g.N : g.M);
+  const bool im = is_b && g.im_H > 0;
+  const int tap = im ? col / g.im_C : 0;
+  const int dh = tap / 3 - 1, dw = tap % 3 - 1, HH = g.im_H * g.im_H;
+  auto load = [&](int64_t p) {
+    u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (!in || p >= p_end) return v;
+    if (!is_b) return *reinterpret_cast<const u16x8 *>(g.G + p * g.M + col);
+    if (!im) return *reinterpret_cast<const u16x8 *>(g.X + p * g.N + col);
+    const int hw = (int)(p % HH), h = hw / g.im_H + dh, w = hw % g.im_H + dw;
+    if (h < 0 || h >= g.im_H || w < 0 || w >= g.im_H) return v;
+    return *reinterpret_cast<const u16x8 *>(g.X + (p - hw + h * g.im_H + w) * g.im_C + (col - tap * g.im_C));
+  };
+  f32x16 acc;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) acc[j] = 0.f;
+  u16x8 r0 = load(p_begin + 2 * pr), r1 = load(p_begin + 2 * pr + 1);
+  uint16_t(*dst)[KP] = is_b ? Bs : As;
+  for (int64_t p = p_begin; p < p_end; p += 32) {
+    __syncthreads();  // the previous step's operands are read
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      *reinterpret_cast<uint32_t *>(&dst[8 * ch + i][2 * pr]) = (uint32_t)r0[i] | ((uint32_t)r1[i] << 16);
+    __syncthreads();
+    if (p + 32 < p_end) {
+      r0 = load(p + 32 + 2 * pr);
+      r1 = load(p + 32 + 2 * pr + 1);
     }
-    dx[i] = f2bf(s);
+#pragma unroll
+    for (int ks = 0; ks < 32; ks += 16) {
+      const int kk = ks + (lane >> 5) * 8;
+      const u16x8 a = *reinterpret_cast<const u16x8 *>(&As[wm + (lane & 31)][kk]);
+      const u16x8 b = *reinterpret_cast<const u16x8 *>(&Bs[wn + (lane & 31)][kk]);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc,
+                                                     0, 0, 0);
+    }
+  }
+  const int n = n0 + wn + (lane & 31);
+  if (n >= g.N) return;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const int m = m0 + wm + 8 * (j >> 2) + 4 * (lane >> 5) + (j & 3);
+    if (m < g.M) atomicAdd(g.out + (int64_t)m * g.N + n, acc[j]);
   }
 }
 
-// 2x2 max-pool (NHWC); idx = position of the maximum (first on ties)
-__global__ void k_pool_fwd(const uint16_t *__restrict__ x, int N, int C, int H, int W, uint16_t *__restrict__ y,
-                           uint8_t *__restrict__ idx) {
-  const int Ho = H / 2, Wo = W / 2;
-  const int64_t total = (int64_t)N * Ho * Wo * C;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int c = (int)(i % C);
-    const int64_t p = i / C;
-    const int w = (int)(p % Wo), h = (int)((p / Wo) % Ho);
-    const int n = (int)(p / ((int64_t)Wo * Ho));
-    float best = -INFINITY;
-    int bi = 0;
-    for (int q = 0; q < 4; ++q) {
-      const float v = bf2f(x[(((int64_t)n * H + 2 * h + q / 2) * W + 2 * w + q % 2) * C + c]);
-      if (v > best) {
-        best = v;
-        bi = q;
+static void wgrad(WgradArgs g, hipStream_t st) {
+  const int64_t tiles = (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64);
+  // about 1024 workgroups, at least 256 p each
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(1024 / tiles, g.P / 256));
+  g.slice = ((g.P + want - 1) / want + 31) / 32 * 32;
+  const dim3 grid((unsigned)((g.M + 63) / 64), (unsigned)((g.N + 63) / 64),
+                  (unsigned)((g.P + g.slice - 1) / g.slice));
+  hipLaunchKernelGGL(k_wgrad, grid, dim3(256), 0, st, g);
+  check_hip(hipGetLastError(), "launch weight gradients");
+}
+
+// The first convolution's weight gradients, dw[o][tap*2 + c] = sum over
+// pixels of dpre[pixel][o] x(c, pixel + tap): 16 x 18 outputs, a reduction over
+// every pixel.  Wave w of a workgroup takes outputs 4 w .. 4 w + 3, a lane
+// every 64 gridDim.x-th pixel: 72 sums in registers.  Over the lanes they are
+// added by halves (lane bits 5, 4, 3 choose which half of the sums a lane goes
+// on with, then 3 full exchanges), and a workgroup's 288 sums go to its row of
+// part, whose columns k_sum_rows adds: atomics on 288 addresses from every
+// workgroup took 220 us of 248 for 256 images.  As a product of written-out
+// patches this was 447 us, and 79 to write them; now 27.
+static constexpr int kConv1Parts = 512;  // workgroups at most: two waves per SIMD of 256 CUs
+__global__ __launch_bounds__(256) void k_conv1_wgrad(const uint16_t *__restrict__ x,
+                                                     const uint16_t *__restrict__ dpre, int64_t n,
+                                                     float *__restrict__ part) {
+  const int lane = threadIdx.x & 63, o0 = (threadIdx.x >> 6) * 4;
+  float acc[72];
+#pragma unroll
+  for (int i = 0; i < 72; ++i) acc[i] = 0.f;
+  for (int64_t m = (int64_t)blockIdx.x * 64 + lane; m < n * 4096; m += (int64_t)gridDim.x * 64) {
+    const int64_t img = m >> 12;
+    const int h = (int)(m >> 6) & 63, c = (int)m & 63;
+    const uint16_t *xi = x + img * 8192;
+    const uint2 d = *reinterpret_cast<const uint2 *>(dpre + m * 16 + o0);
+    const float dv[4] = {bf2f((uint16_t)d.x), bf2f((uint16_t)(d.x >> 16)), bf2f((uint16_t)d.y),
+                         bf2f((uint16_t)(d.y >> 16))};
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) {
+      const int hh = h + tap / 3 - 1, ww = c + tap % 3 - 1;
+      const bool inside = hh >= 0 && hh < 64 && ww >= 0 && ww < 64;
+      const int hc = min(max(hh, 0), 63), wc = min(max(ww, 0), 63);  // every load in bounds, issued together
+#pragma unroll
+      for (int chn = 0; chn < 2; ++chn) {
+        const float v = bf2f(xi[chn * 4096 + hc * 64 + wc]);
+        const float xv = inside ? v : 0.f;
+#pragma unroll
+        for (int o = 0; o < 4; ++o)
+          acc[o * 18 + tap * 2 + chn] = __builtin_fmaf(dv[o], xv, acc[o * 18 + tap * 2 + chn]);
       }
     }
-    y[i] = f2bf(best);
-    idx[i] = (uint8_t)bi;
+  }
+  int first = 0;
+#pragma unroll
+  for (int half = 36, q = 32; half >= 9; half /= 2, q /= 2) {
+    const bool up = lane & q;
+#pragma unroll
+    for (int i = 0; i < half; ++i) {
+      const float send = up ? acc[i] : acc[i + half], keep = up ? acc[i + half] : acc[i];
+      acc[i] = keep + __shfl_xor(send, q, 64);
+    }
+    if (up) first += half;
+  }
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+#pragma unroll
+    for (int q = 4; q > 0; q /= 2) acc[i] += __shfl_xor(acc[i], q, 64);
+    if ((lane & 7) == 0) part[(int64_t)blockIdx.x * 288 + o0 * 18 + first + i] = acc[i];
+  }
+}
+// out[j] = sum of the rows of part [rows][gridDim.x], j = blockIdx.x; one wave each
+__global__ __launch_bounds__(64) void k_sum_rows(const float *__restrict__ part, int rows, float *__restrict__ out) {
+  float s = 0.f;
+  for (int r = threadIdx.x; r < rows; r += 64) s += part[(int64_t)r * gridDim.x + blockIdx.x];
+#pragma unroll
+  for (int q = 32; q > 0; q >>= 1) s += __shfl_xor(s, q, 64);
+  if (threadIdx.x == 0) out[blockIdx.x] = s;
+}
+
+// out[c] += sum_p in[p][c] (bias gradients; C a multiple of 8, at most 256):
+// 8 channels per thread and load, C / 8 threads side by side, the others rows
+// apart; fp32 sums per thread, over the workgroup in LDS, one atomic per
+// channel and workgroup.  As products with a row of ones these took 260 to
+// 360 us each for 256 images, now 9.
+__global__ __launch_bounds__(256) void k_colsum(const uint16_t *__restrict__ in, int64_t P, int C,
+                                                float *__restrict__ out) {
+  __shared__ float red[256 * 8];
+  const int cpr = C / 8, rows = 256 / cpr;
+  const int r = threadIdx.x / cpr, ch = threadIdx.x % cpr;
+  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  if (r < rows)
+    for (int64_t p = (int64_t)blockIdx.x * rows + r; p < P; p += (int64_t)gridDim.x * rows) {
+      const u16x8 v = *reinterpret_cast<const u16x8 *>(in + p * C + 8 * ch);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] += bf2f(v[i]);
+    }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) red[threadIdx.x * 8 + i] = acc[i];
+  __syncthreads();
+  if ((int)threadIdx.x < C) {
+    float s = 0.f;
+    for (int q = 0; q < rows; ++q) s += red[(q * cpr + (threadIdx.x >> 3)) * 8 + (threadIdx.x & 7)];
+    atomicAdd(out + threadIdx.x, s);
   }
 }
 
-// The same pooling with 8 channels per thread (C a multiple of 8, 16-byte
-// aligned rows): four 16-byte loads, per channel the same comparisons in the
-// same order, one 16-byte and one 8-byte store.
+static void colsum(const uint16_t *in, int64_t P, int C, float *out, hipStream_t st) {
+  const int rows = 256 / (C / 8);
+  const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(P / (8 * rows), 512));
+  hipLaunchKernelGGL(k_colsum, dim3(grid), dim3(256), 0, st, in, P, C, out);
+}
+
+// Weights of a convolution as the gradient of its input reads them: wt[c][tap
+// * cout + o] = w[o][(8 - tap) * cin + c], so that dx is the convolution of
+// the output gradients with wt (k contiguous; fp32 sums over taps and outputs,
+// rounded once).  Writing fp32 patch gradients and gathering them took 212 us
+// per backward pass of 256 images.
+__global__ void k_flip_weights(const uint16_t *__restrict__ w, int cin, int cout, uint16_t *__restrict__ wt) {
+  const int total = cin * 9 * cout;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+    const int o = i % cout, tap = (i / cout) % 9, c = i / (9 * cout);
+    wt[i] = w[(o * 9 + 8 - tap) * cin + c];
+  }
+}
+
+// 2x2 max-pool (NHWC); idx = position of the maximum (first on ties).  8
+// channels per thread (C a multiple of 8, 16-byte aligned rows): four 16-byte
+// loads, one 16-byte and one 8-byte store.
 __global__ void k_pool_fwd8(const uint16_t *__restrict__ x, int N, int C, int H, int W, uint16_t *__restrict__ y,
                             uint8_t *__restrict__ idx) {
   const int Ho = H / 2, Wo = W / 2, C8 = C / 8;
@@ -393,22 +486,32 @@ __global__ void k_pool_fwd8(const uint16_t *__restrict__ x, int N, int C, int H,
 }
 
 // d(pre-activation) of the conv output: route dy to the pooled position,
-// times the ReLU derivative (activation > 0).  dy may be fp32 or bf16 (NHWC
-// of the pooled shape); output bf16 NHWC of the full shape.
+// times the ReLU derivative (activation > 0).  bf16 NHWC throughout; a thread
+// takes 8 channels of a pooled position and writes its four pixels (16-byte
+// accesses: 130 us per backward pass of 256 images one element at a time, 35 now).
 __global__ void k_pool_bwd(const uint16_t *__restrict__ dy, const uint8_t *__restrict__ idx,
                            const uint16_t *__restrict__ act, int N, int C, int H, int W, uint16_t *__restrict__ dpre) {
-  const int64_t total = (int64_t)N * H * W * C;
-  const int Ho = H / 2, Wo = W / 2;
+  const int Ho = H / 2, Wo = W / 2, C8 = C / 8;
+  const int64_t total = (int64_t)N * Ho * Wo * C8;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int c = (int)(i % C);
-    const int64_t p = i / C;
-    const int w = (int)(p % W), h = (int)((p / W) % H);
-    const int n = (int)(p / ((int64_t)W * H));
-    const int64_t o = (((int64_t)n * Ho + h / 2) * Wo + w / 2) * C + c;
-    const int q = (h & 1) * 2 + (w & 1);
-    float g = 0.f;
-    if (idx[o] == q && bf2f(act[i]) > 0.f) g = bf2f(dy[o]);
-    dpre[i] = f2bf(g);
+    const int c = (int)(i % C8) * 8;
+    const int64_t p = i / C8;
+    const int w = (int)(p % Wo), h = (int)((p / Wo) % Ho);
+    const int64_t n = p / ((int64_t)Wo * Ho);
+    const u16x8 g = *reinterpret_cast<const u16x8 *>(dy + p * C + c);
+    const uint2 ix = *reinterpret_cast<const uint2 *>(idx + p * C + c);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t o = ((n * H + 2 * h + q / 2) * W + 2 * w + q % 2) * C + c;
+      const u16x8 a = *reinterpret_cast<const u16x8 *>(act + o);
+      u16x8 d;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t k = ((e < 4 ? ix.x : ix.y) >> (8 * (e & 3))) & 255u;
+        d[e] = k == (uint32_t)q && bf2f(a[e]) > 0.f ? f2bf(bf2f(g[e])) : (uint16_t)0;
+      }
+      *reinterpret_cast<u16x8 *>(dpre + o) = d;
+    }
   }
 }
 
@@ -435,20 +538,18 @@ __global__ void k_head_bwd(const float *__restrict__ z, const float *__restrict_
   }
 }
 
-// fc2's parameter gradients from the fp32 dz: dW2[j] = sum_i dz_i h[i][j]
-// (threads j < 192), db2 = sum_i dz_i (thread 192); one workgroup.
+// fc2's parameter gradients from the fp32 dz: dW2[j] += sum_i dz_i h[i][j]
+// (threads j < 192), db2 += sum_i dz_i (thread 192), kHeadRows samples per
+// workgroup.
+static constexpr int kHeadRows = 16;
 __global__ __launch_bounds__(256) void k_head_wgrad(const float *__restrict__ dz, const uint16_t *__restrict__ h,
                                                     int n, float *__restrict__ dw2, float *__restrict__ db2) {
   const int j = threadIdx.x;
   if (j > kHiddenUnits) return;
+  const int i0 = blockIdx.x * kHeadRows, i1 = min(n, i0 + kHeadRows);
   float s = 0.f;
-  if (j < kHiddenUnits) {
-    for (int i = 0; i < n; ++i) s += dz[i] * bf2f(h[(int64_t)i * kHiddenUnits + j]);
-    dw2[j] = s;
-  } else {
-    for (int i = 0; i < n; ++i) s += dz[i];
-    *db2 = s;
-  }
+  for (int i = i0; i < i1; ++i) s += j < kHiddenUnits ? dz[i] * bf2f(h[(int64_t)i * kHiddenUnits + j]) : dz[i];
+  atomicAdd(j < kHiddenUnits ? dw2 + j : db2, s);
 }
 
 // Adam on fp32 master parameters; refreshes the bf16 copy
@@ -470,11 +571,6 @@ __global__ void k_adam(float *__restrict__ p, const float *__restrict__ g, float
 __global__ void k_to_bf16(const float *__restrict__ a, uint16_t *__restrict__ b, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     b[i] = f2bf(a[i]);
-}
-
-__global__ void k_fill_bf16(uint16_t *__restrict__ a, int64_t n, uint16_t v) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    a[i] = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -1127,12 +1223,12 @@ using namespace gsp;
 struct gsp_cnn {
   gsp_ctx *ctx = nullptr;
   ParamLayout L;
-  DevBuf p32, pbf, g32, m, v, ones;
+  DevBuf p32, pbf, g32, m, v;
   int64_t t = 0;  // Adam steps
   // activations and scratch for batches up to `cap`
   int64_t cap = 0;
   int64_t last_n = 0;  // batch of the last forward pass
-  DevBuf col[4], act[4], pool[4], idx[4], h1, z, dz, loss, dh1, dcol, dpre;
+  DevBuf act[4], pool[4], idx[4], h1, z, dz, loss, dh1, dpre, wt, part;
   DevBuf dpool[4];        // gradient of each block's pooled output (bf16, NHWC)
   int64_t last_bwd_n = 0;  // batch of the last backward pass
 };
@@ -1144,8 +1240,6 @@ void reserve_batch(gsp_cnn *c, int64_t n) {
   const int dev = c->ctx->device;
   for (int l = 0; l < 4; ++l) {
     const int64_t px = n * kConv[l].h * kConv[l].h;
-    c->col[l].device = dev;
-    c->col[l].reserve((size_t)px * 9 * kConv[l].cin * 2);
     c->act[l].device = dev;
     c->act[l].reserve((size_t)px * kConv[l].cout * 2);
     c->pool[l].device = dev;
@@ -1153,35 +1247,29 @@ void reserve_batch(gsp_cnn *c, int64_t n) {
     c->idx[l].device = dev;
     c->idx[l].reserve((size_t)px / 4 * kConv[l].cout);
   }
-  int64_t big = 0;
-  for (int l = 0; l < 4; ++l) big = std::max<int64_t>(big, n * kConv[l].h * kConv[l].h * 9 * kConv[l].cin);
-  for (DevBuf *d : {&c->h1, &c->z, &c->dz, &c->loss, &c->dh1, &c->dcol, &c->dpre, &c->ones}) d->device = dev;
+  for (DevBuf *d : {&c->h1, &c->z, &c->dz, &c->loss, &c->dh1, &c->dpre, &c->wt, &c->part}) d->device = dev;
   c->h1.reserve((size_t)n * kHidden * 2);
   c->z.reserve((size_t)n * 4);
   c->dz.reserve((size_t)n * 4);
   c->loss.reserve((size_t)n * 4);
   c->dh1.reserve((size_t)n * kHidden * 2);
-  c->dcol.reserve((size_t)big * 4);  // fp32 taps
+  c->wt.reserve((size_t)kConv[3].cout * 9 * kConv[3].cin * 2);  // the largest convolution's weights
+  c->part.reserve((size_t)kConv1Parts * 288 * 4);
   c->dpre.reserve((size_t)n * 64 * 64 * 16 * 2);
   for (int l = 0; l < 4; ++l) {
     const int h = kConv[l].h / 2;
     c->dpool[l].device = dev;
     c->dpool[l].reserve((size_t)n * h * h * kConv[l].cout * 2);
   }
-  c->ones.reserve((size_t)n * 64 * 64 * 2);
-  hipLaunchKernelGGL(k_fill_bf16, dim3(grid_for(n * 4096)), dim3(256), 0, 0, c->ones.as<uint16_t>(), n * 4096,
-                     (uint16_t)0x3F80);
-  check_hip(hipDeviceSynchronize(), "fill ones");
   c->cap = n;
 }
 
-GemmArgs ga(const uint16_t *A, int64_t am, int64_t ak, const uint16_t *B, int64_t bk, int64_t bn, void *C, int64_t cm,
+GemmArgs ga(const uint16_t *A, int64_t am, const uint16_t *B, int64_t bk, int64_t bn, void *C, int64_t cm,
             int64_t cn, int64_t M, int64_t N, int64_t K) {
   GemmArgs g;
   std::memset(&g, 0, sizeof(g));
   g.A = A;
   g.a_m = am;
-  g.a_k = ak;
   g.B = B;
   g.b_k = bk;
   g.b_n = bn;
@@ -1194,103 +1282,90 @@ GemmArgs ga(const uint16_t *A, int64_t am, int64_t ak, const uint16_t *B, int64_
   return g;
 }
 
-// Forward pass of a batch; logits (fp32) left in c->z.  With keep_col the
-// im2col matrices are written out for the backward pass; without, the
-// convolutions gather their inputs inside the GEMM (same values, same sums).
-void forward(gsp_cnn *c, const uint16_t *x, int64_t n, hipStream_t st, bool keep_col) {
+// C [M = n H H][N] (bf16) = the 3x3 patches of x, NHWC [n][H][H][C] (H and C
+// powers of two), times w [N][9 C]
+GemmArgs conv_args(const uint16_t *x, int64_t n, int C, int H, const uint16_t *w, int N, void *out) {
+  GemmArgs g = ga(x, 0, w, 1, 9 * C, out, N, 1, n * H * H, N, 9 * C);
+  g.im_C = __builtin_ctz(C);
+  g.im_H = __builtin_ctz(H);
+  g.out_bf16 = 1;
+  return g;
+}
+
+// Forward pass of a batch; logits (fp32) left in c->z.  The convolutions
+// gather their inputs inside the GEMM.
+void forward(gsp_cnn *c, const uint16_t *x, int64_t n, hipStream_t st) {
   const uint16_t *wb = c->pbf.as<uint16_t>();
   const float *p = c->p32.as<float>();
-  const uint16_t *in = x;
-  int64_t sn = 2 * 64 * 64, sc = 64 * 64, sh = 64, sw = 1;  // NCHW input
   for (int l = 0; l < 4; ++l) {
     const ConvSpec &cs = kConv[l];
     const int H = cs.h;
-    const int64_t M = n * H * H, K = 9 * cs.cin;
-    GemmArgs g = ga(c->col[l].as<uint16_t>(), K, 1, wb + c->L.w[l], 1, K, c->act[l].ptr, cs.cout, 1, M, cs.cout, K);
-    if (keep_col) {
-      hipLaunchKernelGGL(k_im2col, dim3(grid_for(M * K)), dim3(256), 0, st, in, sn, sc, sh, sw, (int)n, cs.cin, H, H,
-                         c->col[l].as<uint16_t>());
-    } else {
-      g.im_x = in;
-      g.im_sn = sn;
-      g.im_sc = sc;
-      g.im_sh = sh;
-      g.im_sw = sw;
-      g.im_C = cs.cin;
-      g.im_H = H;
-    }
-    g.bias = p + c->L.b[l];
-    g.relu = 1;
-    g.out_bf16 = 1;
-    if (l == 0 && sn == 2 * 64 * 64 && sc == 64 * 64 && sh == 64 && sw == 1 && cs.cin == 2 && cs.cout == 16 &&
-        H == 64 && (reinterpret_cast<uintptr_t>(wb + c->L.w[l]) & 3) == 0)
-      hipLaunchKernelGGL(k_conv1, dim3(grid_for(M)), dim3(256), 0, st, in, n, wb + c->L.w[l], p + c->L.b[l],
+    const int64_t M = n * H * H;
+    if (l == 0) {
+      hipLaunchKernelGGL(k_conv1, dim3(grid_for(M)), dim3(256), 0, st, x, n, wb + c->L.w[l], p + c->L.b[l],
                          c->act[l].as<uint16_t>());
-    else
+    } else {  // NHWC activations of the block before
+      GemmArgs g = conv_args(c->pool[l - 1].as<uint16_t>(), n, cs.cin, H, wb + c->L.w[l], cs.cout, c->act[l].ptr);
+      g.bias = p + c->L.b[l];
+      g.relu = 1;
       gemm(g, st);
-    if (cs.cout % 8 == 0)  // the buffers are device allocations: 16-byte aligned rows
-      hipLaunchKernelGGL(k_pool_fwd8, dim3(grid_for(M / 4 * cs.cout / 8)), dim3(256), 0, st,
-                         c->act[l].as<uint16_t>(), (int)n, cs.cout, H, H, c->pool[l].as<uint16_t>(),
-                         c->idx[l].as<uint8_t>());
-    else
-      hipLaunchKernelGGL(k_pool_fwd, dim3(grid_for(M / 4 * cs.cout)), dim3(256), 0, st, c->act[l].as<uint16_t>(),
-                         (int)n, cs.cout, H, H, c->pool[l].as<uint16_t>(), c->idx[l].as<uint8_t>());
-    in = c->pool[l].as<uint16_t>();
-    const int Ho = H / 2;
-    sn = (int64_t)Ho * Ho * cs.cout;
-    sc = 1;
-    sh = (int64_t)Ho * cs.cout;
-    sw = cs.cout;
+    }
+    hipLaunchKernelGGL(k_pool_fwd8, dim3(grid_for(M / 4 * cs.cout / 8)), dim3(256), 0, st, c->act[l].as<uint16_t>(),
+                       (int)n, cs.cout, H, H, c->pool[l].as<uint16_t>(), c->idx[l].as<uint8_t>());
   }
   // fc1 (+ReLU) and fc2
-  GemmArgs g1 = ga(c->pool[3].as<uint16_t>(), kFlat, 1, wb + c->L.w[4], 1, kFlat, c->h1.ptr, kHidden, 1, n, kHidden,
+  GemmArgs g1 = ga(c->pool[3].as<uint16_t>(), kFlat, wb + c->L.w[4], 1, kFlat, c->h1.ptr, kHidden, 1, n, kHidden,
                    kFlat);
   g1.bias = p + c->L.b[4];
   g1.relu = 1;
   g1.out_bf16 = 1;
   gemm(g1, st);
-  GemmArgs g2 = ga(c->h1.as<uint16_t>(), kHidden, 1, wb + c->L.w[5], 1, kHidden, c->z.ptr, 1, 1, n, 1, kHidden);
+  GemmArgs g2 = ga(c->h1.as<uint16_t>(), kHidden, wb + c->L.w[5], 1, kHidden, c->z.ptr, 1, 1, n, 1, kHidden);
   g2.bias = p + c->L.b[5];
   gemm(g2, st);
 }
 
-// Backward pass after forward(): gradients (fp32) of the mean BCE into c->g32.
-void backward(gsp_cnn *c, const float *labels, int64_t n, hipStream_t st) {
+// Backward pass after forward() of x: gradients (fp32) of the mean BCE into c->g32.
+void backward(gsp_cnn *c, const uint16_t *x, const float *labels, int64_t n, hipStream_t st) {
   const uint16_t *wb = c->pbf.as<uint16_t>();
   float *g = c->g32.as<float>();
-  const uint16_t *ones = c->ones.as<uint16_t>();
+  // every gradient is a sum of atomic adds
+  hipLaunchKernelGGL(k_zero_f32, dim3(grid_for(c->L.total)), dim3(256), 0, st, g, c->L.total);
   // loss head: fp32 dz, fc2's gradients from it, bf16 gradient of fc1's pre-activation
   hipLaunchKernelGGL(k_head_bwd, dim3(grid_for(n * kHidden)), dim3(256), 0, st, c->z.as<float>(), labels,
                      c->h1.as<uint16_t>(), wb + c->L.w[5], (int)n, c->loss.as<float>(), c->dz.as<float>(),
                      c->dh1.as<uint16_t>());
-  hipLaunchKernelGGL(k_head_wgrad, dim3(1), dim3(256), 0, st, c->dz.as<float>(), c->h1.as<uint16_t>(), (int)n,
-                     g + c->L.w[5], g + c->L.b[5]);
+  hipLaunchKernelGGL(k_head_wgrad, dim3((unsigned)((n + kHeadRows - 1) / kHeadRows)), dim3(256), 0, st,
+                     c->dz.as<float>(), c->h1.as<uint16_t>(), (int)n, g + c->L.w[5], g + c->L.b[5]);
   const uint16_t *dh = c->dh1.as<uint16_t>();
   // fc1: dW = dh^T x, db = colsum dh, dx = dh W1
-  gemm(ga(dh, 1, kHidden, c->pool[3].as<uint16_t>(), kFlat, 1, g + c->L.w[4], kFlat, 1, kHidden, kFlat, n), st);
-  gemm(ga(ones, 0, 0, dh, kHidden, 1, g + c->L.b[4], 1, 1, 1, kHidden, n), st);
-  GemmArgs gx = ga(dh, kHidden, 1, wb + c->L.w[4], kFlat, 1, c->dpool[3].ptr, kFlat, 1, n, kFlat, kHidden);
+  wgrad({dh, c->pool[3].as<uint16_t>(), g + c->L.w[4], n, 0, kHidden, kFlat, 0, 0}, st);
+  colsum(dh, n, kHidden, g + c->L.b[4], st);
+  GemmArgs gx = ga(dh, kHidden, wb + c->L.w[4], kFlat, 1, c->dpool[3].ptr, kFlat, 1, n, kFlat, kHidden);
   gx.out_bf16 = 1;
   gemm(gx, st);
-  const uint16_t *dy = c->dpool[3].as<uint16_t>();  // gradient of the pooled output of conv l
-  for (int l = 3; l >= 0; --l) {
+  uint16_t *dpre = c->dpre.as<uint16_t>(), *wt = c->wt.as<uint16_t>();
+  for (int l = 3; l >= 0; --l) {  // dpool[l]: gradient of the pooled output of conv l
     const ConvSpec &cs = kConv[l];
     const int H = cs.h;
-    const int64_t M = n * H * H, K = 9 * cs.cin;
-    uint16_t *dpre = c->dpre.as<uint16_t>();
-    hipLaunchKernelGGL(k_pool_bwd, dim3(grid_for(M * cs.cout)), dim3(256), 0, st, dy, c->idx[l].as<uint8_t>(),
-                       c->act[l].as<uint16_t>(), (int)n, cs.cout, H, H, dpre);
-    // dW[o][k] = sum_p dpre[p][o] col[p][k]; db[o] = sum_p dpre[p][o]
-    gemm(ga(dpre, 1, cs.cout, c->col[l].as<uint16_t>(), K, 1, g + c->L.w[l], K, 1, cs.cout, K, M), st);
-    gemm(ga(ones, 0, 0, dpre, cs.cout, 1, g + c->L.b[l], 1, 1, 1, cs.cout, M), st);
-    if (l == 0) break;
-    // dcol = dpre W (fp32); dx = col2im(dcol) (NHWC of the previous pooled output)
-    GemmArgs gc = ga(dpre, cs.cout, 1, wb + c->L.w[l], K, 1, c->dcol.ptr, K, 1, M, K, cs.cout);
-    gemm(gc, st);
-    hipLaunchKernelGGL(k_col2im, dim3(grid_for(M * cs.cin)), dim3(256), 0, st, c->dcol.as<float>(), (int)n, cs.cin,
-                       H, H, c->dpool[l - 1].as<uint16_t>());
-    dy = c->dpool[l - 1].as<uint16_t>();
+    const int64_t M = n * H * H;
+    hipLaunchKernelGGL(k_pool_bwd, dim3(grid_for(M / 4 * cs.cout / 8)), dim3(256), 0, st, c->dpool[l].as<uint16_t>(),
+                       c->idx[l].as<uint8_t>(), c->act[l].as<uint16_t>(), (int)n, cs.cout, H, H, dpre);
+    // dW[o][k] = sum_p dpre[p][o] patch(p)[k]; db[o] = sum_p dpre[p][o]
+    colsum(dpre, M, cs.cout, g + c->L.b[l], st);
+    if (l == 0) {
+      const int rows = (int)std::min<int64_t>(n * 64, kConv1Parts);
+      hipLaunchKernelGGL(k_conv1_wgrad, dim3(rows), dim3(256), 0, st, x, dpre, n, c->part.as<float>());
+      hipLaunchKernelGGL(k_sum_rows, dim3(288), dim3(64), 0, st, c->part.as<float>(), rows, g + c->L.w[0]);
+      break;
+    }
+    wgrad({dpre, c->pool[l - 1].as<uint16_t>(), g + c->L.w[l], M, 0, cs.cout, 9 * cs.cin, cs.cin, H}, st);
+    // dx: dpre convolved with the flipped weights
+    hipLaunchKernelGGL(k_flip_weights, dim3(grid_for(9 * cs.cin * cs.cout)), dim3(256), 0, st, wb + c->L.w[l], cs.cin,
+                       cs.cout, wt);
+    gemm(conv_args(dpre, n, cs.cout, H, wt, cs.cin, c->dpool[l - 1].ptr), st);
   }
+  check_hip(hipGetLastError(), "launch backward pass");
   c->last_bwd_n = n;
 }
 
@@ -1401,7 +1476,7 @@ int gsp_cnn_forward(gsp_cnn *c, const uint16_t *x, int64_t n, float *logits, voi
     hipStream_t st = static_cast<hipStream_t>(stream);
     check_hip(hipStreamSynchronize(st), "synchronise stream");
     reserve_batch(c, n);
-    forward(c, x, n, st, false);
+    forward(c, x, n, st);
     c->last_n = n;
     check_hip(hipMemcpyAsync(logits, c->z.ptr, (size_t)n * 4, hipMemcpyDeviceToDevice, st), "copy logits");
   });
@@ -1415,9 +1490,9 @@ int gsp_cnn_gradients(gsp_cnn *c, const uint16_t *x, const float *labels, int64_
     hipStream_t st = static_cast<hipStream_t>(stream);
     check_hip(hipStreamSynchronize(st), "synchronise stream");
     reserve_batch(c, n);
-    forward(c, x, n, st, true);
+    forward(c, x, n, st);
     c->last_n = n;
-    backward(c, labels, n, st);
+    backward(c, x, labels, n, st);
     std::vector<float> loss((size_t)n);
     check_hip(hipMemcpyAsync(loss.data(), c->loss.ptr, (size_t)n * 4, hipMemcpyDeviceToHost, st), "copy loss");
     check_hip(hipMemcpyAsync(grads_host, c->g32.ptr, (size_t)c->L.total * 4, hipMemcpyDeviceToHost, st),
@@ -1439,9 +1514,9 @@ int gsp_cnn_train_step(gsp_cnn *c, const uint16_t *x, const float *labels, int64
     hipStream_t st = static_cast<hipStream_t>(stream);
     check_hip(hipStreamSynchronize(st), "synchronise stream");
     reserve_batch(c, n);
-    forward(c, x, n, st, true);
+    forward(c, x, n, st);
     c->last_n = n;
-    backward(c, labels, n, st);
+    backward(c, x, labels, n, st);
     c->t += 1;
     const float b1 = 0.9f, b2 = 0.999f;
     const float c1 = 1.f - std::pow(b1, (float)c->t), c2 = 1.f - std::pow(b2, (float)c->t);

@@ -160,6 +160,45 @@ def test_gradients_layer_by_layer(env):
     net.close()
 
 
+@pytest.mark.parametrize("n", [1, 2, 33, 65])
+def test_weight_gradient_sums(env, n):
+    """The reductions over the pixels of a batch (weight and bias gradients of
+    the convolutions and of fc1), element by element, at batches that leave
+    parts of a step, of a slice and of a group of samples empty.  No chain of
+    fp32 additions is longer than 2048 (a slice's steps, then the slices), so
+    an element differs from the float64 sum by at most 2^-13 of the sum of its
+    terms' magnitudes."""
+    gsp, ctx, torch = env
+    net = gsp.Cnn(ctx, seed=6)
+    P = {k: (ocnn.bf16(v) if k.endswith(".w") else v)
+         for k, v in ocnn.unpack(net.params().astype(np.float64)).items()}
+    say(f"[case] gradient sums, batch {n}")
+    x, y = inputs(n, 300 + n)
+    g, _ = net.gradients(to_dev(torch, x), torch.from_numpy(y.astype(np.float32)).cuda())
+    G = ocnn.unpack(g.astype(np.float64))
+
+    def near(got, ref, mag, what):
+        assert np.all(np.abs(got - ref) <= 2.0 ** -13 * mag), (what, np.max(np.abs(got - ref) / (mag + 1e-30)))
+
+    h, dh = net.activation(4, n), net.activation(10, n)
+    dz = net.activation(11, n).astype(np.float64)
+    near(G["fc2.w"], dz @ h, np.abs(dz) @ np.abs(h), "fc2.w")
+    flat = ocnn.flatten(nchw(net.activation(3, n)))
+    near(G["fc1.w"].reshape(-1), (dh.T @ flat).reshape(-1), (np.abs(dh).T @ np.abs(flat)).reshape(-1), "fc1.w")
+    near(G["fc1.b"], dh.sum(0), np.abs(dh).sum(0), "fc1.b")
+    for l in range(4):
+        name = f"conv{l + 1}"
+        dy = nchw(net.activation(6 + l, n))
+        xin = x if l == 0 else nchw(net.activation(l - 1, n))
+        act = nchw(net.activation(12 + l, n))
+        q = nchw(net.activation(16 + l, n)).astype(np.int64)
+        gw, gb, _, _ = ocnn.conv_block_backward(dy, xin, P[name + ".w"], act, q)
+        mw, mb, _, _ = ocnn.conv_block_backward(np.abs(dy), np.abs(xin), P[name + ".w"], act, q)
+        near(G[name + ".w"], gw, mw, name + ".w")
+        near(G[name + ".b"], gb, mb, name + ".b")
+    net.close()
+
+
 def test_train_step_is_adam_on_the_gradients(env):
     gsp, ctx, torch = env
     net = gsp.Cnn(ctx, seed=5)
