@@ -6,13 +6,14 @@
 //   -> conv3x3(32->64)+ReLU+maxpool2 -> conv3x3(64->128)+ReLU+maxpool2
 //   -> flatten (h, w, c) 2048 -> FC 192 + ReLU -> FC 1 -> logit
 //   loss: binary cross-entropy with logits (mean over the batch); Adam.
-// Every convolution and fully connected product but the first, forward and
-// backward, runs on the gfx950 BF16 matrix cores (v_mfma_f32_32x32x16_bf16):
-// k_gemm for the forward passes and the gradients of the inputs (a
-// convolution of the output gradients with the flipped kernel), its operands
-// gathered from the activations (implicit im2col), bias and ReLU in the
-// epilogue; k_wgrad for the gradients of the weights, whose operands run along
-// their rows.  The first convolution (2 channels) has kernels of its own.
+// Every product runs on the gfx950 matrix cores, BF16 but for the first
+// convolution's (FP32): the convolution blocks forward, fused with their pools,
+// in k_conv1_pool and k_conv_pool; the fully connected layers and the gradients
+// of the inputs (a convolution of the output gradients with the flipped
+// kernel) in k_gemm, operands gathered from the activations (implicit im2col)
+// and bias and ReLU in the epilogue; the gradients of the weights, whose
+// operands run along their rows, in k_wgrad, the first convolution's (18
+// inputs) in k_conv1_wgrad.
 #include <cmath>
 #include <cstring>
 #include <fstream>
@@ -86,8 +87,7 @@ typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 // transposed in LDS ([n][k]) so that both MFMA operands are 16-byte LDS reads.
 // The next k step's operands are loaded into registers while the current one
 // is multiplied.  The forms are template arguments: chosen inside one kernel
-// they cost registers (4 to 7 waves per SIMD in place of 8); conv2 to conv4 of
-// 6754 images took 953 us, now 832.
+// they cost registers (4 to 7 waves per SIMD in place of 8).
 template <bool IM, bool BV>
 __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
   __shared__ __align__(16) uint16_t As[kTM][kTP];
@@ -166,62 +166,6 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
       static_cast<uint16_t *>(g.C)[o] = f2bf(v);
     else
       static_cast<float *>(g.C)[o] = v;
-  }
-}
-
-// The first convolution (2 input channels, 16 outputs, 3x3, padding 1, on
-// 64 x 64 images) directly: as a GEMM it is N = 16, K = 18, a quarter of a
-// 64 x 64 tile with a gather of single elements, so one thread per output
-// pixel instead: its 18 inputs (NCHW bf16) as floats, 16 dot products of
-// exact bf16 x bf16 products summed in fp32 (the weights, [16][18] bf16 with
-// k = tap * 2 + channel, are uniform and come as scalar operands), bias,
-// ReLU, and the pixel's 16 outputs (NHWC bf16).
-__global__ __launch_bounds__(256) void k_conv1(const uint16_t *__restrict__ x, int64_t n,
-                                               const uint16_t *__restrict__ w, const float *__restrict__ bias,
-                                               uint16_t *__restrict__ act) {
-  // read-only in this kernel: through the constant address space the
-  // uniform weight loads become scalar loads (w is 4-byte aligned)
-  typedef const __attribute__((address_space(4))) uint32_t cu32;
-  cu32 *wc = (cu32 *)w;
-  const int64_t total = n * 4096;
-  for (int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; m < total; m += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t img = m >> 12;
-    const int h = (int)(m >> 6) & 63, c = (int)m & 63;
-    const uint16_t *xi = x + img * 8192;
-    float xin[18];
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-      const int hh = h + tap / 3 - 1, ww = c + tap % 3 - 1;
-      const bool in = hh >= 0 && hh < 64 && ww >= 0 && ww < 64;
-      const int hc = min(max(hh, 0), 63), wc = min(max(ww, 0), 63);  // every load in bounds, issued together
-#pragma unroll
-      for (int ch = 0; ch < 2; ++ch) {
-        const float v = bf2f(xi[ch * 4096 + hc * 64 + wc]);
-        xin[tap * 2 + ch] = in ? v : 0.f;
-      }
-    }
-    // four outputs at a time (36 weight dwords in scalar registers), an
-    // 8-byte store each
-#pragma unroll 1
-    for (int o0 = 0; o0 < 16; o0 += 4) {
-      uint32_t pk[2];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int o = o0 + q;
-        float acc = 0.f;
-#pragma unroll
-        for (int k = 0; k < 18; k += 2) {
-          const uint32_t pr = wc[(o * 18 + k) >> 1];  // weights k, k + 1 (bf16, low half first)
-          acc = __builtin_fmaf(xin[k], __builtin_bit_cast(float, pr << 16), acc);
-          acc = __builtin_fmaf(xin[k + 1], __builtin_bit_cast(float, pr & 0xFFFF0000u), acc);
-        }
-        float v = acc + bias[o];
-        v = v > 0.f ? v : 0.f;
-        const uint32_t b = f2bf(v);
-        pk[q >> 1] = (q & 1) ? (pk[q >> 1] | (b << 16)) : b;
-      }
-      *reinterpret_cast<uint2 *>(act + m * 16 + o0) = make_uint2(pk[0], pk[1]);
-    }
   }
 }
 
@@ -446,42 +390,236 @@ __global__ void k_flip_weights(const uint16_t *__restrict__ w, int cin, int cout
   }
 }
 
-// 2x2 max-pool (NHWC); idx = position of the maximum (first on ties).  8
-// channels per thread (C a multiple of 8, 16-byte aligned rows): four 16-byte
-// loads, one 16-byte and one 8-byte store.
-__global__ void k_pool_fwd8(const uint16_t *__restrict__ x, int N, int C, int H, int W, uint16_t *__restrict__ y,
-                            uint8_t *__restrict__ idx) {
-  const int Ho = H / 2, Wo = W / 2, C8 = C / 8;
-  const int64_t total = (int64_t)N * Ho * Wo * C8;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int c = (int)(i % C8) * 8;
-    const int64_t p = i / C8;
-    const int w = (int)(p % Wo), h = (int)((p / Wo) % Ho);
-    const int n = (int)(p / ((int64_t)Wo * Ho));
-    uint4 v[4];
+// --- convolution blocks: 3x3 convolution (padding 1), bias, ReLU, 2x2 max-pool ---
+//
+// One kernel per block writes the ReLU output (NHWC), the pooled output and the
+// position of each maximum (first on ties).  The matrix product is taken as
+// D[channel][pixel], its pixels in the order of the 2x2 squares: four
+// neighbouring lanes hold a square, each several consecutive channels of its
+// pixel, so that the ReLU outputs go out as 8- or 16-byte stores and the pool
+// is a maximum over neighbouring lanes in registers.  A workgroup keeps its
+// weights in registers (each wave 32 channels; conv1 all 16) and goes from
+// image to image: the image's input, with a border of zeros, in LDS, the
+// next one's loads in flight while it is multiplied.
+//
+// What bounds it: the bytes of the three outputs and the input.  6754 images:
+// 1.33, 0.83, 0.41 and 0.21 GB in 342, 185, 104 and 79 us (3.9, 4.5, 4.0 and 2.7
+// TB/s; a large copy moves 4.6), where separate kernels, the convolutions as
+// general products with implicit im2col, took 646, 654, 279 and 205 us.
+
+// ReLU output of channels 2i, 2i + 1 -> packed bf16 (round to nearest even)
+__device__ inline uint32_t relu_pack(float a, float b) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  bf16x2 v;
+  v[0] = (__bf16)(a > 0.f ? a : 0.f);
+  v[1] = (__bf16)(b > 0.f ? b : 0.f);
+  return __builtin_bit_cast(uint32_t, v);
+}
+// Maximum over the 4 lanes of a square, 16 keys per lane: key = the bf16 value
+// (not negative: ordered as an integer) above 3 - position, so that the first
+// of equal values wins.  Each exchange halves the keys a lane goes on with:
+// lane s ends with keys 8 (s & 1) + 4 (s >> 1) .. + 3 in r.
+__device__ inline void pool_keys(const uint32_t (&key)[16], int s, uint32_t (&r)[4]) {
+  uint32_t m[8];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      v[q] = *reinterpret_cast<const uint4 *>(x + (((int64_t)n * H + 2 * h + q / 2) * W + 2 * w + q % 2) * C + c);
-    uint32_t yo[4], io[2] = {0, 0};
+  for (int i = 0; i < 8; ++i) {
+    const uint32_t send = (s & 1) ? key[i] : key[8 + i], keep = (s & 1) ? key[8 + i] : key[i];
+    m[i] = max(keep, (uint32_t)__builtin_amdgcn_mov_dpp((int)send, 0xB1, 0xF, 0xF, true));  // lane ^ 1
+  }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      float best = -INFINITY;
-      int bi = 0;
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t send = (s & 2) ? m[i] : m[4 + i], keep = (s & 2) ? m[4 + i] : m[i];
+    r[i] = max(keep, (uint32_t)__builtin_amdgcn_mov_dpp((int)send, 0x4E, 0xF, 0xF, true));  // lane ^ 2
+  }
+}
+// four keys -> 4 bf16 values and 4 position bytes
+__device__ inline void store_pooled(const uint32_t (&r)[4], uint16_t *pool, uint8_t *idx) {
+  *reinterpret_cast<uint2 *>(pool) =
+      make_uint2((r[0] >> 16) | (r[1] & 0xFFFF0000u), (r[2] >> 16) | (r[3] & 0xFFFF0000u));
+  *reinterpret_cast<uint32_t *>(idx) =
+      0x03030303u - ((r[0] & 3u) | ((r[1] & 3u) << 8) | ((r[2] & 3u) << 16) | ((r[3] & 3u) << 24));
+}
+
+// Blocks 2 to 4: CI input channels (NHWC), CO outputs, H x H pixels.  Wave w
+// takes channels 32 (w % (CO / 32)) .. + 31 and, of the image's tiles of 32
+// pixels (2 rows of 16 columns, or 4 of 8), every (4 / (CO / 32))-th.  Rows of
+// the 32 x 32 x 16 product are channels in the order that leaves each lane 16
+// consecutive ones.  The LDS image is in chunks of 8 channels (16 bytes),
+// permuted within a pixel by its column, the pitch of a row chosen with it, so
+// that any 16 consecutive lanes read 16 different 16-byte columns of the banks.
+template <int CI, int CO, int H>
+__global__ __launch_bounds__(256, CI == 64 ? 2 : CI == 32 ? 3 : 4) void k_conv_pool(const uint16_t *__restrict__ x, int64_t n,
+                                                                    const uint16_t *__restrict__ w,
+                                                                    const float *__restrict__ bias,
+                                                                    uint16_t *__restrict__ act,
+                                                                    uint16_t *__restrict__ pool,
+                                                                    uint8_t *__restrict__ idx) {
+  constexpr int G = CI / 8;                                  // 16-byte chunks per pixel
+  constexpr int RS = (H + 2) * G + (CI == 32 ? 2 : 4);       // row pitch in chunks: 72, 74, 84
+  constexpr int NT = CO / 32, PG = 4 / NT;                   // channel tiles, waves per channel tile
+  constexpr int TW = H < 16 ? H : 16, TH = 32 / TW;          // pixel tile
+  constexpr int TPR = H / TW, TILES = H * H / 32 / PG;       // tiles side by side; tiles per wave
+  constexpr int KS = CI / 16;                                // product steps per tap
+  constexpr int ST = H * H * G / 256;                        // chunks staged per thread
+  constexpr int SWM = CI == 64 ? 3 : 1, SWS = CI == 64 ? 1 : 2;
+  __shared__ __align__(16) u16x8 img[(H + 2) * RS];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int half = lane >> 5, s = lane & 3, quad = (lane & 31) >> 2;
+  const int ct = wave % NT, pg = wave / NT;
+  const int px = 2 * (quad % (TW / 2)) + (s & 1), py = 2 * (quad / (TW / 2)) + (s >> 1);  // pixel in a tile
+  for (int i = tid; i < (H + 2) * RS; i += 256) img[i] = u16x8{0, 0, 0, 0, 0, 0, 0, 0};
+
+  // weights: row r = 8 g + 4 h + i of the product is channel 16 h + 4 g + i
+  const int r = lane & 31, ch = ct * 32 + 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3);
+  bf16x8 wt[9 * KS];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint32_t wd = (&v[q].x)[e >> 1];
-        const float f = bf2f((uint16_t)((e & 1) ? wd >> 16 : wd & 0xFFFFu));
-        if (f > best) {
-          best = f;
-          bi = q;
-        }
-      }
-      const uint32_t b = f2bf(best);
-      yo[e >> 1] = (e & 1) ? (yo[e >> 1] | (b << 16)) : b;
-      io[e >> 2] |= (uint32_t)bi << (8 * (e & 3));
+  for (int k = 0; k < 9 * KS; ++k)
+    wt[k] = __builtin_bit_cast(
+        bf16x8, *reinterpret_cast<const u16x8 *>(w + (int64_t)ch * 9 * CI + k * 16 + half * 8));
+  float b[16];
+#pragma unroll
+  for (int j = 0; j < 16; ++j) b[j] = bias[ct * 32 + 16 * half + j];
+
+  // this lane's chunk of the window's columns (px, px + 1, px + 2 of the
+  // bordered image) at the product steps whose chunk differs in the permuted bits
+  constexpr int KV = CI == 64 ? 2 : 1;
+  int base[3][KV];
+#pragma unroll
+  for (int d = 0; d < 3; ++d)
+#pragma unroll
+    for (int v = 0; v < KV; ++v) {
+      const int sw = ((px + d) >> SWS) & SWM;
+      base[d][v] = py * RS + (px + d) * G + ((2 * v + half) ^ sw);
     }
-    *reinterpret_cast<uint4 *>(y + p * C + c) = make_uint4(yo[0], yo[1], yo[2], yo[3]);
-    *reinterpret_cast<uint2 *>(idx + p * C + c) = make_uint2(io[0], io[1]);
+  // a wave's tiles differ by whole rows, or by 16 columns: both leave sw as it is
+  u16x8 st[ST];
+  const u16x8 *xg = reinterpret_cast<const u16x8 *>(x);
+  if (blockIdx.x < n)
+#pragma unroll
+    for (int j = 0; j < ST; ++j) st[j] = xg[(int64_t)blockIdx.x * (H * H * G) + j * 256 + tid];
+  for (int64_t m = blockIdx.x; m < n; m += gridDim.x) {
+    __syncthreads();  // the previous image is read (first: the border is zero)
+#pragma unroll
+    for (int j = 0; j < ST; ++j) {
+      const int i = j * 256 + tid, p = i / G, col = p % H + 1;
+      img[(p / H + 1) * RS + col * G + ((i % G) ^ ((col >> SWS) & SWM))] = st[j];
+    }
+    __syncthreads();
+    if (m + gridDim.x < n)
+#pragma unroll
+      for (int j = 0; j < ST; ++j) st[j] = xg[(m + gridDim.x) * (H * H * G) + j * 256 + tid];
+#pragma unroll 1
+    for (int q = 0; q < TILES; ++q) {
+      const int tile = q * PG + pg, ty = tile / TPR * TH, tx = tile % TPR * TW;
+      const int off = ty * RS + tx * G;
+      f32x16 acc;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) acc[j] = 0.f;
+#pragma unroll
+      for (int k = 0; k < 9 * KS; ++k) {
+        const int tap = k / KS, ks = k % KS;
+        const u16x8 v = img[base[tap % 3][ks % KV] + off + (tap / 3) * RS + 2 * (ks - ks % KV)];
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wt[k], __builtin_bit_cast(bf16x8, v), acc, 0, 0, 0);
+      }
+      uint32_t pk[8], key[16], top[4];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        pk[j] = relu_pack(acc[2 * j] + b[2 * j], acc[2 * j + 1] + b[2 * j + 1]);
+        key[2 * j] = (pk[j] << 16) | (uint32_t)(3 - s);
+        key[2 * j + 1] = (pk[j] & 0xFFFF0000u) | (uint32_t)(3 - s);
+      }
+      const int yy = ty + py, xx = tx + px;
+      uint4 *ao = reinterpret_cast<uint4 *>(act + ((m * H + yy) * H + xx) * CO + ct * 32 + 16 * half);
+      ao[0] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+      ao[1] = make_uint4(pk[4], pk[5], pk[6], pk[7]);
+      pool_keys(key, s, top);
+      const int64_t po = ((m * (H / 2) + yy / 2) * (H / 2) + xx / 2) * CO + ct * 32 + 16 * half + 8 * (s & 1) +
+                         4 * (s >> 1);
+      store_pooled(top, pool + po, idx + po);
+    }
+  }
+}
+
+// Block 1: 2 input channels (NCHW), 16 outputs, 64 x 64 pixels: 18 products of
+// K = 1 (v_mfma_f32_16x16x1f32: 4 blocks of 16 channels x 16 pixels, float
+// operands), each one fused multiply-add per output, so that a sum runs over
+// taps and channels in order as scalar code would have it: the 18 terms in one
+// bf16 product round differently, and a flipped rounding of a bf16 output
+// travels through the network (logits 3e-4 apart).  Twice the rate of fused
+// multiply-adds on the vector units, which are left to the epilogue.  A wave
+// takes 2 rows of 32 pixels, a block 2 rows of 8; the image is in LDS as
+// floats, rows 16 dwords apart in the banks (a half wave reads 2 rows of 16).
+// After the pool each lane stores 4 channels of one square.  AL: x is 16-byte
+// aligned (else element loads).
+template <bool AL>
+__global__ __launch_bounds__(256) void k_conv1_pool(const uint16_t *__restrict__ x, int64_t n,
+                                                    const uint16_t *__restrict__ w, const float *__restrict__ bias,
+                                                    uint16_t *__restrict__ act, uint16_t *__restrict__ pool,
+                                                    uint8_t *__restrict__ idx) {
+  constexpr int RD = 80, PD = 66 * RD;  // rows of 8 border, 64, 8 border elements; 66 a channel
+  __shared__ __align__(16) float img[2 * PD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int kg = lane >> 4, s = lane & 3, quad = (lane & 15) >> 2;
+  const int px = 2 * quad + (s & 1), py = s >> 1;
+  for (int i = tid; i < 2 * PD; i += 256) img[i] = 0.f;
+
+  float wt[18], b[4];
+#pragma unroll
+  for (int k = 0; k < 18; ++k) wt[k] = bf2f(w[(lane & 15) * 18 + k]);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) b[j] = bias[4 * kg + j];
+  const int base = py * RD + 8 * kg + px + 7;  // window of the pixel this lane brings to the product
+
+  u16x8 st[4];  // chunk i of an image: channel i >> 9, row (i >> 3) & 63, columns 8 (i & 7) ..
+  auto load = [&](int64_t m) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint16_t *p = x + m * 8192 + (j * 256 + tid) * 8;
+      if (AL)
+        st[j] = *reinterpret_cast<const u16x8 *>(p);
+      else
+#pragma unroll
+        for (int e = 0; e < 8; ++e) st[j][e] = p[e];
+    }
+  };
+  if (blockIdx.x < n) load(blockIdx.x);
+  for (int64_t m = blockIdx.x; m < n; m += gridDim.x) {
+    __syncthreads();  // the previous image is read (first: the border is zero)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int i = j * 256 + tid;
+      float *d = &img[(i >> 9) * PD + (((i >> 3) & 63) + 1) * RD + 8 + 8 * (i & 7)];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) d[e] = bf2f(st[j][e]);
+    }
+    __syncthreads();
+    if (m + gridDim.x < n) load(m + gridDim.x);
+#pragma unroll 1
+    for (int q = 0; q < 16; ++q) {
+      const int g = q * 4 + wave, y = 2 * (g >> 1), x0 = 32 * (g & 1);
+      const float *p = img + base + y * RD + x0;
+      f32x16 acc;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) acc[j] = 0.f;
+#pragma unroll
+      for (int k = 0; k < 18; ++k)
+        acc = __builtin_amdgcn_mfma_f32_16x16x1f32(wt[k], p[(k & 1) * PD + (k / 6) * RD + k / 2 % 3], acc, 0, 0, 0);
+      uint32_t key[16], top[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {  // block t: channels 4 kg .. + 3 of pixel lane % 16
+        uint2 o;
+        o.x = relu_pack(acc[4 * t] + b[0], acc[4 * t + 1] + b[1]);
+        o.y = relu_pack(acc[4 * t + 2] + b[2], acc[4 * t + 3] + b[3]);
+        *reinterpret_cast<uint2 *>(act + ((m * 64 + y + py) * 64 + x0 + 8 * t + px) * 16 + 4 * kg) = o;
+        key[4 * t] = (o.x << 16) | (uint32_t)(3 - s);
+        key[4 * t + 1] = (o.x & 0xFFFF0000u) | (uint32_t)(3 - s);
+        key[4 * t + 2] = (o.y << 16) | (uint32_t)(3 - s);
+        key[4 * t + 3] = (o.y & 0xFFFF0000u) | (uint32_t)(3 - s);
+      }
+      pool_keys(key, s, top);  // of block 2 (s & 1) + (s >> 1)
+      const int64_t po = ((m * 32 + y / 2) * 32 + x0 / 2 + 4 * (2 * (s & 1) + (s >> 1)) + quad) * 16 + 4 * kg;
+      store_pooled(top, pool + po, idx + po);
+    }
   }
 }
 
@@ -1292,27 +1430,32 @@ GemmArgs conv_args(const uint16_t *x, int64_t n, int C, int H, const uint16_t *w
   return g;
 }
 
-// Forward pass of a batch; logits (fp32) left in c->z.  The convolutions
-// gather their inputs inside the GEMM.
+template <int CI, int CO, int H>
+void conv_block(gsp_cnn *c, int l, int64_t n, hipStream_t st) {
+  // as many workgroups as are resident (LDS, and for the widest the registers
+  // of its weights), each keeps its weights over its images
+  const unsigned grid = (unsigned)std::min<int64_t>(n, 256 * (CI == 64 ? 2 : CI == 32 ? 3 : 4));
+  hipLaunchKernelGGL((k_conv_pool<CI, CO, H>), dim3(grid), dim3(256), 0, st, c->pool[l - 1].as<uint16_t>(), n,
+                     c->pbf.as<uint16_t>() + c->L.w[l], c->p32.as<float>() + c->L.b[l], c->act[l].as<uint16_t>(),
+                     c->pool[l].as<uint16_t>(), c->idx[l].as<uint8_t>());
+  check_hip(hipGetLastError(), "launch convolution block");
+}
+
+// Forward pass of a batch; logits (fp32) left in c->z.
 void forward(gsp_cnn *c, const uint16_t *x, int64_t n, hipStream_t st) {
   const uint16_t *wb = c->pbf.as<uint16_t>();
   const float *p = c->p32.as<float>();
-  for (int l = 0; l < 4; ++l) {
-    const ConvSpec &cs = kConv[l];
-    const int H = cs.h;
-    const int64_t M = n * H * H;
-    if (l == 0) {
-      hipLaunchKernelGGL(k_conv1, dim3(grid_for(M)), dim3(256), 0, st, x, n, wb + c->L.w[l], p + c->L.b[l],
-                         c->act[l].as<uint16_t>());
-    } else {  // NHWC activations of the block before
-      GemmArgs g = conv_args(c->pool[l - 1].as<uint16_t>(), n, cs.cin, H, wb + c->L.w[l], cs.cout, c->act[l].ptr);
-      g.bias = p + c->L.b[l];
-      g.relu = 1;
-      gemm(g, st);
-    }
-    hipLaunchKernelGGL(k_pool_fwd8, dim3(grid_for(M / 4 * cs.cout / 8)), dim3(256), 0, st, c->act[l].as<uint16_t>(),
-                       (int)n, cs.cout, H, H, c->pool[l].as<uint16_t>(), c->idx[l].as<uint8_t>());
-  }
+  const dim3 grid1((unsigned)std::min<int64_t>(n, 256 * 3));
+  if ((reinterpret_cast<uintptr_t>(x) & 15) == 0)
+    hipLaunchKernelGGL(k_conv1_pool<true>, grid1, dim3(256), 0, st, x, n, wb + c->L.w[0], p + c->L.b[0],
+                       c->act[0].as<uint16_t>(), c->pool[0].as<uint16_t>(), c->idx[0].as<uint8_t>());
+  else
+    hipLaunchKernelGGL(k_conv1_pool<false>, grid1, dim3(256), 0, st, x, n, wb + c->L.w[0], p + c->L.b[0],
+                       c->act[0].as<uint16_t>(), c->pool[0].as<uint16_t>(), c->idx[0].as<uint8_t>());
+  check_hip(hipGetLastError(), "launch first convolution block");
+  conv_block<16, 32, 32>(c, 1, n, st);
+  conv_block<32, 64, 16>(c, 2, n, st);
+  conv_block<64, 128, 8>(c, 3, n, st);
   // fc1 (+ReLU) and fc2
   GemmArgs g1 = ga(c->pool[3].as<uint16_t>(), kFlat, wb + c->L.w[4], 1, kFlat, c->h1.ptr, kHidden, 1, n, kHidden,
                    kFlat);

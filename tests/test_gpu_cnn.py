@@ -98,6 +98,36 @@ def test_forward_layer_by_layer(env):
     net.close()
 
 
+def test_forward_many_images_and_unaligned_input(env):
+    """Every image of a batch larger than the resident workgroups goes as it
+    goes alone (bit for bit: a value's sums do not depend on the batch), also
+    from an input that is only 2-byte aligned; an infinity reaches no pixel
+    outside its 3x3 neighbourhood."""
+    gsp, ctx, torch = env
+    net = gsp.Cnn(ctx, seed=7)
+    n, part = 1411, 37
+    x, _ = inputs(part, 400)
+    xd = to_dev(torch, x)
+    rows = torch.arange(n, device="cuda:0") % part
+    big = torch.empty(n * 8192 + 1, dtype=torch.int16, device="cuda:0")[1:].view(n, 2, 64, 64)
+    big.copy_(xd[rows])
+    which = [0, 1, 2, 3, 4, 5] + list(range(12, 20))
+    net.forward(xd)
+    small = {k: net.activation(k, part) for k in which}
+    say(f"[case] forward, batch {n}, 2-byte aligned")
+    net.forward(big)
+    r = rows.cpu().numpy()
+    for k in which:
+        assert np.array_equal(net.activation(k, n), small[k][r]), k
+    bad = x[:1].copy()
+    bad[0, 1, 20, 31] = np.inf
+    net.forward(to_dev(torch, bad))
+    far = np.ones((64, 64), bool)
+    far[19:22, 30:33] = False
+    assert np.array_equal(net.activation(12, 1)[0][far], small[12][0][far])
+    net.close()
+
+
 def fp32_kept(got, ref, what, errs):
     e = rel_l2(got, ref)
     errs[what] = e
