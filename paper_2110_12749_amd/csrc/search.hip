@@ -15,7 +15,8 @@
 // launches (one item per workgroup or wave) and the fixed-grid launches of the
 // streaming graph.
 //
-// Both are HBM-bound streaming passes over the int32 DM-time data:
+// Both are streaming passes over the int32 DM-time data, k_stats bound by HBM
+// (5.9 TB/s), k_search by its vector instructions:
 //  k_stats  one workgroup per trial, 8 loads in flight per lane, 128-bit
 //           integer moment sums, mu and sigma finished in double;
 //  k_search one wave per (trial, segment of box ends): segment plus look-back
@@ -121,17 +122,26 @@ __global__ __launch_bounds__(kStatsThreads) void k_stats(const SeriesTable *__re
 // ---------------------------------------------------------------------------
 // One wave owns one item: a trial and a segment [s0, s1) of its box ends.  It
 // walks the samples from lo = max(first valid sample, s0 - (w_max - 1)) in
-// blocks of 8 x 64: each lane holds one sample per 64-sample step, a wave-wide
-// scan (DPP) plus the running carry gives the exact prefix sums C of the
-// samples less the trial's integer mean c, and these go into a per-wave LDS
-// ring that keeps the last RING of them.  A box (e, w) sums to
-// C(e) - C(e - w) + w c.  Per width an integer prefilter flags the box ends
-// whose sum can reach the threshold (in 32 bits, on the ring's low halves,
-// wherever no sample within a box's reach lies 2^31 / w_max or more from c,
-// so that every box's C difference fits; in 64 bits elsewhere); only those
-// get the exact double SNR.  Runs of flagged ends are followed across steps and blocks inside the
-// wave and written as fragments (one atomic each).  Waves never wait for each
-// other: there is no workgroup barrier after the widths are loaded.
+// blocks of 512: each lane holds two runs of 4 samples, added up in the lane
+// and by two wave-wide scans (DPP) plus the running carry to the exact prefix
+// sums C of the samples less the trial's integer mean c, and these go, four to
+// an LDS access, into a per-wave ring that keeps the last RING of them.  A box
+// (e, w) sums to C(e) - C(e - w) + w c.  Per width an integer prefilter finds
+// whether any box of the block reaches the bound of its width (in 32 bits, on
+// the ring's low halves, wherever no sample within a box's reach lies
+// 2^31 / w_max or more from c, so that every box's C difference fits): 8
+// differences and a maximum per lane.  Only blocks where one does, or that
+// hold a large sample, are looked at box end by box end (64 a step), and only
+// ends that pass there get the exact double SNR.  Runs of flagged ends are
+// followed across steps and blocks inside the wave and written as fragments
+// (one atomic each).  Waves never wait for each other: there is no workgroup
+// barrier after the widths are loaded.
+//
+// What bounds it: vector instructions, some 260 per block of a wave (10 widths;
+// 80% busy).  4.57 GB of a survey beam, widths 1 to 512: 1.44 ms (3.79 when each
+// step of 64 samples had its own scan and each box end its own LDS read and
+// compare; 1.84 with flat loads, which LDS waits include; 3 workgroups per CU
+// instead of 4, from 1 KB more LDS, 2.2).
 static constexpr int kSearchThreads = 256;
 static constexpr int kSearchBlock = 512;  // samples per block: 8 steps of 64
 
@@ -170,8 +180,7 @@ __device__ __forceinline__ int64_t wave_scan_i64(int64_t x) {
   return x;
 }
 
-// Inclusive scan of an int32 over the 64 lanes (same DPP pattern as the
-// int64 scan below), for partial sums known to fit.
+// The same of an int32, for partial sums known to fit.
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ int32_t add_dpp_i32(int32_t v) {
   return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROW_MASK, 0xf, false);
@@ -193,11 +202,29 @@ __device__ __forceinline__ int64_t readlane_i64(int64_t v, int l) {
 }
 __device__ __forceinline__ int64_t lane63(int64_t v) { return readlane_i64(v, 63); }
 
+// Four consecutive samples of a series (4-byte aligned).  A series is read as
+// global memory: through a pointer read from the job table the compiler would
+// take flat loads, which every wait for LDS also waits for.
+typedef int32_t Quad __attribute__((ext_vector_type(4), aligned(4)));
+typedef const __attribute__((address_space(1))) int32_t *SeriesPtr;
+__device__ __forceinline__ Quad load_quad(SeriesPtr p) {
+  return *(const __attribute__((address_space(1))) Quad *)p;
+}
+
+// max of m and the four differences p[i] - q (mod 2^32, as signed)
+__device__ __forceinline__ int32_t max4(int32_t m, const uint32_t *p, int32_t a, int32_t b, int32_t c, int32_t d) {
+  m = max(max(m, (int32_t)(p[0] - (uint32_t)a)), (int32_t)(p[1] - (uint32_t)b));
+  return max(max(m, (int32_t)(p[2] - (uint32_t)c)), (int32_t)(p[3] - (uint32_t)d));
+}
+
 // Per-wave LDS: the prefix ring, the step's exact best SNR and width per
 // lane, and the open run.
 template <int RING>
 struct SearchWaveLds {
-  int32_t ring_lo[RING], ring_hi[RING];  // the centred prefix sums, low and high halves
+  // the centred prefix sums, low and high halves: C after sample e at (e - lo) mod RING
+  alignas(16) int32_t ring_lo[RING], ring_hi[RING];
+  // of each 4 the smallest (low half; they differ by less than 2^24); the first 64 again behind the last
+  int32_t qmin[RING / 4 + 64];
   __device__ int64_t get(int j) const {
     return (int64_t)(((uint64_t)(uint32_t)ring_hi[j] << 32) | (uint32_t)ring_lo[j]);
   }
@@ -206,7 +233,7 @@ struct SearchWaveLds {
     ring_hi[j] = (int32_t)(uint32_t)((uint64_t)v >> 32);
   }
   double sb[64];
-  int32_t sk[64];
+  uint8_t sk[64];
   int64_t o_first, o_peak;
   double o_snr;
   int32_t o_k, o_left;
@@ -217,8 +244,8 @@ struct SearchWaveLds {
 template <int RING>
 __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_search(SearchArgs a) {
   static_assert((RING & (RING - 1)) == 0, "ring length is a power of two");
-  extern __shared__ int64_t lds64[];
-  __shared__ int32_t wsh[64];
+  extern __shared__ __align__(16) int64_t lds64[];
+  __shared__ __align__(16) int32_t wsh[64];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nwaves = blockDim.x >> 6;
@@ -229,6 +256,14 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
   const int nw = a.nw;
   if ((int)threadIdx.x < nw) wsh[threadIdx.x] = a.widths[threadIdx.x];
   __syncthreads();  // the only workgroup barrier
+  // widths that are no multiple of 4 (a mask), and lane i: the i-th of the others
+  const uint64_t unaligned = __ballot(lane < nw && (wsh[min(lane, nw - 1)] & 3) != 0);
+  const uint64_t aligned = (nw < 64 ? (1ull << nw) - 1 : ~0ull) & ~unaligned;
+  const int n_al = __popcll(aligned), n4 = (n_al + 3) & ~3;
+  int lane_qk = 0;
+  for (uint64_t m = aligned, i = 0; m; m &= m - 1, ++i)
+    if (lane == (int)i) lane_qk = __builtin_ctzll(m);
+  const int lane_q4 = lane < n_al ? wsh[lane_qk] >> 2 : 1;
 
   for (int64_t b = (int64_t)blockIdx.x * nwaves + wave; b < n_items; b += (int64_t)gridDim.x * nwaves) {
     const SeriesJob &J = tb->job[find_job_by_item(tb, b)];
@@ -242,13 +277,15 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
     // centred samples small)
     const int64_t cmean = (int64_t)fmin(fmax(rint(mu), -2147483648.0), 2147483647.0);
     if (!(sigma > 0.0)) continue;  // uniform over the wave
-    const int32_t *x = J.x + (int64_t)trial * J.pitch + J.e_begin;  // relative positions
+    SeriesPtr x = (SeriesPtr)(J.x + (int64_t)trial * J.pitch + J.e_begin);  // relative positions
     const int64_t look = J.look;
     const int64_t s0 = seg * a.tile;
     const int64_t s1 = min(s0 + (int64_t)a.tile, n);
-    const int64_t lo = max(-look, s0 - (int64_t)(a.wmax - 1));
-    // every box of every end in [s0, s1) starts at or after the first sample
-    const bool full = s0 - (int64_t)(a.wmax - 1) >= -look;
+    // whole blocks before s0 where there are samples, so that a segment's
+    // blocks are whole but for the series' last
+    const int64_t reach_blocks = (a.wmax - 1 + kSearchBlock - 1) / kSearchBlock;
+    int64_t lo = s0 - reach_blocks * kSearchBlock;
+    if (lo < -look) lo = max(-look, s0 - (int64_t)(a.wmax - 1));
 
     // prefilter bounds: a box can reach the threshold only if its sum is
     // >= w mu + thr sigma sqrt(w); lim sits 2 below that bound (far more than
@@ -271,12 +308,22 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
       if (lane_lim != INT64_MIN && lane_lim != INT64_MAX) lane_lim -= cmean * (int64_t)lane_w;
       lane_l32 = (int32_t)max((int64_t)INT32_MIN, min((int64_t)INT32_MAX, lane_lim));
     }
+    int32_t lane_ql = __shfl(lane_l32, lane_qk, 64);
+    if (lane >= n_al) lane_ql = INT32_MAX;
     // samples this far from c or farther make the 32-bit prefilter unsafe for
     // the boxes that reach them (w_max of them sum to less than 2^31 in size)
-    const int64_t big = (int64_t)(0x7FFFFFFF / (uint32_t)a.wmax);
-    const int64_t reach_blocks = (a.wmax - 1 + kSearchBlock - 1) / kSearchBlock;
-    int64_t last_big = -(reach_blocks + 1);  // the last block holding such a sample
-    if (lane == 0) W.put(0, 0);  // C(lo - 1)
+    // (8 more for the bounds over groups of 4 ends and 4 starts)
+    const int64_t big = (int64_t)(0x7FFFFFFF / (uint32_t)(a.wmax + 8));
+    // samples nearer to c than this have block sums in 32 bits (and are not
+    // big); 0: c so large that the differences themselves might wrap
+    const int32_t near =
+        cmean > -(int64_t(1) << 30) && cmean < (int64_t(1) << 30) ? (int32_t)min((int64_t)(1 << 21), big) : 0;
+    int64_t last_big = -(reach_blocks + 1);   // the last block holding such a sample
+    int64_t last_slow = -(reach_blocks + 1);  // the last block without group minima
+    if (lane == 0) {  // C(lo - 1)
+      W.put(RING - 1, 0);
+      W.qmin[RING / 4 - 1] = 0;
+    }
     __builtin_amdgcn_wave_barrier();
 
     bool open = false;
@@ -301,55 +348,169 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
 
     const int64_t count = s1 - lo;
     const int64_t nblk = (count + kSearchBlock - 1) / kSearchBlock;
-    // samples in flight: the next block's 8 per lane (indices clamped into
-    // [lo, s1 - 1], so every load stays inside the series)
-    int32_t vn[8];
-#pragma unroll
-    for (int it = 0; it < 8; ++it) vn[it] = x[min(lo + 64 * it + lane, s1 - 1)];
+    const int64_t nfull = count / kSearchBlock;  // blocks with all their samples before s1
+    // the quads of the next block in flight: samples eb + 4 lane .. + 3 and 256 further
+    Quad q0 = {}, q1 = {};
+    if (nfull > 0) {
+      q0 = load_quad(x + lo + 4 * lane);
+      q1 = load_quad(x + lo + 256 + 4 * lane);
+    }
     int64_t carry = 0;
     for (int64_t blk = 0; blk < nblk; ++blk) {
       const int64_t eb = lo + blk * kSearchBlock;  // position of lane 0, step 0
-      int32_t v[8];
-#pragma unroll
-      for (int it = 0; it < 8; ++it) v[it] = vn[it];
-      if (blk + 1 < nblk) {
-#pragma unroll
-        for (int it = 0; it < 8; ++it) vn[it] = x[min(eb + kSearchBlock + 64 * it + lane, s1 - 1)];
-      }
+      const int r0 = (int)(eb - lo);
       // ---- exact centred prefix sums into the ring ----
-      const int r0 = (int)(eb - lo + 1);
-      int64_t P[8];  // C at the lane's box end + 1
-      bool blk_big = false;
+      uint32_t p32[8];  // low halves of C after samples eb + 256 j + 4 lane + i, at 4 j + i
+      int32_t qmax[2] = {0, 0}, ymax = 0;  // of each 4 sums and of the lane's samples the largest
+      bool quads = false;
+      if (blk < nfull) {
+        const Quad c0 = q0, c1 = q1;
+        if (blk + 1 < nfull) {
+          q0 = load_quad(x + eb + kSearchBlock + 4 * lane);
+          q1 = load_quad(x + eb + kSearchBlock + 256 + 4 * lane);
+        }
+        int32_t y[8];
+        uint32_t far = 0;
 #pragma unroll
-      for (int it = 0; it < 8; ++it) {
-        const int64_t e = eb + 64 * it + lane;
-        // samples about the trial's integer mean c: when every |x - c| of the
-        // step is below 2^25 their 64-lane partial sums fit an int32 scan
-        // (positions past the segment count as c, i.e. add nothing)
-        const int64_t y = e < s1 ? (int64_t)v[it] - cmean : 0;
-        if (__ballot(y <= -(int64_t)(1 << 25) || y >= (int64_t)(1 << 25)) == 0ull)
-          P[it] = carry + (int64_t)wave_scan_i32((int32_t)y);
-        else
-          P[it] = carry + wave_scan_i64(y);
-        blk_big |= __ballot(y <= -big || y >= big) != 0ull;
-        carry = lane63(P[it]);
-        W.put((r0 + 64 * it + lane) & (RING - 1), P[it]);
+        for (int i = 0; i < 8; ++i) {
+          y[i] = (int32_t)((uint32_t)(i < 4 ? c0[i & 3] : c1[i & 3]) - (uint32_t)cmean);
+          far = max(far, (uint32_t)y[i] + (uint32_t)(near - 1));
+        }
+        ymax = max(max(max(y[0], y[1]), max(y[2], y[3])), max(max(y[4], y[5]), max(y[6], y[7])));
+        quads = near > 0 && __ballot(far > 2u * (uint32_t)near - 2u) == 0ull;
+        if (quads) {  // |x - c| < near: sums of the block fit 32 bits
+#pragma unroll
+          for (int i = 1; i < 8; ++i)
+            if (i != 4) y[i] += y[i - 1];
+          const int32_t in0 = wave_scan_i32(y[3]), in1 = wave_scan_i32(y[7]);
+          const int32_t t0 = __builtin_amdgcn_readlane(in0, 63), t1 = __builtin_amdgcn_readlane(in1, 63);
+          const int32_t ex[2] = {in0 - y[3], in1 - y[7] + t0};
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const int32_t *s = y + 4 * j;
+            const uint32_t base = (uint32_t)carry + (uint32_t)ex[j];
+            qmax[j] = (int32_t)(base + (uint32_t)max(max(s[0], s[1]), max(s[2], s[3])));
+            const int32_t low = (int32_t)(base + (uint32_t)min(min(s[0], s[1]), min(s[2], s[3])));
+            W.qmin[((r0 >> 2) & (RING / 4 - 1)) + 64 * j + lane] = low;
+            if (j == 0 && (r0 & (RING - 1)) == 0) W.qmin[RING / 4 + lane] = low;
+          }
+          int4 h[2];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const int64_t P = carry + (int64_t)(ex[i >> 2] + y[i]);
+            p32[i] = (uint32_t)P;
+            reinterpret_cast<int32_t *>(&h[i >> 2])[i & 3] = (int32_t)(uint32_t)((uint64_t)P >> 32);
+          }
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const int at = (r0 + 256 * j + 4 * lane) & (RING - 1);
+            *reinterpret_cast<int4 *>(&W.ring_lo[at]) =
+                make_int4((int)p32[4 * j], (int)p32[4 * j + 1], (int)p32[4 * j + 2], (int)p32[4 * j + 3]);
+            *reinterpret_cast<int4 *>(&W.ring_hi[at]) = h[j];
+          }
+          carry += (int64_t)(t0 + t1);
+        }
       }
-      if (blk_big) last_big = blk;
+      if (!quads) {  // the last block of a segment, or samples far from c: 64 samples at a time
+        bool blk_big = false;
+#pragma unroll 1
+        for (int it = 0; it < 8; ++it) {
+          const int64_t e = eb + 64 * it + lane;
+          // (positions past the segment count as c, i.e. add nothing)
+          const int64_t y = e < s1 ? (int64_t)x[min(e, s1 - 1)] - cmean : 0;
+          const int64_t P = carry + wave_scan_i64(y);
+          blk_big |= __ballot(y <= -big || y >= big) != 0ull;
+          carry = lane63(P);
+          W.put((r0 + 64 * it + lane) & (RING - 1), P);
+        }
+        if (blk_big) last_big = blk;
+        last_slow = blk;
+      }
       __builtin_amdgcn_wave_barrier();
       if (eb + kSearchBlock - 1 < s0) continue;  // look-back block: sums only
 
-      // ---- integer prefilter, widths outer: per width the 8 ring reads are
-      // issued together; each compare leaves a wave mask ----
+      // every box of every end starts at or after the first sample
+      const bool full = max(eb, s0) - (int64_t)(a.wmax - 1) >= -look;
+      // ---- integer prefilter.  32 bits wherever every box of the block sums
+      // to less than 2^31 in size about w c: C differences of the ring's low
+      // halves are exact then ----
+      const bool bits32 = full && blk - last_big > reach_blocks;
+      bool any = true;
+      if (quads && bits32) {
+        // does any box of the block reach its width's bound?  First the
+        // largest of 4 ends less the smallest of their starts' quad (two
+        // quads where w is no multiple of 4), which is seldom above a bound
+        // that no box reaches: the widths that are multiples of 4 four at a
+        // time, without a branch, so that their LDS reads overlap.  Then
+        // exactly, for the widths left: per lane the 8 prefix sums w before
+        // its own, two aligned quads, or two pairs of neighbouring ones.
+        const int at0 = (r0 >> 2) + lane;
+        uint64_t need = nw < 64 ? (1ull << nw) - 1 : ~0ull, hit = 0;
+        if (blk - last_slow > reach_blocks) {
+          need = 0;
+          for (int k = 0; k < n4; k += 4) {
+            uint64_t h[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const int32_t *m = &W.qmin[(at0 - __builtin_amdgcn_readlane(lane_q4, k + u)) & (RING / 4 - 1)];
+              const int32_t d = max((int32_t)((uint32_t)qmax[0] - (uint32_t)m[0]),
+                                    (int32_t)((uint32_t)qmax[1] - (uint32_t)m[64]));
+              h[u] = __ballot(d >= __builtin_amdgcn_readlane(lane_ql, k + u));
+            }
+            if (h[0] | h[1] | h[2] | h[3])
+#pragma unroll
+              for (int u = 0; u < 4; ++u)
+                if (h[u] && k + u < n_al) need |= 1ull << __builtin_amdgcn_readlane(lane_qk, k + u);
+          }
+          for (uint64_t odd = unaligned; odd; odd &= odd - 1) {
+            const int k = __builtin_ctzll(odd);
+            const int w = __builtin_amdgcn_readlane(lane_w, k);
+            int32_t d = ymax;  // w = 1
+            if (w > 1) {
+              const int32_t *m = &W.qmin[(at0 - (w >> 2)) & (RING / 4 - 1)];
+              const int32_t *mm = &W.qmin[(at0 - (w >> 2) - 1) & (RING / 4 - 1)];
+              d = max(max((int32_t)((uint32_t)qmax[0] - (uint32_t)m[0]), (int32_t)((uint32_t)qmax[1] - (uint32_t)m[64])),
+                      max((int32_t)((uint32_t)qmax[0] - (uint32_t)mm[0]),
+                          (int32_t)((uint32_t)qmax[1] - (uint32_t)mm[64])));
+            }
+            if (__ballot(d >= __builtin_amdgcn_readlane(lane_l32, k))) need |= 1ull << k;
+          }
+        }
+        const int4 *ring4 = reinterpret_cast<const int4 *>(W.ring_lo);
+        for (; need; need &= need - 1) {
+          const int k = __builtin_ctzll(need);
+          const int w = __builtin_amdgcn_readlane(lane_w, k);
+          const int at = at0 - (w >> 2);
+          int32_t best = INT32_MIN;
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const int4 B = ring4[(at + 64 * j) & (RING / 4 - 1)];
+            if ((w & 3) == 0) {
+              best = max4(best, p32 + 4 * j, B.x, B.y, B.z, B.w);
+              continue;
+            }
+            const int4 A = ring4[(at + 64 * j - 1) & (RING / 4 - 1)];
+            if ((w & 3) == 1)
+              best = max4(best, p32 + 4 * j, A.w, B.x, B.y, B.z);
+            else if ((w & 3) == 2)
+              best = max4(best, p32 + 4 * j, A.z, A.w, B.x, B.y);
+            else
+              best = max4(best, p32 + 4 * j, A.y, A.z, A.w, B.x);
+          }
+          hit |= __ballot(best >= __builtin_amdgcn_readlane(lane_l32, k));
+        }
+        any = hit != 0ull;
+        if (!any && !open) continue;
+      }
+      // ---- box ends that may reach it, 64 a step; widths outer: per width the
+      // 8 ring reads are issued together, each compare leaves a wave mask ----
       uint64_t mk[8];
 #pragma unroll
       for (int it = 0; it < 8; ++it) mk[it] = 0;
-      if (full && blk - last_big > reach_blocks) {
-        // every box of the block sums to less than 2^31 in size about w c:
-        // the C differences are exact in 32 bits (the ring's low halves)
-        uint32_t p32[8];
+      if (any && bits32) {
+        uint32_t pv[8];
 #pragma unroll
-        for (int it = 0; it < 8; ++it) p32[it] = (uint32_t)P[it];
+        for (int it = 0; it < 8; ++it) pv[it] = (uint32_t)W.ring_lo[(r0 + lane + 64 * it) & (RING - 1)];
         for (int k = 0; k < nw; ++k) {
           const int w = __builtin_amdgcn_readlane(lane_w, k);
           const int32_t L = __builtin_amdgcn_readlane(lane_l32, k);
@@ -358,20 +519,12 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
           for (int it = 0; it < 8; ++it) qv[it] = (uint32_t)W.ring_lo[(bw + 64 * it) & (RING - 1)];
 #pragma unroll
-          for (int it = 0; it < 8; ++it) mk[it] |= __ballot((int32_t)(p32[it] - qv[it]) >= L);
+          for (int it = 0; it < 8; ++it) mk[it] |= __ballot((int32_t)(pv[it] - qv[it]) >= L);
         }
-      } else if (full) {
-        for (int k = 0; k < nw; ++k) {
-          const int w = __builtin_amdgcn_readlane(lane_w, k);
-          const int64_t L = readlane_i64(lane_lim, k);
-          const int bw = r0 + lane - w;
-          int64_t qv[8];
+      } else if (any) {
+        int64_t pv[8];
 #pragma unroll
-          for (int it = 0; it < 8; ++it) qv[it] = W.get((bw + 64 * it) & (RING - 1));
-#pragma unroll
-          for (int it = 0; it < 8; ++it) mk[it] |= __ballot(P[it] - qv[it] >= L);
-        }
-      } else {
+        for (int it = 0; it < 8; ++it) pv[it] = W.get((r0 + lane + 64 * it) & (RING - 1));
         for (int k = 0; k < nw; ++k) {
           const int w = __builtin_amdgcn_readlane(lane_w, k);
           const int64_t L = readlane_i64(lane_lim, k);
@@ -381,7 +534,7 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
           for (int it = 0; it < 8; ++it) qv[it] = W.get((bw + 64 * it) & (RING - 1));
 #pragma unroll
           for (int it = 0; it < 8; ++it)
-            mk[it] |= __ballot((P[it] - qv[it] >= L) & ((int64_t)w <= eb + 64 * it + lane + look + 1));
+            mk[it] |= __ballot((pv[it] - qv[it] >= L) & (full | ((int64_t)w <= eb + 64 * it + lane + look + 1)));
         }
       }
       uint32_t mbits = 0;
@@ -402,7 +555,7 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
         double bs = 0.0;
         int kb = 0;
         if (maybe) {
-          const int re = (int)(e - lo + 1);
+          const int re = (int)(e - lo);
           const int64_t q1 = W.get(re & (RING - 1));
           // only widths whose integer sum passes the prefilter bound can
           // reach the threshold; when one does, the best width is among them
@@ -432,7 +585,7 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
         }
         if (m == 0ull) continue;
         W.sb[lane] = bs;
-        W.sk[lane] = kb;
+        W.sk[lane] = (uint8_t)kb;
         __builtin_amdgcn_wave_barrier();
         const bool last_step = e0 + 63 >= s1 - 1;  // the segment's last box end is on this step
         const bool start = fl && (lane == 0 || !((m >> (lane - 1)) & 1ull));
@@ -522,6 +675,22 @@ SearchTiling search_tiling(int32_t max_width) {
   t.lds = per_wave * (size_t)t.waves;
   // long segments keep the look-back re-read small; at least 16 blocks
   t.tile = std::max(8192, ((max_width - 1) / kSearchBlock + 1) * kSearchBlock * 16);
+  return t;
+}
+
+// Segments of a whole plan's search, whose fragment buffer grows with what is
+// found: halved, down to twice the look-back, while the plan gives fewer waves
+// than the chip holds (16 a CU).  A quick look's 200 trials of 16384 samples
+// are 400 waves of 8192 box ends, 43 us, or 3200 of 1024, 22 us.
+static SearchTiling batch_tiling(const gsp_dmt_desc *desc, int32_t max_width) {
+  SearchTiling t = search_tiling(max_width);
+  const int smallest = std::max(1, (max_width - 2 + kSearchBlock) / kSearchBlock) * kSearchBlock * 2;
+  auto items = [&](int tile) {
+    int64_t n = 0;
+    for (int s = 0; s < desc->n_seg; ++s) n += (int64_t)desc->seg[s].n_dm * ((desc->n_out[s] + tile - 1) / tile);
+    return n;
+  };
+  while (t.tile / 2 >= smallest && items(t.tile) < 16 * 256) t.tile /= 2;
   return t;
 }
 
@@ -620,7 +789,7 @@ const double *stats_musig(gsp_ctx *ctx, const gsp_dmt_desc *) { return ctx->stat
 void launch_search(gsp_ctx *ctx, const int32_t *dmt, const gsp_dmt_desc *desc, const int32_t *widths_dev,
                    int32_t n_widths, int32_t max_width, float thr, Frag *frags, int64_t cap,
                    unsigned long long *counter, hipStream_t st) {
-  const SearchTiling tl = search_tiling(max_width);
+  const SearchTiling tl = batch_tiling(desc, max_width);
   SeriesTable t;
   batch_table(desc, dmt, t);
   finalize_table(t, tl);

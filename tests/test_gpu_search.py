@@ -80,3 +80,28 @@ def test_search_tail_lengths(env):
     for n in (1, 63, 64, 65, 511, 512, 513, 8191, 8192, 8193, 8192 + 511, 16385):
         say(f"[case] search length {n}")
         run_case(env, x[:, :n], [1, 2, 4, 8, 16, 32, 64], 4.0)
+
+
+@pytest.mark.parametrize("n_tr,n", [(1, 4), (3, 515), (40, 1536), (17, 2051), (5, 40007), (4200, 533)])
+@pytest.mark.parametrize("widths", [[1], [2, 3, 5, 30], [1, 6, 32, 33], [4, 512, 513], [7, 1023, 1030]])
+def test_search_segments_and_far_samples(env, n_tr, n, widths):
+    """Few trials (short segments) and many (long ones), every residue of the
+    width modulo 4, look-backs around a block; a trial each of ordinary noise,
+    of noise with samples at the type's limits (64-bit sums), of samples at
+    the upper limit (differences wrap 32 bits), with a spike just inside and
+    just outside the bound of the 32-bit sums."""
+    rng = np.random.default_rng(1000 * n_tr + n + len(widths))
+    x = rng.normal(1000.0, 50.0, size=(n_tr, n)).astype(np.int64)
+    big = 0x7FFFFFFF // max(widths)
+    for i in range(0, n_tr, 5):
+        at = rng.integers(0, n, 3)
+        x[i, at] += 700
+        if i + 1 < n_tr:
+            x[i + 1, at] = rng.choice([-2 ** 31, 2 ** 31 - 1], 3)
+        if i + 2 < n_tr:
+            x[i + 2] = 2 ** 31 - 1 - np.abs(x[i + 2] - 1000)
+            x[i + 2, at[:1]] = -2 ** 31
+        if i + 3 < n_tr:
+            x[i + 3, at] = 1000 + np.array([min(2 ** 21, big) - 300, min(2 ** 21, big) + 300, 2 ** 21])
+    say(f"[case] search segments {n_tr} x {n} widths {widths}")
+    run_case(env, np.clip(x, -2 ** 31, 2 ** 31 - 1).astype(np.int32), [w for w in widths if w <= n] or [1], 4.0)
