@@ -76,10 +76,11 @@ RowTables &row_tables(gsp_ctx *ctx, const gsp_dmt_desc *desc, const double *freq
     slot.reset();  // the tuned shape changed since the tables were built
   if (!slot) {
     // a default does not suit every row: the pattern tile's partial sums may
-    // not fit the LDS (next: its smaller tile) or not pay (then plain_shape); the byte-quad
-    // tile's copies may not (such rows split their band between two tiles
-    // where the quads that do not fit lie at one end of it, else keep the
-    // 16-bit tile).  A tuned shape is not replaced.
+    // not fit the LDS or its smaller tile be faster (next: that one) or not
+    // pay (then plain_shape); the byte-quad tile's copies may not fit (such
+    // rows split their band between two tiles where the quads that do not fit
+    // lie at one end of it, else keep the 16-bit tile).  A tuned shape is not
+    // replaced.
     std::vector<DedispShape> order{want};
     const bool tuned = ctx->tuned.count(row_signature(desc, s)) > 0;
     if (!tuned) {
@@ -88,19 +89,22 @@ RowTables &row_tables(gsp_ctx *ctx, const gsp_dmt_desc *desc, const double *freq
           order.push_back(want);
           order.back().tpw = 8;
         }
-        order.push_back(plain_shape(desc->seg[s].downsamp, desc->nchan));
+        order.push_back(plain_shape(desc, s));
       }
+      DedispShape pair;  // the 16-bit tile's default (4, 4, 8, 32)
+      pair.kind = 0;
+      pair.groups = 4;
+      pair.tpw = 4;
+      pair.waves = 8;
+      pair.chunk = 32;
+      const bool pair_first = order.back().kind == 0;
+      if (pair_first && desc->seg[s].downsamp == 1 && desc->nchan % 4 == 0)  // where it does not fit
+        order.push_back(quad_shape());
       if (order.back().kind == 2) {
         DedispShape split = order.back();
         split.kind = 3;
         order.push_back(split);
-        DedispShape pair;  // the 16-bit tile's default (4, 4, 8, 32)
-        pair.kind = 0;
-        pair.groups = 4;
-        pair.tpw = 4;
-        pair.waves = 8;
-        pair.chunk = 32;
-        order.push_back(pair);
+        if (!pair_first) order.push_back(pair);
       }
     }
     std::unique_ptr<RowTables> rt;

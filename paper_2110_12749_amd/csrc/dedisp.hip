@@ -168,25 +168,57 @@ namespace gsp {
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-DedispShape plain_shape(int32_t D, int32_t nchan) {
+// Clocks of a row on the 16-bit tile (32 trials x 512 outputs) and on the
+// byte-quad tile (96 x 256): rounds of 512 workgroups, two to a CU, the last
+// one cheaper if each has a CU of its own.  Fitted to 126 rows of 64 to 3700
+// channels, 16 to 1300 trials and 3000 to 480000 outputs: the 16-bit tile to
+// 5 %, the byte-quad tile to 23 % (its copies' width is not looked at).
+static double tile_clocks(int32_t n_dm, int64_t n_out, int32_t nchan, int trials, int outputs, double pair,
+                          double alone, double round, double launch) {
+  const int64_t tiles = (int64_t)((n_dm + trials - 1) / trials) * ((n_out + outputs - 1) / outputs);
+  const int64_t rest = tiles % 512;
+  const double work = (double)trials * ((nchan + 7) / 8) * outputs / 512.0;
+  return launch + (double)(tiles / 512) * (pair * work + round) +
+         (rest ? (rest > 256 ? pair : alone) * work + round : 0.0);
+}
+double plain_clocks(int32_t n_dm, int64_t n_out, int32_t nchan) {
+  return tile_clocks(n_dm, n_out, nchan, 32, 512, 190.0, 115.0, 5e3, 18e3);
+}
+double quad_clocks(int32_t n_dm, int64_t n_out, int32_t nchan) {
+  return tile_clocks(n_dm, n_out, nchan, 96, 256, 90.0, 45.0, 39e3, 3e3);
+}
+
+DedispShape quad_shape() {  // byte-quad tile with staging waves: 12 summing waves
+  DedispShape s;
+  s.kind = 2;
+  s.groups = 4;
+  s.tpw = 8;
+  s.waves = 12;
+  s.chunk = 64;
+  return s;
+}
+
+// The byte-quad tile takes D = 1 rows of whole quads, but for those of at least
+// 64 channels where the 16-bit tile is faster: rows of one or two rounds, in
+// which the byte-quad tile's 39000 clocks a round count (64 channels, 29 trials,
+// 134000 outputs: 0.047 against 0.031 ms; 39 trials, 177000: 0.059 against
+// 0.045 ms).
+DedispShape plain_shape(const gsp_dmt_desc *desc, int32_t seg) {
+  const int32_t D = desc->seg[seg].downsamp, n_dm = desc->seg[seg].n_dm, nchan = desc->nchan;
+  if (D == 1 && nchan % 4 == 0 &&
+      (nchan < 64 || quad_clocks(n_dm, desc->n_out[seg], nchan) <= plain_clocks(n_dm, desc->n_out[seg], nchan)))
+    return quad_shape();
   DedispShape s;
   s.tpw = 4;
   s.waves = 8;
   s.groups = 4;
   s.chunk = 32;
-  if (D == 1 && nchan % 4 == 0) {  // byte-quad tile with staging waves: 12 summing waves
-    s.kind = 2;
-    s.groups = 4;
-    s.tpw = 8;
-    s.waves = 12;
-    s.chunk = 64;
-  }
   return s;
 }
 
 DedispShape default_shape(const gsp_dmt_desc *desc, int32_t s) {
-  const int32_t D = desc->seg[s].downsamp, n_dm = desc->seg[s].n_dm;
-  if (D > 8) return plain_shape(D, desc->nchan);  // the pattern tile's samples have 11 bits
+  const int32_t D = desc->seg[s].downsamp;
+  if (D > 8) return plain_shape(desc, s);  // the pattern tile's samples have 11 bits
   DedispShape p;
   p.kind = 4;
   p.groups = 4;
@@ -194,10 +226,9 @@ DedispShape default_shape(const gsp_dmt_desc *desc, int32_t s) {
   p.chunk = 16;
   // 96 or 64 trials per tile.  Downsampled rows: 64 (their building is most of
   // the time and grows with the trials: 13.5 ms for the survey's D = 4 row
-  // with 96, 12.8 with 64; D = 2 the same).  D = 1: a tile's building costs
-  // about 24 trials' sums (49.7 ms for 16 tiles of 96, 54.9 for 24 of 64).
-  auto cost = [&](int t) { return (n_dm + 8 * t - 1) / (8 * t) * (8 * t + 24); };
-  p.tpw = D == 1 && cost(12) <= cost(8) ? 12 : 8;
+  // with 96, 12.8 with 64; D = 2 the same).  D = 1: 96, unless 64 are found
+  // to be faster when the tables are built.
+  p.tpw = D == 1 ? 12 : 8;
   return p;
 }
 

@@ -698,38 +698,74 @@ void pat_tables_host(const RowTables &rt, PatHost &H) {
   H.built = built;
 }
 
-// Whether the pattern tile beats the row's other default, from the work its
-// tables list.  Clocks of a workgroup, fitted to the survey rows (D = 1 with
-// 96 and 64 trials per tile: 49.7 and 54.9 ms) and good to about 15 % from 30
-// to 1000 tiles of 512 and 4096 channels: 90 per building unit (170 for
-// 16-bit samples) and 11.4 per trial and group of 8 channels.  The other
-// tiles take 44 (byte quads, 96 trials x 256 outputs) or 95 (16-bit, 32 x
-// 512) per trial, 8 channels and 512 outputs at two workgroups per CU, 0.6 of
-// that when alone on theirs.  So the pattern tile is left where the channels
-// are so wide, or the trials so far apart, that most trials have patterns of
-// their own (512 channels over 500 MHz at D = 4: 0.156 against 0.119 ms) and
-// for few trials of a tile (padding).  Rows of up to 4096 tiles x groups take
-// the same time either way (512 channels, 32 and 64 tiles: 0.104 and 0.111
-// against 0.109 and 0.111 ms; 192 tiles: 0.116 against 0.171): they keep the
-// other tile, whose tables are smaller.
-bool pat_tables_pay(const RowTables &rt, const PatHost &H) {
+// Clocks of a row on the pattern tile, from the work that its tables list:
+// rounds of 256 workgroups (one to a CU), each some 20000 or 32000 clocks
+// (filling and draining), 145 per building unit (195 for 16-bit samples) and
+// 7.2 (8.4) per trial and group of 8 channels.  Fitted to the same 126 rows as
+// the other tiles, to 8 %.
+double pat_clocks(const RowTables &rt, const PatHost &H) {
   const int ng = (rt.nchan + kPatG - 1) / kPatG, MT = rt.shape.trials_per_block();
   const int64_t n_dm_tiles = (rt.n_dm + MT - 1) / MT;
   const int64_t tiles = n_dm_tiles * ((rt.n_out + 2 * kPatH - 1) / (2 * kPatH));
-  if (tiles * ng <= 4096) return false;
   const double units = (double)(H.units.size() - 4 * kPatBuild) / (double)n_dm_tiles;
-  const double here = (double)((tiles + 255) / 256) * (units * (rt.D == 1 ? 90.0 : 170.0) + 11.4 * MT * ng);
-  const bool quad = rt.D == 1 && rt.nchan % 4 == 0;
-  const int mt = quad ? 96 : 32, t = quad ? 256 : 512;
-  const int64_t other_tiles = (int64_t)((rt.n_dm + mt - 1) / mt) * ((rt.n_out + t - 1) / t);
-  const double other = (double)((other_tiles + 511) / 512) * (other_tiles <= 256 ? 0.6 : 1.0) * mt * ng * t / 256.0 *
-                       (quad ? 44.0 : 95.0);
-  return here < other;
+  const double rounds = (double)((tiles + 255) / 256);
+  return rt.D == 1 ? 15e3 + rounds * (20e3 + 145.0 * units + 7.2 * MT * ng)
+                   : 2e3 + rounds * (32e3 + 195.0 * units + 8.35 * MT * ng);
+}
+
+// Whether the pattern tile beats the row's other default (the byte-quad tile's
+// estimate, which does not see how wide its copies are, 25 % up).  It does
+// not where the channels are so wide, or the trials so far apart, that most
+// trials have patterns of their own (64 channels over 500 MHz, 688 trials at
+// D = 2: 0.229 against 0.184 ms), nor for few trials of a tile.  Over the 126
+// rows the defaults so chosen take 1.69 times less time in the mean than
+// without the pattern tile, the fastest choice for each row 1.70 times.
+bool pat_tables_pay(const RowTables &rt, const PatHost &H) {
+  double other = plain_clocks(rt.n_dm, rt.n_out, rt.nchan);
+  if (rt.D == 1 && rt.nchan % 4 == 0) other = std::min(other, 1.25 * quad_clocks(rt.n_dm, rt.n_out, rt.nchan));
+  return pat_clocks(rt, H) < other;
+}
+
+// Whether 64 trials per tile are faster than the 96 of rt.  With many tiles it
+// is the trials' padding that decides: a tile's building costs about 24 trials'
+// sums (the survey's D = 1 row: 49.7 ms for 16 tiles of 96, 54.9 for 24 of
+// 64), so that the second set of tables is built only where rounds are few
+// (1024 channels, 782 trials, 17900 outputs: 0.336 ms in 2 rounds of 96, 0.257
+// in 2 of 64).
+static bool fewer_trials_faster(const RowTables &rt, const PatHost &H) {
+  auto padded = [&](int t) { return (int64_t)(rt.n_dm + 8 * t - 1) / (8 * t) * (8 * t + 24); };
+  const int64_t tiles = (int64_t)((rt.n_dm + 95) / 96) * ((rt.n_out + 2 * kPatH - 1) / (2 * kPatH));
+  if (tiles > 8 * 256) return padded(8) < padded(12);
+  RowTables small;
+  small.n_dm = rt.n_dm;
+  small.D = rt.D;
+  small.nchan = rt.nchan;
+  small.N = rt.N;
+  small.n_out = rt.n_out;
+  small.max_delay = rt.max_delay;
+  small.shape = rt.shape;
+  small.shape.tpw = 8;
+  small.delays_host = rt.delays_host;
+  PatHost S;
+  try {
+    pat_tables_host(small, S);
+  } catch (const Error &) {
+    return false;
+  }
+  return pat_clocks(small, S) < pat_clocks(rt, H);
 }
 
 void build_pat_tables(gsp_ctx *ctx, RowTables &rt, bool must) {
+  // small rows keep the other tile, whose tables are smaller: up to 2048 times
+  // 64 trials, 512 outputs and a group at D = 1, where that is the byte-quad
+  // tile, 1024 at others
+  const int64_t t_tiles = (rt.n_out + 2 * kPatH - 1) / (2 * kPatH);
+  if (!must && rt.n_dm * t_tiles * ((rt.nchan + kPatG - 1) / kPatG) <= 64 * (rt.D == 1 ? 2048 : 1024))
+    fail(GSP_EINVAL, "too small a row for the pattern tile");
   PatHost H;
   pat_tables_host(rt, H);
+  if (!must && rt.shape.tpw == 12 && fewer_trials_faster(rt, H))
+    fail(GSP_EINVAL, "fewer trials per pattern tile are faster on this row");
   if (!must && !pat_tables_pay(rt, H)) fail(GSP_EINVAL, "the pattern tile does not pay on this row");
   rt.q_pitch = H.pitch;
   rt.lds_bytes = 2 * kPatLdsDw * 4;

@@ -202,10 +202,14 @@ std::string plan_key(const gsp_dmt_desc *desc, const double *freqs);
 
 // Dedispersion (dedisp.hip)
 // default: the pattern tile (D <= 8) where its tables fit and pay, else
-// plain_shape: the byte-quad tile where it applies (D = 1, nchan % 4 == 0),
-// else the 16-bit tile
+// plain_shape: the byte-quad tile where it applies (D = 1, nchan % 4 == 0) and
+// is not slower, else the 16-bit tile
 DedispShape default_shape(const gsp_dmt_desc *desc, int32_t s);
-DedispShape plain_shape(int32_t D, int32_t nchan);
+DedispShape plain_shape(const gsp_dmt_desc *desc, int32_t s);
+DedispShape quad_shape();  // the byte-quad tile's default
+// estimated clocks of a row on the 16-bit and on the byte-quad tile
+double plain_clocks(int32_t n_dm, int64_t n_out, int32_t nchan);
+double quad_clocks(int32_t n_dm, int64_t n_out, int32_t nchan);
 bool shape_supported(const DedispShape &s);
 std::string row_signature(const gsp_dmt_desc *desc, int32_t s);
 DedispShape shape_for_row(gsp_ctx *ctx, const gsp_dmt_desc *desc, int32_t s);

@@ -212,3 +212,33 @@ def test_split_tuned_then_parity(split_case):
     shapes = ctx.autotune(fb, w.freqs, desc, n_reps=1)
     say(f"  tuned {shapes}")
     _check_rows(gsp, ctx, w, fb, desc, ref, torch)
+
+
+@pytest.mark.parametrize("nchan,nsamp,seg,kind,tpw", [
+    (64, 134091, (0.0, 0.2, 29, 1), 0, 4),       # whole quads, but the 16-bit tile is faster
+    (1024, 40000, (0.0, 0.2, 130, 1), 4, 8),     # one round of 64 trials a tile, not two of 96
+    (2048, 60000, (0.0, 0.1, 96, 1), 4, 8),      # one round either way: the shorter one
+    (2048, 150000, (0.0, 0.1, 96, 1), 4, 12),    # two rounds of 96 trials, three of 64
+    (64, 180000, (0.0, 2.0, 688, 2), 0, 4),      # trials so far apart that few patterns are shared
+    (171, 264000, (0.0, 0.5, 51, 4), 4, 8),
+])
+def test_defaults_by_estimated_time(dev, nchan, nsamp, seg, kind, tpw):
+    """The default shape is the one estimated to be fastest; every choice gives
+    the sums of the 16-bit tile."""
+    import torch
+    from paper_2110_12749_amd import gsp
+    freqs = 1000.0 + (np.arange(nchan) + 0.5) * 500.0 / nchan
+    desc = gsp.plan_shape(nsamp, freqs, 98.304e-6, [seg])
+    ctx = gsp.Context(0)
+    try:
+        torch.manual_seed(nchan)
+        fb = torch.randint(0, 256, (nsamp, nchan), dtype=torch.uint8, device="cuda")
+        used = ctx.row_shape(freqs, desc, 0)
+        say(f"[case] {nchan} channels, row {seg}: {used}")
+        assert (used[4], used[1]) == (kind, tpw)
+        got = ctx.dedisperse(fb, freqs, desc, out=torch.full((desc.total,), -1, dtype=torch.int32, device="cuda"))
+        ctx.set_row_shape(freqs, desc, 0, 4, 4, 8, 32, 0)
+        assert torch.equal(got, ctx.dedisperse(fb, freqs, desc))
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
