@@ -190,18 +190,76 @@ static void gemm(const GemmArgs &g, hipStream_t st) {
   check_hip(hipGetLastError(), "launch gemm");
 }
 
-// Weight gradients: out[m][n] += sum_p G[p][m] X[p][n] (out fp32, row-major,
-// zeroed before), G the output gradients [P][M], X the inputs: plain rows
-// [P][N], or, with im_H > 0, the 3x3 patches of NHWC activations (n =
-// tap*im_C + c as in GemmArgs, p = (image*H + h)*H + w).  M, N and im_C are
-// multiples of 8.
+// --- sums over a batch: weight and bias gradients ---
+// Each kernel below sums slices of the batch, a workgroup each, and writes them
+// as rows of partial sums; one k_sum_parts adds the rows of every gradient in
+// order, so that the gradients of a batch are the same every time.
+struct PartJob {
+  const float *src;  // [rows][stride]
+  float *dst;        // [cols]
+  int32_t rows, cols, stride, block0;
+};
+static constexpr int kPartJobs = 12;
+struct PartTable {
+  PartJob job[kPartJobs];
+  int32_t n_jobs, n_blocks;
+};
+// 32 columns per workgroup, every 8th row per thread, then the 8 in order
+__global__ __launch_bounds__(256) void k_sum_parts(PartTable t) {
+  __shared__ float red[8][32];
+  int j = 0;
+  while (j + 1 < t.n_jobs && t.job[j + 1].block0 <= (int)blockIdx.x) ++j;
+  const PartJob &J = t.job[j];
+  const int c = threadIdx.x & 31, g = threadIdx.x >> 5, col = ((int)blockIdx.x - J.block0) * 32 + c;
+  float s = 0.f;
+  if (col < J.cols) {
+    const float *p = J.src + col;
+    int r = g;
+    for (; r + 24 < J.rows; r += 32) {  // 4 loads in flight
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = p[(int64_t)(r + 8 * u) * J.stride];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) s += v[u];
+    }
+    for (; r < J.rows; r += 8) s += p[(int64_t)r * J.stride];
+  }
+  red[g][c] = s;
+  __syncthreads();
+  if (g == 0 && col < J.cols) {
+#pragma unroll
+    for (int q = 1; q < 8; ++q) s += red[q][c];
+    J.dst[col] = s;
+  }
+}
+
+// The partial sums of one backward pass: rows taken from a buffer, then summed.
+struct Parts {
+  float *buf;
+  int64_t used = 0;
+  PartTable t;
+  explicit Parts(float *b) : buf(b) { t.n_jobs = t.n_blocks = 0; }
+  float *take(int64_t rows, int64_t stride) {
+    float *p = buf + used;
+    used += rows * stride;
+    return p;
+  }
+  void sum(const float *src, int64_t rows, int64_t stride, int64_t cols, float *dst) {
+    t.job[t.n_jobs++] = {src, dst, (int32_t)rows, (int32_t)cols, (int32_t)stride, t.n_blocks};
+    t.n_blocks += (int32_t)((cols + 31) / 32);
+  }
+};
+
+// Weight gradients: out[m][n] = sum_p G[p][m] X[p][n] (row-major, a row of
+// partial sums per slice of p), G the output gradients [P][M], X the inputs:
+// plain rows [P][N], or, with im_H > 0, the 3x3 patches of NHWC activations (n
+// = tap*im_C + c, p = (image*H + h)*H + w).  M, N and im_C are multiples of 8.
 //
 // Both operands are contiguous along their rows and long along p, the
 // reduction.  A workgroup takes 64 x 64 outputs over a slice of p: per step of
 // 32 p, 128 threads load 16 bytes of two neighbouring rows of G, 128 of X, and
 // write the pairs (p, p + 1) of each column as a dword of the transposed LDS
-// tiles; then as k_gemm.  Slices (grid.z, atomic fp32 adds) give some 1000
-// workgroups.  Single-element gathers of written-out patches and slices of
+// tiles; then as k_gemm.  Slices (grid.z) give some 1000 workgroups.  Single-element gathers of written-out patches and slices of
 // 4096 p left 72 to 256 workgroups waiting for loads: 450 to 660 us per
 // convolution for 256 images, now 24 (with fc1's, on average).
 struct WgradArgs {
@@ -263,19 +321,25 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs g) {
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
     const int m = m0 + wm + 8 * (j >> 2) + 4 * (lane >> 5) + (j & 3);
-    if (m < g.M) atomicAdd(g.out + (int64_t)m * g.N + n, acc[j]);
+    if (m < g.M) g.out[((int64_t)blockIdx.z * g.M + m) * g.N + n] = acc[j];
   }
 }
 
-static void wgrad(WgradArgs g, hipStream_t st) {
-  const int64_t tiles = (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64);
-  // about 1024 workgroups, at least 256 p each
-  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(1024 / tiles, g.P / 256));
-  g.slice = ((g.P + want - 1) / want + 31) / 32 * 32;
-  const dim3 grid((unsigned)((g.M + 63) / 64), (unsigned)((g.N + 63) / 64),
-                  (unsigned)((g.P + g.slice - 1) / g.slice));
+// p per workgroup: about 1024 workgroups, at least 256 p each
+static int64_t wgrad_slice(int64_t P, int M, int N) {
+  const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(1024 / tiles, P / 256));
+  return ((P + want - 1) / want + 31) / 32 * 32;
+}
+
+static void wgrad(const uint16_t *G, const uint16_t *X, int64_t P, int M, int N, int im_C, int im_H, float *dst,
+                  Parts &parts, hipStream_t st) {
+  const int64_t slice = wgrad_slice(P, M, N), rows = (P + slice - 1) / slice;
+  WgradArgs g = {G, X, parts.take(rows, (int64_t)M * N), P, slice, M, N, im_C, im_H};
+  const dim3 grid((unsigned)((M + 63) / 64), (unsigned)((N + 63) / 64), (unsigned)rows);
   hipLaunchKernelGGL(k_wgrad, grid, dim3(256), 0, st, g);
   check_hip(hipGetLastError(), "launch weight gradients");
+  parts.sum(g.out, rows, (int64_t)M * N, (int64_t)M * N, dst);
 }
 
 // The first convolution's weight gradients, dw[o][tap*2 + c] = sum over
@@ -284,9 +348,9 @@ static void wgrad(WgradArgs g, hipStream_t st) {
 // every 64 gridDim.x-th pixel: 72 sums in registers.  Over the lanes they are
 // added by halves (lane bits 5, 4, 3 choose which half of the sums a lane goes
 // on with, then 3 full exchanges), and a workgroup's 288 sums go to its row of
-// part, whose columns k_sum_rows adds: atomics on 288 addresses from every
-// workgroup took 220 us of 248 for 256 images.  As a product of written-out
-// patches this was 447 us, and 79 to write them; now 27.
+// part: atomics on 288 addresses from every workgroup took 220 us of 248 for
+// 256 images.  As a product of written-out patches this was 447 us, and 79 to
+// write them; now 27.
 static constexpr int kConv1Parts = 512;  // workgroups at most: two waves per SIMD of 256 CUs
 __global__ __launch_bounds__(256) void k_conv1_wgrad(const uint16_t *__restrict__ x,
                                                      const uint16_t *__restrict__ dpre, int64_t n,
@@ -335,19 +399,9 @@ __global__ __launch_bounds__(256) void k_conv1_wgrad(const uint16_t *__restrict_
     if ((lane & 7) == 0) part[(int64_t)blockIdx.x * 288 + o0 * 18 + first + i] = acc[i];
   }
 }
-// out[j] = sum of the rows of part [rows][gridDim.x], j = blockIdx.x; one wave each
-__global__ __launch_bounds__(64) void k_sum_rows(const float *__restrict__ part, int rows, float *__restrict__ out) {
-  float s = 0.f;
-  for (int r = threadIdx.x; r < rows; r += 64) s += part[(int64_t)r * gridDim.x + blockIdx.x];
-#pragma unroll
-  for (int q = 32; q > 0; q >>= 1) s += __shfl_xor(s, q, 64);
-  if (threadIdx.x == 0) out[blockIdx.x] = s;
-}
-
-// out[c] += sum_p in[p][c] (bias gradients; C a multiple of 8, at most 256):
-// 8 channels per thread and load, C / 8 threads side by side, the others rows
-// apart; fp32 sums per thread, over the workgroup in LDS, one atomic per
-// channel and workgroup.  As products with a row of ones these took 260 to
+// out[workgroup][c] = sum of in[p][c] over its p (bias gradients; C a multiple of
+// 8, at most 256): 8 channels per thread and load, C / 8 threads side by side,
+// the others rows apart; fp32 sums per thread, then over the workgroup in LDS.  As products with a row of ones these took 260 to
 // 360 us each for 256 images, now 9.
 __global__ __launch_bounds__(256) void k_colsum(const uint16_t *__restrict__ in, int64_t P, int C,
                                                 float *__restrict__ out) {
@@ -367,14 +421,19 @@ __global__ __launch_bounds__(256) void k_colsum(const uint16_t *__restrict__ in,
   if ((int)threadIdx.x < C) {
     float s = 0.f;
     for (int q = 0; q < rows; ++q) s += red[(q * cpr + (threadIdx.x >> 3)) * 8 + (threadIdx.x & 7)];
-    atomicAdd(out + threadIdx.x, s);
+    out[(int64_t)blockIdx.x * C + threadIdx.x] = s;
   }
 }
 
-static void colsum(const uint16_t *in, int64_t P, int C, float *out, hipStream_t st) {
-  const int rows = 256 / (C / 8);
-  const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(P / (8 * rows), 512));
-  hipLaunchKernelGGL(k_colsum, dim3(grid), dim3(256), 0, st, in, P, C, out);
+static int64_t colsum_rows(int64_t P, int C) {
+  return std::max<int64_t>(1, std::min<int64_t>(P / (8 * (256 / (C / 8))), 512));
+}
+
+static void colsum(const uint16_t *in, int64_t P, int C, float *dst, Parts &parts, hipStream_t st) {
+  const int64_t rows = colsum_rows(P, C);
+  float *out = parts.take(rows, C);
+  hipLaunchKernelGGL(k_colsum, dim3((unsigned)rows), dim3(256), 0, st, in, P, C, out);
+  parts.sum(out, rows, C, C, dst);
 }
 
 // Weights of a convolution as the gradient of its input reads them: wt[c][tap
@@ -676,18 +735,18 @@ __global__ void k_head_bwd(const float *__restrict__ z, const float *__restrict_
   }
 }
 
-// fc2's parameter gradients from the fp32 dz: dW2[j] += sum_i dz_i h[i][j]
-// (threads j < 192), db2 += sum_i dz_i (thread 192), kHeadRows samples per
-// workgroup.
+// fc2's parameter gradients from the fp32 dz: sum_i dz_i h[i][j] (threads j <
+// 192) and sum_i dz_i (thread 192), kHeadRows samples per workgroup, a row of
+// 193 partial sums each.
 static constexpr int kHeadRows = 16;
 __global__ __launch_bounds__(256) void k_head_wgrad(const float *__restrict__ dz, const uint16_t *__restrict__ h,
-                                                    int n, float *__restrict__ dw2, float *__restrict__ db2) {
+                                                    int n, float *__restrict__ part) {
   const int j = threadIdx.x;
   if (j > kHiddenUnits) return;
   const int i0 = blockIdx.x * kHeadRows, i1 = min(n, i0 + kHeadRows);
   float s = 0.f;
   for (int i = i0; i < i1; ++i) s += j < kHiddenUnits ? dz[i] * bf2f(h[(int64_t)i * kHiddenUnits + j]) : dz[i];
-  atomicAdd(j < kHiddenUnits ? dw2 + j : db2, s);
+  part[(int64_t)blockIdx.x * (kHiddenUnits + 1) + j] = s;
 }
 
 // Adam on fp32 master parameters; refreshes the bf16 copy
@@ -1392,7 +1451,15 @@ void reserve_batch(gsp_cnn *c, int64_t n) {
   c->loss.reserve((size_t)n * 4);
   c->dh1.reserve((size_t)n * kHidden * 2);
   c->wt.reserve((size_t)kConv[3].cout * 9 * kConv[3].cin * 2);  // the largest convolution's weights
-  c->part.reserve((size_t)kConv1Parts * 288 * 4);
+  int64_t part = kConv1Parts * 288 + (n / kHeadRows + 1) * (kHidden + 1) +
+                 ((n + wgrad_slice(n, kHidden, kFlat) - 1) / wgrad_slice(n, kHidden, kFlat)) * kHidden * kFlat +
+                 colsum_rows(n, kHidden) * kHidden;
+  for (int l = 0; l < 4; ++l) {
+    const ConvSpec &cs = kConv[l];
+    const int64_t px = n * cs.h * cs.h, slice = wgrad_slice(px, cs.cout, 9 * cs.cin);
+    part += (px + slice - 1) / slice * cs.cout * 9 * cs.cin + colsum_rows(px, cs.cout) * cs.cout;
+  }
+  c->part.reserve((size_t)part * 4);
   c->dpre.reserve((size_t)n * 64 * 64 * 16 * 2);
   for (int l = 0; l < 4; ++l) {
     const int h = kConv[l].h / 2;
@@ -1472,18 +1539,21 @@ void forward(gsp_cnn *c, const uint16_t *x, int64_t n, hipStream_t st) {
 void backward(gsp_cnn *c, const uint16_t *x, const float *labels, int64_t n, hipStream_t st) {
   const uint16_t *wb = c->pbf.as<uint16_t>();
   float *g = c->g32.as<float>();
-  // every gradient is a sum of atomic adds
-  hipLaunchKernelGGL(k_zero_f32, dim3(grid_for(c->L.total)), dim3(256), 0, st, g, c->L.total);
+  Parts parts(c->part.as<float>());
   // loss head: fp32 dz, fc2's gradients from it, bf16 gradient of fc1's pre-activation
   hipLaunchKernelGGL(k_head_bwd, dim3(grid_for(n * kHidden)), dim3(256), 0, st, c->z.as<float>(), labels,
                      c->h1.as<uint16_t>(), wb + c->L.w[5], (int)n, c->loss.as<float>(), c->dz.as<float>(),
                      c->dh1.as<uint16_t>());
-  hipLaunchKernelGGL(k_head_wgrad, dim3((unsigned)((n + kHeadRows - 1) / kHeadRows)), dim3(256), 0, st,
-                     c->dz.as<float>(), c->h1.as<uint16_t>(), (int)n, g + c->L.w[5], g + c->L.b[5]);
+  const int64_t head = (n + kHeadRows - 1) / kHeadRows;
+  float *hp = parts.take(head, kHidden + 1);
+  hipLaunchKernelGGL(k_head_wgrad, dim3((unsigned)head), dim3(256), 0, st, c->dz.as<float>(), c->h1.as<uint16_t>(),
+                     (int)n, hp);
+  parts.sum(hp, head, kHidden + 1, kHidden, g + c->L.w[5]);
+  parts.sum(hp + kHidden, head, kHidden + 1, 1, g + c->L.b[5]);
   const uint16_t *dh = c->dh1.as<uint16_t>();
   // fc1: dW = dh^T x, db = colsum dh, dx = dh W1
-  wgrad({dh, c->pool[3].as<uint16_t>(), g + c->L.w[4], n, 0, kHidden, kFlat, 0, 0}, st);
-  colsum(dh, n, kHidden, g + c->L.b[4], st);
+  wgrad(dh, c->pool[3].as<uint16_t>(), n, kHidden, kFlat, 0, 0, g + c->L.w[4], parts, st);
+  colsum(dh, n, kHidden, g + c->L.b[4], parts, st);
   GemmArgs gx = ga(dh, kHidden, wb + c->L.w[4], kFlat, 1, c->dpool[3].ptr, kFlat, 1, n, kFlat, kHidden);
   gx.out_bf16 = 1;
   gemm(gx, st);
@@ -1495,19 +1565,21 @@ void backward(gsp_cnn *c, const uint16_t *x, const float *labels, int64_t n, hip
     hipLaunchKernelGGL(k_pool_bwd, dim3(grid_for(M / 4 * cs.cout / 8)), dim3(256), 0, st, c->dpool[l].as<uint16_t>(),
                        c->idx[l].as<uint8_t>(), c->act[l].as<uint16_t>(), (int)n, cs.cout, H, H, dpre);
     // dW[o][k] = sum_p dpre[p][o] patch(p)[k]; db[o] = sum_p dpre[p][o]
-    colsum(dpre, M, cs.cout, g + c->L.b[l], st);
+    colsum(dpre, M, cs.cout, g + c->L.b[l], parts, st);
     if (l == 0) {
-      const int rows = (int)std::min<int64_t>(n * 64, kConv1Parts);
-      hipLaunchKernelGGL(k_conv1_wgrad, dim3(rows), dim3(256), 0, st, x, dpre, n, c->part.as<float>());
-      hipLaunchKernelGGL(k_sum_rows, dim3(288), dim3(64), 0, st, c->part.as<float>(), rows, g + c->L.w[0]);
+      const int64_t rows = std::min<int64_t>(n * 64, kConv1Parts);
+      float *out = parts.take(rows, 288);
+      hipLaunchKernelGGL(k_conv1_wgrad, dim3((unsigned)rows), dim3(256), 0, st, x, dpre, n, out);
+      parts.sum(out, rows, 288, 288, g + c->L.w[0]);
       break;
     }
-    wgrad({dpre, c->pool[l - 1].as<uint16_t>(), g + c->L.w[l], M, 0, cs.cout, 9 * cs.cin, cs.cin, H}, st);
+    wgrad(dpre, c->pool[l - 1].as<uint16_t>(), M, cs.cout, 9 * cs.cin, cs.cin, H, g + c->L.w[l], parts, st);
     // dx: dpre convolved with the flipped weights
     hipLaunchKernelGGL(k_flip_weights, dim3(grid_for(9 * cs.cin * cs.cout)), dim3(256), 0, st, wb + c->L.w[l], cs.cin,
                        cs.cout, wt);
     gemm(conv_args(dpre, n, cs.cout, H, wt, cs.cin, c->dpool[l - 1].ptr), st);
   }
+  hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)parts.t.n_blocks), dim3(256), 0, st, parts.t);
   check_hip(hipGetLastError(), "launch backward pass");
   c->last_bwd_n = n;
 }
