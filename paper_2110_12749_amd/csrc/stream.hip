@@ -20,7 +20,8 @@
 // is captured once into a hipGraph and replayed, the host rewriting the job
 // tables between replays.  While a step's kernels run, each beam's next
 // pending block is copied to the device on a second stream, into the other of
-// the beam's two input buffers.  Beams are admitted against a device-memory budget;
+// the beam's two input buffers; a block pushed while its beam has none waiting
+// is copied at once.  Beams are admitted against a device-memory budget;
 // a beam that does not fit waits in a queue (its blocks stay on the host) and
 // is admitted when finished beams release their memory.
 #include <algorithm>
@@ -380,6 +381,24 @@ PinnedBlock take_pinned(gsp_stream *s, size_t bytes) {
   check_hip(hipHostMalloc((void **)&b.p, bytes, hipHostMallocDefault), "allocate pinned block");
   b.bytes = bytes;
   return b;
+}
+
+// A pushed block into its pinned buffer: pieces of at least 4 MB side by side
+// on up to 4 threads (84 MB: 2.7 ms on one, 1.1 on four).
+void copy_block(uint8_t *dst, const uint8_t *src, size_t bytes) {
+  const size_t n = std::min<size_t>(4, bytes >> 22);
+  std::vector<std::thread> t;
+  size_t done = 0;
+  try {
+    for (size_t k = 0; k + 1 < n; ++k) {
+      const size_t piece = bytes / n;
+      t.emplace_back([=] { std::memcpy(dst + done, src + done, piece); });
+      done += piece;
+    }
+  } catch (...) {  // no more threads: the rest here
+  }
+  std::memcpy(dst + done, src + done, bytes - done);
+  for (auto &x : t) x.join();
 }
 
 void give_pinned(gsp_stream *s, PinnedBlock b) {
@@ -966,7 +985,7 @@ int gsp_stream_push(gsp_stream *s, int32_t beam_id, const uint8_t *block, int64_
     PendingBlock p;
     p.buf = take_pinned(s, bytes);
     lk.unlock();  // the copy runs unlocked; the beam may be closed meanwhile
-    std::memcpy(p.buf.p, block, (size_t)nsamp * nchan);
+    copy_block(p.buf.p, block, (size_t)nsamp * nchan);
     lk.lock();
     it = s->beams.find(beam_id);
     if (it == s->beams.end() || it->second->ended || it->second->closing) {
@@ -977,6 +996,19 @@ int gsp_stream_push(gsp_stream *s, int32_t beam_id, const uint8_t *block, int64_
     p.nsamp = nsamp;
     p.arrival = Clock::now();
     if (nsamp < s->B) b.ended = true;
+    // The block the beam's next step takes goes to the device at once, while
+    // the next push copies (84 MB: 1.5 ms on the link), into the input buffer
+    // that no step reads.  Not while a step has a block of the beam (it chooses
+    // the buffers, and copies ahead itself) or one waits before this one.
+    if (b.admitted && !b.inflight && b.pending.empty() && b.pf_src == nullptr) {
+      const int v = b.cur ^ 1;
+      if (hipMemcpyAsync(b.in[v].ptr, p.buf.p, (size_t)nsamp * nchan, hipMemcpyHostToDevice, s->cst) == hipSuccess) {
+        b.pf_src = p.buf.p;
+        b.pf_buf = v;
+      } else {
+        (void)hipGetLastError();  // the step copies it
+      }
+    }
     b.pending.push_back(p);
     s->cv.notify_all();
   });
