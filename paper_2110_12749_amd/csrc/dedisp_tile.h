@@ -34,6 +34,16 @@ struct DedispArgs {
   int64_t seg_stride;
 };
 
+// A job's arguments read from a table in device memory
+__device__ __forceinline__ DedispArgs job_args_global(DedispArgs a) {
+  a.Y = as_global((const char *)a.Y);
+  a.addr = as_global(a.addr);
+  a.base = as_global(a.base);
+  a.out = as_global((char *)a.out);
+  a.chunks = as_global(a.chunks);
+  return a;
+}
+
 __device__ __forceinline__ int xcd_remap(int b, int G) {
   // hardware dispatches workgroup b to XCD b % 8; give each XCD a contiguous
   // range of logical tiles

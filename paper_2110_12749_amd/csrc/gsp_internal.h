@@ -121,6 +121,20 @@ struct SeriesJob {
   int32_t n_dm;
   int32_t trial0;  // global trial index of the job's first trial (finalize_table)
 };
+// p, the same in every lane, as a pointer into global memory.  Of a pointer
+// that a kernel reads from a job table the compiler knows no more than that it
+// is generic, and takes flat loads, which every wait for LDS also waits for.
+// (Through an empty asm: a cast there and back alone is folded away.)
+template <class T>
+__device__ __forceinline__ T *as_global(T *p) {
+#ifdef __HIP_DEVICE_COMPILE__
+  uint64_t v = reinterpret_cast<uint64_t>(p);
+  asm("" : "+s"(v));
+  return (T *)(__attribute__((address_space(1))) T *)v;
+#else
+  return p;
+#endif
+}
 static constexpr int kMaxJobs = 1024;
 struct SeriesTable {
   SeriesJob job[kMaxJobs];

@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kStatsThreads) void k_stats(const SeriesTable *__re
     if (need && need[g] == 0) continue;  // a trial nobody reads: left as it was
     const SeriesJob &J = tb->job[find_job_by_trial(tb, g)];
     const int64_t n = J.n;
-    const int32_t *x = J.x + (int64_t)(g - J.trial0) * J.pitch + J.e_begin;
+    const int32_t *x = as_global(J.x) + (int64_t)(g - J.trial0) * J.pitch + J.e_begin;
     const int64_t x0 = n > 0 ? x[0] : 0;
     int64_t s1 = 0;
     unsigned __int128 s2 = 0;

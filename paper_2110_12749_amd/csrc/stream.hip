@@ -114,7 +114,9 @@ __global__ __launch_bounds__(256) void k_stage_ring(const StageTable *__restrict
   const int tid = threadIdx.x;
   const int64_t n_items = tb->n_items;
   for (int64_t b = blockIdx.x; b < n_items; b += gridDim.x) {
-    const StageJob J = tb->job[find_by_item0(tb, b)];
+    StageJob J = tb->job[find_by_item0(tb, b)];
+    J.X = as_global(J.X);
+    J.Y = as_global(J.Y);
     const int64_t local = b - J.item0;
     const int ct = (int)(local % J.c_tiles);
     const int64_t tt = local / J.c_tiles;
@@ -225,7 +227,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
   }
   for (int64_t b = first; b < end; b += stride) {
     const int j = __builtin_amdgcn_readfirstlane(find_by_item0(tb, b));
-    const DedispArgs a = tb->job[j].a;
+    const DedispArgs a = job_args_global(tb->job[j].a);
     const int64_t local = b - tb->job[j].item0;
     __syncthreads();  // LDS of the previous tile is free
     dedisp_tile<K, TPW, uint16_t>(a, (int)(local % a.n_dm_tiles), (int)(local / a.n_dm_tiles), lds);
@@ -247,7 +249,7 @@ __global__ __launch_bounds__(256) void k_tail(const TailTable *__restrict__ tb) 
         hi = mid - 1;
     }
     const TailJob J = tb->job[lo];
-    int32_t *row = J.x + (int64_t)(g - J.trial0) * J.pitch;
+    int32_t *row = as_global(J.x) + (int64_t)(g - J.trial0) * J.pitch;
     for (int64_t k = threadIdx.x; k < J.look; k += 256) keep[k] = row[J.w + k];
     __syncthreads();
     for (int64_t k = threadIdx.x; k < J.look; k += 256) row[k] = keep[k];

@@ -81,6 +81,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
     DedispArgs a = tb->job[j].a;
     a.Y = src_base + reinterpret_cast<intptr_t>(a.Y);
     a.out = dst_base + reinterpret_cast<intptr_t>(a.out);
+    a = job_args_global(a);
     const int64_t local = b - tb->job[j].item0;
     __syncthreads();  // LDS of the previous tile is free
     dedisp_tile<K, TPW, SrcT, OutT, SEG>(a, (int)(local % a.n_dm_tiles), (int)(local / a.n_dm_tiles), lds);
