@@ -61,22 +61,6 @@ static constexpr int kPatBuild = 8;      // building waves
 static constexpr int kPatRec = 4 * 16 * 3;  // dwords of a pattern block's records
 static constexpr int kPatLdsDw = 20480;  // LDS dwords of one buffer (two buffers: 160 KB, one workgroup per CU)
 
-struct PatArgs {
-  const uint8_t *Y;          // channel-major staged rows, NB bytes per sample (2: the split form)
-  const uint32_t *addr;      // [n_groups][n_dm_pad / 2] LDS dword offsets per (group, trial), two trials per dword
-  const int32_t *tile_pass;  // [n_dm_tiles + 1] first pass record of each DM tile
-  const int2 *passes;        // {first group, first unit}; a sentinel ends each tile
-  const PatUnit *units;
-  const int32_t *chan;       // per subgroup: byte offset of each of its 8 channels' windows from the group's first row
-  const uint32_t *pats;      // per pattern block [4][16][3]: lane's pattern (column) and channel pair (see compute)
-  int32_t *out;              // out[i * out_pitch + t]
-  int64_t out_pitch, n_out;
-  int32_t n_dm, n_dm_pad, n_dm_tiles, n_t_tiles;
-  int32_t flush;             // groups between carries of the 16-bit halves
-  int32_t excess;            // added to every sum by the channels the last group lacks
-  int32_t accumulate;        // add the sums to what out holds (the other part of a split row)
-};
-
 typedef int32_t v4i __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_a __attribute__((ext_vector_type(2), aligned(4)));
 typedef uint32_t u32x3_a __attribute__((ext_vector_type(3), aligned(4)));
@@ -91,13 +75,9 @@ struct PatRaw {
 
 // TPW: trials per summing wave; NB: bytes per staged sample
 template <int TPW, int NB>
-__global__ __launch_bounds__(64 * (kPatSum + kPatBuild)) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void k_dedisp_pat(PatArgs a) {
+__device__ __forceinline__ void pat_tile(const PatArgs &a, const int L, uint32_t *lds) {
   static_assert(TPW % 2 == 0, "trials are read in pairs");
   constexpr int NP = kPatBuild;
-  extern __shared__ __align__(16) uint32_t lds[];
-  const int G = a.n_dm_tiles * a.n_t_tiles;
-  const int L = xcd_remap(blockIdx.x, G);
   const int dm_tile = L % a.n_dm_tiles, t_tile = L / a.n_dm_tiles;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -396,10 +376,55 @@ void k_dedisp_pat(PatArgs a) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int64_t tt = (int64_t)t0 + h * kPatH + lane + 64 * k;
-        if (tt < a.n_out) orow[tt] = (int32_t)s[h] + (a.accumulate ? orow[tt] : 0);
+        if (tt < a.n_out && tt >= a.t_lo) orow[tt] = (int32_t)s[h];
       }
     }
   }
+}
+
+template <int TPW, int NB>
+__global__ __launch_bounds__(64 * (kPatSum + kPatBuild)) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void k_dedisp_pat(PatArgs a) {
+  extern __shared__ __align__(16) uint32_t lds[];
+  pat_tile<TPW, NB>(a, xcd_remap(blockIdx.x, a.n_dm_tiles * a.n_t_tiles), lds);
+}
+
+// The tiles of a job table, one per workgroup; the grid, fixed when a graph is
+// captured, may hold more.
+template <int TPW, int NB>
+__global__ __launch_bounds__(64 * (kPatSum + kPatBuild)) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void k_dedisp_pat_jobs(const PatJobTable *tb) {
+  extern __shared__ __align__(16) uint32_t lds[];
+  typedef const __attribute__((address_space(4))) PatJobTable ctable;  // scalar loads
+  ctable *t = (ctable *)tb;
+  const int n_items = (int)t->n_items;
+  if ((int)blockIdx.x >= n_items) return;
+  const int L = xcd_remap(blockIdx.x, n_items);
+  int lo = 0, hi = t->n_jobs - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if ((int)t->job[mid].item0 <= L)
+      lo = mid;
+    else
+      hi = mid - 1;
+  }
+  static_assert(sizeof(PatArgs) % 8 == 0, "copied by 8 bytes");
+  typedef const __attribute__((address_space(4))) uint64_t cu64;
+  cu64 *src = (cu64 *)&t->job[lo].a;
+  uint64_t w[sizeof(PatArgs) / 8];
+#pragma unroll
+  for (int k = 0; k < (int)(sizeof(PatArgs) / 8); ++k) w[k] = src[k];
+  PatArgs a;
+  __builtin_memcpy(&a, w, sizeof(a));
+  a.Y = as_global(a.Y);
+  a.addr = as_global(a.addr);
+  a.tile_pass = as_global(a.tile_pass);
+  a.passes = as_global(a.passes);
+  a.units = as_global(a.units);
+  a.chan = as_global(a.chan);
+  a.pats = as_global(a.pats);
+  a.out = as_global(a.out);
+  pat_tile<TPW, NB>(a, L - (int)t->job[lo].item0, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -794,33 +819,37 @@ static void launch_p(const PatArgs &a, int64_t lds, hipStream_t st) {
   hipLaunchKernelGGL(kern, dim3(a.n_dm_tiles * a.n_t_tiles), dim3(64 * (kPatSum + kPatBuild)), (size_t)lds, st, a);
 }
 
-void launch_dedisp_pat(gsp_ctx *ctx, const RowTables &rt, int32_t *out_row, hipStream_t st) {
-  const DedispShape &sh = rt.shape;
-  const int NB = rt.D == 1 ? 1 : 2;
+PatArgs pat_args(const RowTables &rt, const uint8_t *Y, int32_t *out, int64_t out_pitch, int32_t t_lo, int64_t n_out) {
   PatArgs a;
   std::memset(&a, 0, sizeof(a));
-  a.excess = NB == 1 ? 128 * (-rt.nchan & (kPatG - 1)) : 0;
-  a.Y = ctx->staged.as<uint8_t>();
+  a.excess = rt.D == 1 ? 128 * (-rt.nchan & (kPatG - 1)) : 0;
+  a.Y = Y;
   a.addr = rt.addr.as<uint32_t>();
   a.tile_pass = rt.q_tile_pass.as<int32_t>();
   a.passes = rt.q_passes.as<int2>();
   a.units = rt.q_items.as<PatUnit>();
   a.chan = rt.q_chan.as<int32_t>();
   a.pats = rt.q_copies.as<uint32_t>();
-  a.out = out_row;
-  a.out_pitch = rt.n_out;
-  a.n_out = rt.n_out;
+  a.out = out;
+  a.out_pitch = out_pitch;
+  a.n_out = n_out;
+  a.t_lo = t_lo;
   a.n_dm = rt.n_dm;
-  const int MT = sh.trials_per_block();
+  const int MT = rt.shape.trials_per_block();
   a.n_dm_tiles = (rt.n_dm + MT - 1) / MT;
   a.n_dm_pad = a.n_dm_tiles * MT;
-  const int64_t n_t = (rt.n_out + 2 * kPatH - 1) / (2 * kPatH);
+  const int64_t n_t = (n_out + 2 * kPatH - 1) / (2 * kPatH);
   if ((int64_t)a.n_dm_tiles * n_t >= (1LL << 31)) fail(GSP_EOVERFLOW, "too many dedispersion tiles");
   a.n_t_tiles = (int32_t)n_t;
   // a half holds at most 2047 after a carry; each group adds at most 255 D kPatG
   a.flush = (65535 - 2047) / (255 * rt.D * kPatG);  // >= 3 for D <= 8; at least 2 are added between carries
+  return a;
+}
+
+void launch_dedisp_pat(gsp_ctx *ctx, const RowTables &rt, int32_t *out_row, hipStream_t st) {
+  const PatArgs a = pat_args(rt, ctx->staged.as<uint8_t>(), out_row, rt.n_out, 0, rt.n_out);
   ProfScope prof(ctx, "dedisperse_pattern", st, (double)rt.n_dm * (double)rt.n_out * (double)rt.nchan);
-  switch (sh.tpw * 4 + NB) {
+  switch (rt.shape.tpw * 4 + (rt.D == 1 ? 1 : 2)) {
     case 12 * 4 + 1: launch_p<12, 1>(a, rt.lds_bytes, st); break;
     case 12 * 4 + 2: launch_p<12, 2>(a, rt.lds_bytes, st); break;
     case 8 * 4 + 1: launch_p<8, 1>(a, rt.lds_bytes, st); break;
@@ -828,6 +857,30 @@ void launch_dedisp_pat(gsp_ctx *ctx, const RowTables &rt, int32_t *out_row, hipS
     default: fail(GSP_EINVAL, "unsupported dedispersion shape");
   }
   check_hip(hipGetLastError(), "launch dedispersion kernel");
+}
+
+int pat_form(const RowTables &rt) { return rt.D > 1 ? 2 : rt.shape.tpw == 8 ? 1 : 0; }
+
+static const void *pat_jobs_kernel(int form) {
+  return form == 0   ? (const void *)k_dedisp_pat_jobs<12, 1>
+         : form == 1 ? (const void *)k_dedisp_pat_jobs<8, 1>
+                     : (const void *)k_dedisp_pat_jobs<8, 2>;
+}
+
+void set_pat_jobs_attributes(int form) {
+  check_hip(hipFuncSetAttribute(pat_jobs_kernel(form), hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kPatLdsDw * 4),
+            "set LDS size");
+}
+
+void launch_pat_jobs(int form, const PatJobTable *tb_dev, int64_t grid, hipStream_t st) {
+  const dim3 g((unsigned)grid), blk(64 * (kPatSum + kPatBuild));
+  const size_t lds = 2 * kPatLdsDw * 4;
+  switch (form) {
+    case 0: hipLaunchKernelGGL((k_dedisp_pat_jobs<12, 1>), g, blk, lds, st, tb_dev); break;
+    case 1: hipLaunchKernelGGL((k_dedisp_pat_jobs<8, 1>), g, blk, lds, st, tb_dev); break;
+    default: hipLaunchKernelGGL((k_dedisp_pat_jobs<8, 2>), g, blk, lds, st, tb_dev); break;
+  }
+  check_hip(hipGetLastError(), "launch pattern jobs");
 }
 
 }  // namespace gsp

@@ -285,7 +285,31 @@ struct PatUnit {                   // building work: 64 positions x 16 patterns
   int32_t group, pad;
 };
 static_assert(sizeof(PatUnit) == 32, "read with one scalar load");
-struct PatHost {                   // the pattern tile's tables on the host (PatArgs in dedisp_pat.hip)
+struct PatArgs {
+  const uint8_t *Y;          // channel-major staged rows, NB bytes per sample (2: the split form)
+  const uint32_t *addr;      // [n_groups][n_dm_pad / 2] LDS dword offsets per (group, trial), two trials per dword
+  const int32_t *tile_pass;  // [n_dm_tiles + 1] first pass record of each DM tile
+  const int2 *passes;        // {first group, first unit}; a sentinel ends each tile
+  const PatUnit *units;
+  const int32_t *chan;       // per subgroup: byte offset of each of its 8 channels' windows from the group's first row
+  const uint32_t *pats;      // per pattern block [4][16][3]: lane's pattern (column) and channel pair (see compute)
+  int32_t *out;              // out[i * out_pitch + t]
+  int64_t out_pitch, n_out;
+  int32_t n_dm, n_dm_pad, n_dm_tiles, n_t_tiles;
+  int32_t flush;             // groups between carries of the 16-bit halves
+  int32_t excess;            // added to every sum by the channels the last group lacks
+  int32_t t_lo;              // first output stored
+};
+struct PatJob {
+  PatArgs a;
+  int64_t item0;                   // first tile of the job
+};
+struct PatJobTable {
+  int64_t n_items;
+  int32_t n_jobs, pad;
+  PatJob job[kMaxJobs];
+};
+struct PatHost {                   // the pattern tile's tables on the host
   std::vector<int32_t> tile_pass, passes, chan;
   std::vector<PatUnit> units;
   std::vector<uint32_t> pats, addr;
@@ -293,9 +317,18 @@ struct PatHost {                   // the pattern tile's tables on the host (Pat
   double built = 0;                // LDS dwords built per time tile, all DM tiles
 };
 void pat_tables_host(const RowTables &rt, PatHost &H);
+double pat_clocks(const RowTables &rt, const PatHost &H);  // estimated clocks of the row
 bool pat_tables_pay(const RowTables &rt, const PatHost &H);
 void build_pat_tables(gsp_ctx *ctx, RowTables &rt, bool must);  // must: also where another tile is faster
 void launch_dedisp_pat(gsp_ctx *ctx, const RowTables &rt, int32_t *out_row, hipStream_t st);
+// Arguments of outputs [t_lo, n_out) of a row staged at Y, written to out[i * out_pitch + t]
+PatArgs pat_args(const RowTables &rt, const uint8_t *Y, int32_t *out, int64_t out_pitch, int32_t t_lo, int64_t n_out);
+// The tiles of a table's jobs, at most `grid` of them; tables of one tile form
+// each: forms 0 to 2 are 96 trials, 64 trials (both D = 1), 64 trials (D > 1)
+static constexpr int kPatForms = 3;
+int pat_form(const RowTables &rt);
+void set_pat_jobs_attributes(int form);
+void launch_pat_jobs(int form, const PatJobTable *tb_dev, int64_t grid, hipStream_t st);
 
 // Search (search.hip)
 SearchTiling search_tiling(int32_t max_width);

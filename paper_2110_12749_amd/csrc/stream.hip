@@ -15,8 +15,9 @@
 // later block.
 //
 // One step processes one pending block of every active beam.  Its device
-// work is a fixed sequence of five kernels (stage, dedisperse, stats, search,
-// look-back shift) that read their work from device job tables; the sequence
+// work is a fixed sequence of kernels (stage, dedisperse, stats, search,
+// look-back shift; rows on the pattern tile are copied out of their rings first
+// and have a dedispersion kernel for each form of the tile) that read their work from device job tables; the sequence
 // is captured once into a hipGraph and replayed, the host rewriting the job
 // tables between replays.  While a step's kernels run, each beam's next
 // pending block is copied to the device on a second stream, into the other of
@@ -28,6 +29,7 @@
 #include <chrono>
 #include <cmath>
 #include <condition_variable>
+#include <cstddef>
 #include <cstring>
 #include <deque>
 #include <mutex>
@@ -74,6 +76,25 @@ struct DedispTable {
   int32_t n_jobs;
   int64_t n_items;
 };
+
+// A row's ring window as a linear copy in the pattern tile's form
+struct UnringJob {
+  const uint16_t *Y;  // ring
+  uint8_t *dst;       // [nchan][dpitch], NB bytes per sample
+  int64_t pitch, ring;
+  int64_t phys0;      // ring position of the first sample (a multiple of 4, as the ring's length)
+  int64_t count;      // samples
+  int64_t dpitch;
+  int64_t item0;
+  int32_t nchan, NB;
+  int32_t chunks;     // of kUnringChunk samples per channel
+};
+struct UnringTable {
+  int64_t n_items;
+  int32_t n_jobs, pad;
+  UnringJob job[kMaxJobs];
+};
+static constexpr int kUnringChunk = 2048;
 
 struct TailJob {
   int32_t *x;      // window buffer, [n_dm][pitch]
@@ -234,6 +255,38 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
   }
 }
 
+// Ring windows to linear copies: item = (job, channel, 2048 samples), a thread
+// 4 samples at a time (8 bytes of the ring, which a run of 4 never leaves).
+// Written as bytes (D = 1), or with each sample's low 4 bits apart from the rest
+// (the pattern tile's form of wider samples).  Bound by its bytes: 1.9 GB for a
+// step of 4 beams of 4096 channels.
+__global__ __launch_bounds__(256) void k_unring(const UnringTable *__restrict__ tb) {
+  const int64_t n_items = tb->n_items;
+  for (int64_t b = blockIdx.x; b < n_items; b += gridDim.x) {
+    const UnringJob &J = tb->job[find_by_item0(tb, b)];
+    const int64_t local = b - J.item0;
+    const int64_t c = local / J.chunks;
+    const int64_t s0 = (local - c * J.chunks) * kUnringChunk;
+    const uint16_t *src = as_global(J.Y) + c * J.pitch;
+    uint8_t *dst = as_global(J.dst) + c * J.dpitch * J.NB;
+#pragma unroll
+    for (int k = 0; k < kUnringChunk / 1024; ++k) {
+      const int64_t x = s0 + 4 * ((int)threadIdx.x + 256 * k);
+      if (x >= J.count) continue;
+      int64_t pos = J.phys0 + x;
+      if (pos >= J.ring) pos -= J.ring;
+      const uint2 v = *reinterpret_cast<const uint2 *>(src + pos);
+      if (J.NB == 1) {
+        *reinterpret_cast<uint32_t *>(dst + x) = (v.x & 0xFFu) | ((v.x >> 8) & 0xFF00u) | ((v.y & 0xFFu) << 16) |
+                                                 ((v.y << 8) & 0xFF000000u);
+      } else {
+        auto split = [](uint32_t w) { return (w & 0x000F000Fu) | ((w << 4) & 0xFF00FF00u); };
+        *reinterpret_cast<uint2 *>(dst + 2 * x) = make_uint2(split(v.x), split(v.y));
+      }
+    }
+  }
+}
+
 // Look-back shift: the last `look` samples of [look-back | window] move to
 // the front of each trial's buffer (through LDS: the ranges may overlap).
 __global__ __launch_bounds__(256) void k_tail(const TailTable *__restrict__ tb) {
@@ -282,6 +335,8 @@ struct StreamRow {
   int32_t D = 1, n_dm = 0;
   int64_t M = 0;          // maximum delay (row samples)
   RowTables tables;       // LDS offsets and staging bases for the stream shape
+  std::unique_ptr<RowTables> pat;  // the pattern tile's tables, where it is faster
+  int64_t lin_bytes = 0;  // of its linear copy
   DevBuf ring;            // uint16 [nchan][R + kGuard]
   int64_t R = 0;
   DevBuf win;             // int32 [n_dm][look + Wcap]
@@ -343,6 +398,12 @@ struct gsp_stream {
   std::unique_ptr<DedispTable> h_dedisp = std::make_unique<DedispTable>();
   std::unique_ptr<SeriesTable> h_series = std::make_unique<SeriesTable>();
   std::unique_ptr<TailTable> h_tail = std::make_unique<TailTable>();
+  // pattern tile: jobs of each tile form, and linear copies of their windows
+  DevBuf d_unring, d_pat[kPatForms], lin;
+  std::unique_ptr<UnringTable> h_unring = std::make_unique<UnringTable>();
+  std::unique_ptr<PatJobTable> h_pat[kPatForms] = {std::make_unique<PatJobTable>(), std::make_unique<PatJobTable>(),
+                                                   std::make_unique<PatJobTable>()};
+  int64_t pat_grid[kPatForms] = {0, 0, 0};  // workgroups the graph was captured with
   int64_t frag_cap = 1 << 16;
   int64_t regrown = 0;  // steps whose search ran again with a grown fragment buffer
   int64_t musig_cap = 0;
@@ -420,6 +481,70 @@ int64_t beam_bytes(const gsp_stream *s, const Beam &b) {
   return m;
 }
 
+// The pattern tile's tables of a row, where they fit and the tile is estimated
+// to be faster than k_dedisp_jobs's even after the window's copy (read as 16-bit
+// samples, written as NB bytes at 4.6 TB/s, 2.4 GHz).  4 beams of 4096 channels,
+// 1175 trials and 20480 samples: 12.9 ms a step with k_dedisp_jobs, 4.6 with
+// the copies and the pattern tile.
+void plan_pattern(gsp_stream *s, StreamRow &row, int32_t nchan) {
+  if (row.D > 8) return;  // the pattern tile's samples have 11 bits
+  const int NB = row.D == 1 ? 1 : 2;
+  double best = plain_clocks(row.n_dm, row.Wcap, nchan) -
+                (double)nchan * (double)(row.Wcap + row.M) * (2 + NB) * 2.4e9 / 4.6e12;
+  int best_tpw = 0;
+  auto p = std::make_unique<RowTables>();
+  p->n_dm = row.n_dm;
+  p->D = row.D;
+  p->nchan = nchan;
+  p->N = row.Wcap + row.M + 3;  // a window starts at a multiple of 4
+  p->n_out = row.Wcap + 3;
+  p->max_delay = row.M;
+  p->shape.kind = 4;
+  p->shape.groups = 4;
+  p->shape.waves = 8;
+  p->shape.chunk = 16;
+  p->delays_host = row.tables.delays_host;
+  for (int tpw : {12, 8}) {
+    if (tpw == 12 && row.D > 1) continue;
+    p->shape.tpw = tpw;
+    p->shape.chunk = 16;
+    try {
+      PatHost H;
+      pat_tables_host(*p, H);
+      const double t = pat_clocks(*p, H);
+      if (t < best) {
+        best = t;
+        best_tpw = tpw;
+      }
+    } catch (const Error &e) {
+      if (e.status != GSP_EINVAL) throw;  // its partial sums do not fit the LDS
+    }
+  }
+  if (!best_tpw) return;
+  p->shape.tpw = best_tpw;
+  build_pat_tables(s->ctx, *p, true);
+  p->delays_host = std::vector<int32_t>();
+  row.lin_bytes = (p->q_pitch * nchan * NB + 256 + 255) / 256 * 256;
+  row.pat = std::move(p);
+}
+
+// Room for `want` bytes of linear copies, as far as memory that later
+// admissions may need is left alone; rows without room keep k_dedisp_jobs.
+static constexpr int64_t kLinMax = int64_t(8) << 30;
+void reserve_copies(gsp_stream *s, int64_t want) {
+  want = std::min(want, kLinMax);
+  if (want <= (int64_t)s->lin.bytes) return;
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return;
+  if ((int64_t)free_b + (int64_t)s->lin.bytes < want + (s->budget - s->used) + (int64_t(1) << 30)) return;
+  s->lin.device = s->ctx->device;
+  try {
+    s->lin.reserve((size_t)want);
+  } catch (const Error &) {
+    (void)hipGetLastError();  // no room after all
+  }
+}
+
 // Build the per-row state of a beam (host tables; device memory allocated at admission).
 void plan_beam(gsp_stream *s, Beam &b) {
   gsp_dmt_desc d;
@@ -445,6 +570,7 @@ void plan_beam(gsp_stream *s, Beam &b) {
     row->tables.dmin.device = s->ctx->device;
     // the staged rows are uint16 for every D in a stream (one kernel instance)
     build_row_tables(s->ctx, &d, b.freqs.data(), r, sh, row->tables, unit_max<uint16_t>());  // rings are uint16
+    plan_pattern(s, *row, b.nchan);
     b.rows.push_back(std::move(row));
   }
 }
@@ -498,6 +624,8 @@ void set_attributes(gsp_stream *s, int64_t dd_lds) {
   check_hip(hipFuncSetAttribute((const void *)k_dedisp_jobs<kStreamGroups, kStreamTpw>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)dd_lds),
             "set LDS size");
+  for (int k = 0; k < kPatForms; ++k)
+    if (s->pat_grid[k] > 0) set_pat_jobs_attributes(k);
 }
 
 // The fixed kernel sequence of a step (captured into the step graph).
@@ -510,6 +638,10 @@ void launch_sequence(gsp_stream *s, int64_t dd_lds) {
   hipLaunchKernelGGL(k_tail, dim3((unsigned)grid_of(4)), dim3(256), (size_t)s->look * 4, st,
                      s->d_tail.as<TailTable>());
   hipLaunchKernelGGL(k_stage_ring, dim3((unsigned)grid_of(4)), dim3(256), 0, st, s->d_stage.as<StageTable>());
+  if (s->pat_grid[0] + s->pat_grid[1] + s->pat_grid[2] > 0)
+    hipLaunchKernelGGL(k_unring, dim3((unsigned)grid_of(8)), dim3(256), 0, st, s->d_unring.as<UnringTable>());
+  for (int k = 0; k < kPatForms; ++k)
+    if (s->pat_grid[k] > 0) launch_pat_jobs(k, s->d_pat[k].as<PatJobTable>(), s->pat_grid[k], st);
   auto kd = k_dedisp_jobs<kStreamGroups, kStreamTpw>;
   hipLaunchKernelGGL(kd, dim3((unsigned)grid_of(2)), dim3(64 * kStreamWaves), (size_t)dd_lds, st,
                      s->d_dedisp.as<DedispTable>());
@@ -558,6 +690,17 @@ int64_t step_once(gsp_stream *s) {
   tr.n_jobs = 0;
   tt.n_jobs = 0;
   tt.n_trials = 0;
+  UnringTable &tu = *s->h_unring;
+  tu.n_jobs = 0;
+  tu.n_items = 0;
+  int64_t lin_want = 0, lin_used = 0;
+  for (auto &w : work)
+    for (auto &r : w.b->rows) lin_want += r->lin_bytes;
+  if (lin_want > 0) reserve_copies(s, lin_want);
+  for (auto &t : s->h_pat) {
+    t->n_jobs = 0;
+    t->n_items = 0;
+  }
   int64_t dd_lds = 0;
   struct JobRef {
     Beam *b;
@@ -604,39 +747,65 @@ int64_t step_once(gsp_stream *s) {
       if (e <= a) continue;
       R.emitted = e;
       // dedispersion job over outputs [a, e)
-      if (td.n_jobs >= kMaxJobs || tr.n_jobs >= kMaxJobs) fail(GSP_ECAPACITY, "too many streaming jobs");
-      DedispJob &D = td.job[td.n_jobs++];
-      const RowTables &rt = R.tables;
-      DedispArgs &A = D.a;
-      A.seg_ch = 0;  // one output for all channels
-      A.seg_stride = 0;
       const int64_t origin = a & ~int64_t(3);
-      A.Y = R.ring.ptr;
-      A.pitch = R.R + kGuard;
-      A.addr = rt.addr.as<uint32_t>();
-      A.base = rt.dmin.as<int32_t>();
-      A.out = R.win.as<int32_t>() + s->look;
-      A.out_pitch = s->look + R.Wcap;
-      A.t_origin = origin;
-      A.t_lo = a;
-      A.t_hi = e;
-      A.ring = R.R;
-      A.phys0 = origin % R.R;
-      A.n_dm = R.n_dm;
-      const int MT = rt.shape.trials_per_block();
-      A.n_dm_tiles = (R.n_dm + MT - 1) / MT;
-      A.n_dm_pad = A.n_dm_tiles * MT;
-      A.nchan = b.nchan;
-      A.chunks = rt.passes.as<int32_t>();
-      A.n_chunks = rt.n_passes;
-      A.max_chunk = rt.max_chunk;
-      A.data_dw = rt.data_dw;
-      A.flush = std::max(1, std::min(65535 / (255 * R.D), 256));
-      const int64_t T = rt.shape.samples_per_block();
-      A.n_t_tiles = (int32_t)((e - origin + T - 1) / T);
-      D.item0 = td.n_items;
-      td.n_items += (int64_t)A.n_dm_tiles * A.n_t_tiles;
-      dd_lds = std::max<int64_t>(dd_lds, rt.lds_bytes);
+      if (R.pat && lin_used + R.lin_bytes <= (int64_t)s->lin.bytes) {
+        // samples [origin, N1) copied out of the ring, then the pattern tile
+        const RowTables &rt = *R.pat;
+        if (tu.n_jobs >= kMaxJobs || tr.n_jobs >= kMaxJobs) fail(GSP_ECAPACITY, "too many streaming jobs");
+        UnringJob &U = tu.job[tu.n_jobs++];
+        U.Y = R.ring.as<uint16_t>();
+        U.dst = s->lin.as<uint8_t>() + lin_used;
+        U.pitch = R.R + kGuard;
+        U.ring = R.R;
+        U.phys0 = origin % R.R;
+        U.count = N1 - origin;
+        U.dpitch = rt.q_pitch;
+        U.nchan = b.nchan;
+        U.NB = R.D == 1 ? 1 : 2;
+        U.chunks = (int32_t)((U.count + kUnringChunk - 1) / kUnringChunk);
+        U.item0 = tu.n_items;
+        tu.n_items += (int64_t)U.nchan * U.chunks;
+        lin_used += R.lin_bytes;
+        PatJobTable &tp = *s->h_pat[pat_form(rt)];
+        PatJob &P = tp.job[tp.n_jobs++];
+        P.a = pat_args(rt, U.dst, R.win.as<int32_t>() + s->look - (a - origin), s->look + R.Wcap,
+                       (int32_t)(a - origin), e - origin);
+        P.item0 = tp.n_items;
+        tp.n_items += (int64_t)P.a.n_dm_tiles * P.a.n_t_tiles;
+      } else {
+        if (td.n_jobs >= kMaxJobs || tr.n_jobs >= kMaxJobs) fail(GSP_ECAPACITY, "too many streaming jobs");
+        DedispJob &D = td.job[td.n_jobs++];
+        const RowTables &rt = R.tables;
+        DedispArgs &A = D.a;
+        A.seg_ch = 0;  // one output for all channels
+        A.seg_stride = 0;
+        A.Y = R.ring.ptr;
+        A.pitch = R.R + kGuard;
+        A.addr = rt.addr.as<uint32_t>();
+        A.base = rt.dmin.as<int32_t>();
+        A.out = R.win.as<int32_t>() + s->look;
+        A.out_pitch = s->look + R.Wcap;
+        A.t_origin = origin;
+        A.t_lo = a;
+        A.t_hi = e;
+        A.ring = R.R;
+        A.phys0 = origin % R.R;
+        A.n_dm = R.n_dm;
+        const int MT = rt.shape.trials_per_block();
+        A.n_dm_tiles = (R.n_dm + MT - 1) / MT;
+        A.n_dm_pad = A.n_dm_tiles * MT;
+        A.nchan = b.nchan;
+        A.chunks = rt.passes.as<int32_t>();
+        A.n_chunks = rt.n_passes;
+        A.max_chunk = rt.max_chunk;
+        A.data_dw = rt.data_dw;
+        A.flush = std::max(1, std::min(65535 / (255 * R.D), 256));
+        const int64_t T = rt.shape.samples_per_block();
+        A.n_t_tiles = (int32_t)((e - origin + T - 1) / T);
+        D.item0 = td.n_items;
+        td.n_items += (int64_t)A.n_dm_tiles * A.n_t_tiles;
+        dd_lds = std::max<int64_t>(dd_lds, rt.lds_bytes);
+      }
       // search job over the window, boxes reaching back into the look-back
       SeriesJob &S = tr.job[tr.n_jobs++];
       S.x = R.win.as<int32_t>();
@@ -676,10 +845,29 @@ int64_t step_once(gsp_stream *s) {
   check_hip(hipMemcpyAsync(s->d_dedisp.ptr, &td, sizeof(DedispTable), hipMemcpyHostToDevice, st), "copy tables");
   check_hip(hipMemcpyAsync(s->d_series.ptr, &tr, sizeof(SeriesTable), hipMemcpyHostToDevice, st), "copy tables");
   check_hip(hipMemcpyAsync(s->d_tail.ptr, &tt, sizeof(TailTable), hipMemcpyHostToDevice, st), "copy tables");
-  // kernels: replay the captured graph (re-captured if the LDS need grew)
+  bool regrid = false;  // more workgroups than the graph was captured with
+  auto upload = [&](DevBuf &dst, const void *src, size_t used, size_t all) {
+    dst.device = s->ctx->device;
+    dst.reserve(all);
+    check_hip(hipMemcpyAsync(dst.ptr, src, used, hipMemcpyHostToDevice, st), "copy tables");
+  };
+  bool pattern = tu.n_jobs > 0;
+  for (int k = 0; k < kPatForms; ++k) pattern |= s->pat_grid[k] > 0;
+  if (pattern)
+    upload(s->d_unring, &tu, offsetof(UnringTable, job) + sizeof(UnringJob) * (size_t)tu.n_jobs, sizeof(UnringTable));
+  for (int k = 0; k < kPatForms; ++k) {
+    const PatJobTable &tp = *s->h_pat[k];
+    if (tp.n_items > s->pat_grid[k]) {
+      s->pat_grid[k] = tp.n_items;
+      regrid = true;
+    }
+    if (s->pat_grid[k] > 0)
+      upload(s->d_pat[k], &tp, offsetof(PatJobTable, job) + sizeof(PatJob) * (size_t)tp.n_jobs, sizeof(PatJobTable));
+  }
+  // kernels: replay the captured graph (re-captured if the LDS need or the pattern tiles grew)
   const int64_t lds_need = std::max<int64_t>(dd_lds, 64 * 1024);
   if (s->use_graph) {
-    if (!s->exec || lds_need > s->graph_lds) {
+    if (!s->exec || lds_need > s->graph_lds || regrid) {
       if (s->exec) (void)hipGraphExecDestroy(s->exec);
       if (s->graph) (void)hipGraphDestroy(s->graph);
       s->exec = nullptr;

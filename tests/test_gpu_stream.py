@@ -397,3 +397,50 @@ def test_full_shape_windows_equal_batch_and_oracle(env):
     say(f"  streamed candidates of {sum(map(len, cand_trials))} trials match the oracle ({n_cmp} oracle runs)")
     del dmt
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("nchan,block,graph", [(256, 8192, True), (203, 4112, False), (1024, 2064, True)])
+def test_pattern_rows_equal_batch(env, nchan, block, graph):
+    """Rows large enough for the pattern tile (copied out of their rings, which
+    these lengths wrap at many offsets), two beams in a mix, and rows of the
+    other tile beside them: every window equals the batch dedispersion on the
+    16-bit tile; the first windows are short, and the last block is."""
+    gsp, ctx, torch = env
+    segs = [(0.0, 0.05, 400, 1), (20.0, 0.1, 330, 2), (53.0, 0.2, 300, 4), (113.0, 30.0, 3, 4)]
+    freqs = 1400.0 + (np.arange(nchan) + 0.5) * 100.0 / nchan
+    ts = 49.152e-6
+    n_blk, last = 7, block // 2
+    nsamp = (n_blk - 1) * block + last
+    rng = np.random.default_rng(nchan)
+    X = [rng.integers(0, 256, (nsamp, nchan), dtype=np.uint8) for _ in range(2)]
+    X[1][:] = 255
+    desc = gsp.plan_shape(nsamp, freqs, ts, segs)
+    ref = []
+    for x in X:
+        c = gsp.Context(0)
+        for r in range(len(segs)):
+            c.set_row_shape(freqs, desc, r, 4, 4, 8, 32, 0)
+        v = gsp.segment_views(desc, c.dedisperse(torch.from_numpy(x).cuda(), freqs, desc))
+        ref.append([t.cpu().numpy() for t in v])
+        c.close()
+    s = gsp.Stream(ctx, 1 << 34, block, WIDTHS, 50.0)
+    s.set_graph(graph)
+    ids = [s.open_beam(nchan, freqs, ts, segs)[0] for _ in X]
+    say(f"[case] stream pattern rows, {nchan} channels, blocks of {block}")
+    checked = 0
+    for k in range(n_blk - 1):
+        for bid, x in zip(ids, X):
+            s.push(bid, x[k * block:(k + 1) * block])
+        assert s.step() == 2
+        for bid, full in zip(ids, ref):
+            for r, seg in enumerate(segs):
+                M = nsamp // seg[3] - int(desc.n_out[r])
+                a, b = max(0, k * block // seg[3] - M), max(0, (k + 1) * block // seg[3] - M)
+                t0, arr = s.window(bid, r, seg[2])
+                assert (t0, arr.shape[1]) == (a, b - a), (k, r)
+                assert np.array_equal(arr, full[r][:, a:b]), (k, r)
+                checked += b - a
+    assert checked > 0
+    s.push(ids[0], X[0][(n_blk - 1) * block:])  # a short last block: the beam ends
+    assert s.step() == 1
+    s.close()
