@@ -20,8 +20,9 @@
 //    consecutive samples of a channel, so it is a plain load: the host lets
 //    every channel's shifts start at a 4-byte boundary (loads from other
 //    addresses take 4 times as long: 65 against 16 clocks per 64 lanes).  A
-//    lane's 4 consecutive x take one load (uint8) or two, x + 1 multiplying
-//    the window of x with the one-hot matrix moved on by a sample.
+//    lane's 8 consecutive x take one 16-byte load (uint8; 4 to a 12-byte load
+//    gave a wide band's D = 1 row 44.6 ms, now 40.3), 4 take two (16 bits); x +
+//    1 multiplies the window of x with the one-hot matrix moved on by a sample.
 //    uint8 samples enter as x - 128 (signed bytes; the accumulator starts at
 //    128 per channel); the 11-bit sums of D <= 8 samples enter as two bytes
 //    (x >> 4) and (x & 15) whose one-hot weights are 16 and 1.  Sums are exact
@@ -40,7 +41,7 @@
 // the building waves third.  Measured on the survey plan (4096 channels, 2^20
 // samples, rows D = 1, 2, 4, 8): 49.7, 25.1, 12.8 and 7.0 ms (129, 84, 60 and
 // 40 T sample-adds/s) against 111, 78, 29 and 11 ms on the byte-quad tile
-// (D = 1) and the 16-bit tile; on 270-1620 MHz the D = 1 row takes 44.6 ms
+// (D = 1) and the 16-bit tile; on 270-1620 MHz the D = 1 row takes 40.3 ms
 // against 70.7.
 #include <algorithm>
 #include <array>
@@ -66,11 +67,15 @@ typedef uint32_t u32x2_a __attribute__((ext_vector_type(2), aligned(4)));
 typedef uint32_t u32x3_a __attribute__((ext_vector_type(3), aligned(4)));
 typedef uint32_t u32x4_a __attribute__((ext_vector_type(4), aligned(4)));
 
-// Samples of one channel from a lane's first position on, as loaded:
-// NB = 1: 12 bytes; NB = 2: 16 bytes, and 16 from the third sample on
+// positions between a building lane's rows (and the 4 or 8 of each that it
+// takes): with uint8 samples a 16-byte load holds the windows of 8 positions;
+// 16-bit ones would need 32 registers more
+constexpr int pat_rows(int NB) { return NB == 1 ? 8 : 4; }
+// Samples of one channel from a lane's first position on: NB = 1: 16; NB = 2:
+// 8, and 8 from the third on
 template <int NB>
 struct PatRaw {
-  uint32_t w[NB == 1 ? 3 : 8];
+  uint32_t w[4 * NB];
 };
 
 // TPW: trials per summing wave; NB: bytes per staged sample
@@ -104,8 +109,9 @@ __device__ __forceinline__ void pat_tile(const PatArgs &a, const int L, uint32_t
     // samples and patterns into one of NS register sets.  (Loads run up to 4
     // units past the tile's last one; the table has that many to spare.)
     __builtin_amdgcn_s_setprio(2);
+    constexpr int RS = pat_rows(NB);
     const int bw = wave - NC;
-    const int m = lane & 15, kg = lane >> 4;  // A: row m (positions x + 4m + jj); B: column m; k: channels 2kg, 2kg + 1
+    const int m = lane & 15, kg = lane >> 4;  // A: row m (positions x + RS m + j); B: column m; k: channels 2kg, 2kg + 1
     typedef const __attribute__((address_space(4))) int cint;
     typedef const __attribute__((address_space(4))) PatUnit cunit;
     cint *passes = (cint *)(a.passes + p_first);
@@ -125,7 +131,7 @@ __device__ __forceinline__ void pat_tile(const PatArgs &a, const int L, uint32_t
       u32x3_a r;             // the lane's pattern record
       int x, rel;            // first position, less the subgroup's first one
     };
-    const uint32_t lane_x = (uint32_t)(t0 + 4 * m) * NB;
+    const uint32_t lane_x = (uint32_t)(t0 + RS * m) * NB;
     auto load = [&](Set &s, const Unit &h, const int2 co) {
       const uint8_t *base = a.Y + h.base + h.x * NB;
 #pragma unroll
@@ -135,14 +141,10 @@ __device__ __forceinline__ void pat_tile(const PatArgs &a, const int L, uint32_t
         for (int hf = 0; hf < 2; ++hf) {
           const uint8_t *p = base + vo + hf * kPatH * NB;
           uint32_t *w = s.raw[hf][e].w;
-          if constexpr (NB == 1) {
-            const u32x3_a v = *reinterpret_cast<const u32x3_a *>(p);
-            w[0] = v.x, w[1] = v.y, w[2] = v.z;
-          } else {
-            const u32x4_a v = *reinterpret_cast<const u32x4_a *>(p);
-            const u32x4_a v2 = *reinterpret_cast<const u32x4_a *>(p + 4);
-            w[0] = v.x, w[1] = v.y, w[2] = v.z, w[3] = v.w;
-            w[4] = v2.x, w[5] = v2.y, w[6] = v2.z, w[7] = v2.w;
+#pragma unroll
+          for (int q = 0; q < NB; ++q) {
+            const u32x4_a v = *reinterpret_cast<const u32x4_a *>(p + 4 * q);
+            w[4 * q] = v.x, w[4 * q + 1] = v.y, w[4 * q + 2] = v.z, w[4 * q + 3] = v.w;
           }
         }
       }
@@ -157,11 +159,12 @@ __device__ __forceinline__ void pat_tile(const PatArgs &a, const int L, uint32_t
       if constexpr (NB == 1) {  // the lane's two channels, 8 bytes each
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-          uint32_t w[3];
+          uint32_t w[4];
 #pragma unroll
-          for (int q = 0; q < 3; ++q) w[q] = s.raw[hf][e].w[q] ^ 0x80808080u;  // x - 128
-          A[2 * e] = (int)(j2 ? __builtin_amdgcn_alignbyte(w[1], w[0], 2) : w[0]);
-          A[2 * e + 1] = (int)(j2 ? __builtin_amdgcn_alignbyte(w[2], w[1], 2) : w[1]);
+          for (int q = 0; q < 4; ++q) w[q] = s.raw[hf][e].w[q] ^ 0x80808080u;  // x - 128
+          const int f = j2 >> 1;
+          A[2 * e] = (int)((j2 & 1) ? __builtin_amdgcn_alignbyte(w[f + 1], w[f], 2) : w[f]);
+          A[2 * e + 1] = (int)((j2 & 1) ? __builtin_amdgcn_alignbyte(w[f + 2], w[f + 1], 2) : w[f + 1]);
         }
       } else {  // channel ks of the two, 16 bytes
 #pragma unroll
@@ -172,7 +175,7 @@ __device__ __forceinline__ void pat_tile(const PatArgs &a, const int L, uint32_t
     const v4i bias = NB == 1 ? v4i{128 * kPatG, 128 * kPatG, 128 * kPatG, 128 * kPatG} : v4i{0, 0, 0, 0};
     // Pattern record of a lane: {LDS dword of the subgroup's first position,
     // the pattern's first position less that one | positions << 16 (both
-    // multiples of 16), one-hot bytes or words: for each of the lane's two
+    // multiples of 4 RS), one-hot bytes or words: for each of the lane's two
     // channels 8 bits per 64 bits of operand B, shift (6 bits) and validity}
     auto compute = [&](const Set &s, uint32_t *dst) {
       v4i B[2][NB];  // for position offsets 2 j2, and 2 j2 + 1: the same shifts plus one
@@ -201,34 +204,39 @@ __device__ __forceinline__ void pat_tile(const PatArgs &a, const int L, uint32_t
       // LDS (a shift and or per dword, no moves); NB = 2 starts the second
       // from the first
       v4i D[2][4];
+      const uint32_t p = (uint32_t)(s.rel + 4 * RS * kg);
+      const bool valid = p - (s.r.y & 0xFFFFu) < (s.r.y >> 16);
+      uint32_t *d = dst + (s.r.x + p);
 #pragma unroll
-      for (int hf = 1; hf >= 0; --hf) {
+      for (int j4 = 0; j4 < RS / 4; ++j4) {  // position offsets 4 j4 + jj
 #pragma unroll
-        for (int ks = 0; ks < NB; ++ks) {
-          const v4i A[2] = {make_a(s, hf, ks, 0), make_a(s, hf, ks, 1)};
+        for (int hf = 1; hf >= 0; --hf) {
 #pragma unroll
-          for (int jj = 0; jj < 4; ++jj) {
-            const v4i c = ks ? D[hf][jj] : NB == 1 || hf ? bias : D[1][jj] << 16;
-            D[hf][jj] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[jj >> 1], B[jj & 1][ks], c, 0, 0, 0);
+          for (int ks = 0; ks < NB; ++ks) {
+            const v4i A[2] = {make_a(s, hf, ks, 2 * j4), make_a(s, hf, ks, 2 * j4 + 1)};
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+              const v4i c = ks ? D[hf][jj] : NB == 1 || hf ? bias : D[1][jj] << 16;
+              D[hf][jj] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[jj >> 1], B[jj & 1][ks], c, 0, 0, 0);
+            }
           }
         }
-      }
-      // lane (column m, row block kg): positions x = s.x + 16 kg + 4 q + jj
-      const uint32_t p = (uint32_t)(s.rel + 16 * kg);
-      if (p - (s.r.y & 0xFFFFu) < (s.r.y >> 16)) {
-        uint32_t *d = dst + (s.r.x + p);
+        // lane (column m, row block kg): positions x = s.x + 4 RS kg + RS q + 4 j4 + jj
+        if (valid) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          v4i w;
+          for (int q = 0; q < 4; ++q) {
+            v4i w;
 #pragma unroll
-          for (int jj = 0; jj < 4; ++jj) w[jj] = NB == 1 ? D[0][jj][q] | D[1][jj][q] << 16 : D[0][jj][q];
-          *reinterpret_cast<v4i *>(d + 4 * q) = w;
+            for (int jj = 0; jj < 4; ++jj) w[jj] = NB == 1 ? D[0][jj][q] | D[1][jj][q] << 16 : D[0][jj][q];
+            *reinterpret_cast<v4i *>(d + RS * q + 4 * j4) = w;
+          }
         }
+        if (j4 + 1 < RS / 4) __builtin_amdgcn_sched_barrier(0);  // registers for one half's products
       }
     };
     // NS sets in turn: unit k's inputs are in set k % NS, those of the NS - 1
     // units before it in flight; its offsets are loaded a unit before its samples
-    constexpr int NS = NB == 1 ? 3 : 2;
+    constexpr int NS = 2;
     Set set[NS];
     int2 co[NS];      // offsets of the unit whose samples go to set k next
     Unit hd[NS];      // and its header
@@ -459,14 +467,14 @@ struct Pattern {
 
 void build_pat_tile(const RowTables &rt, int i0, int MT, const std::vector<int32_t> &first, PatTile &T) {
   const int nchan = rt.nchan, n_dm = rt.n_dm, ng = (int)first.size();
-  const int NB = rt.D == 1 ? 1 : 2;
+  const int NB = rt.D == 1 ? 1 : 2, RS = pat_rows(NB), run = 4 * RS - 1;
   const int32_t *d = rt.delays_host.data();
   T.addr.assign((size_t)ng * (MT / 2), 0);
   std::vector<Pattern> P;
   std::vector<int32_t> pat_of(MT), dst, xs;
   int64_t used = 0;
   int in_pass = 0;
-  // a pass's work goes to the building waves in turn, 64 positions of a
+  // a pass's work goes to the building waves in turn, 16 RS positions of a
   // subgroup (all their pattern blocks) to the one with the least so far;
   // their unit lists are interleaved, all filled up to the same length
   // with units of block 0, which has no patterns
@@ -511,8 +519,8 @@ void build_pat_tile(const RowTables &rt, int i0, int MT, const std::vector<int32
       }
       pat_of[j] = k;
     }
-    // LDS windows of whole 16-position runs (what a lane writes); the 16-byte
-    // chunk of a position differs by 1 mod 4 between neighbouring patterns,
+    // LDS windows of whole runs of 4 RS positions (what a lane writes); the 16-byte
+    // chunk of a position differs by 1 mod RS between neighbouring patterns,
     // which spreads the writes of 16 patterns over the banks (73 B/clk/CU
     // against 16 where they agree)
     const int np = (int)P.size();
@@ -520,9 +528,9 @@ void build_pat_tile(const RowTables &rt, int i0, int MT, const std::vector<int32
     xs.resize(np);
     auto place = [&](int64_t at) {
       for (int k = 0; k < np; ++k) {
-        const int32_t s = P[k].lo & ~15, e = (P[k].hi + kPatH + 15) & ~15;
+        const int32_t s = P[k].lo & ~run, e = (P[k].hi + kPatH + run) & ~run;
         xs[k] = s;
-        while ((((at - s) >> 2) & 3) != (k & 3)) at += 4;
+        while ((((at - s) >> 2) & (RS - 1)) != (k & (RS - 1))) at += 4;
         dst[k] = (int32_t)at;
         at += e - s;
       }
@@ -580,17 +588,17 @@ void build_pat_tile(const RowTables &rt, int i0, int MT, const std::vector<int32
       std::vector<int32_t> bs(nblk, INT32_MAX), be(nblk, 0);  // positions each block covers
       for (int k = s; k < e; ++k) {
         bs[(k - s) / 16] = std::min(bs[(k - s) / 16], xs[k]);
-        be[(k - s) / 16] = std::max(be[(k - s) / 16], (P[k].hi + kPatH + 15) & ~15);
+        be[(k - s) / 16] = std::max(be[(k - s) / 16], (P[k].hi + kPatH + run) & ~run);
       }
       const int32_t x0 = *std::min_element(bs.begin(), bs.end()), x1 = *std::max_element(be.begin(), be.end());
-      if (x1 - x0 >= 65536 - 64) {
+      if (x1 - x0 >= 65536 - 16 * RS) {
         T.err = "a channel group's delays spread too wide";
         return;
       }
       T.pats.resize(T.pats.size() + (size_t)nblk * kPatRec, 0);
       for (int k = s; k < e; ++k) {
         uint32_t *blk = T.pats.data() + (size_t)(blk0 + (k - s) / 16) * kPatRec;
-        const uint32_t len = (uint32_t)(((P[k].hi + kPatH + 15) & ~15) - xs[k]);
+        const uint32_t len = (uint32_t)(((P[k].hi + kPatH + run) & ~run) - xs[k]);
         for (int kg = 0; kg < 4; ++kg) {
           uint32_t *r = blk + 3 * (16 * kg + (k - s) % 16);
           r[0] = (uint32_t)(dst[k] - (xs[k] - x0));
@@ -606,16 +614,16 @@ void build_pat_tile(const RowTables &rt, int i0, int MT, const std::vector<int32
           }
         }
       }
-      for (int32_t x = x0; x < x1; x += 64) {
+      for (int32_t x = x0; x < x1; x += 16 * RS) {
         int b0 = nblk, b1 = -1;
         for (int b = 0; b < nblk; ++b)
-          if (bs[b] < x + 64 && be[b] > x) {
+          if (bs[b] < x + 16 * RS && be[b] > x) {
             b0 = std::min(b0, b);
             b1 = b;
           }
         if (b1 < 0) continue;
         todo.push_back({sub, x, x - x0, blk0 + b0, b1 - b0 + 1, g});
-        T.far = std::max<int64_t>(T.far, x + 60 + kPatH + max_lo + 12);
+        T.far = std::max<int64_t>(T.far, x + 15 * RS + kPatH + max_lo + 16);
       }
       s = e;
     }
@@ -724,18 +732,19 @@ void pat_tables_host(const RowTables &rt, PatHost &H) {
 }
 
 // Clocks of a row on the pattern tile, from the work that its tables list:
-// rounds of 256 workgroups (one to a CU), each some 20000 or 32000 clocks
-// (filling and draining), 145 per building unit (195 for 16-bit samples) and
-// 7.2 (8.4) per trial and group of 8 channels.  Fitted to the same 126 rows as
-// the other tiles, to 8 %.
+// rounds of 256 workgroups (one to a CU), each some 10000 or 22000 clocks
+// (filling and draining), 208 per building unit of 128 positions (183 for
+// 16-bit samples' 64) and 8.5 per trial and group of 8 channels.  Fitted to the
+// same 126 rows as the other tiles, to 7 %; D > 1 then 17 % up, so that no row
+// came out slower than on the other tile.
 double pat_clocks(const RowTables &rt, const PatHost &H) {
   const int ng = (rt.nchan + kPatG - 1) / kPatG, MT = rt.shape.trials_per_block();
   const int64_t n_dm_tiles = (rt.n_dm + MT - 1) / MT;
   const int64_t tiles = n_dm_tiles * ((rt.n_out + 2 * kPatH - 1) / (2 * kPatH));
   const double units = (double)(H.units.size() - 4 * kPatBuild) / (double)n_dm_tiles;
   const double rounds = (double)((tiles + 255) / 256);
-  return rt.D == 1 ? 15e3 + rounds * (20e3 + 145.0 * units + 7.2 * MT * ng)
-                   : 2e3 + rounds * (32e3 + 195.0 * units + 8.35 * MT * ng);
+  return rt.D == 1 ? 8.4e3 + rounds * (9.9e3 + 208.0 * units + 8.54 * MT * ng)
+                   : 1.17 * (0.5e3 + rounds * (21.9e3 + 183.0 * units + 8.67 * MT * ng));
 }
 
 // Whether the pattern tile beats the row's other default (the byte-quad tile's
@@ -743,8 +752,8 @@ double pat_clocks(const RowTables &rt, const PatHost &H) {
 // not where the channels are so wide, or the trials so far apart, that most
 // trials have patterns of their own (64 channels over 500 MHz, 688 trials at
 // D = 2: 0.229 against 0.184 ms), nor for few trials of a tile.  Over the 126
-// rows the defaults so chosen take 1.69 times less time in the mean than
-// without the pattern tile, the fastest choice for each row 1.70 times.
+// rows the defaults so chosen take 1.78 times less time in the mean than
+// without the pattern tile, the fastest choice for each row 1.79 times.
 bool pat_tables_pay(const RowTables &rt, const PatHost &H) {
   double other = plain_clocks(rt.n_dm, rt.n_out, rt.nchan);
   if (rt.D == 1 && rt.nchan % 4 == 0) other = std::min(other, 1.25 * quad_clocks(rt.n_dm, rt.n_out, rt.nchan));

@@ -277,7 +277,7 @@ void launch_dedisp_quad(gsp_ctx *ctx, const RowTables &rt, int32_t *out_row, hip
 // (kind 4); GSP_EINVAL when the row does not suit it (D > 8, a group's
 // partial sums wider than the LDS)
 bool pat_shape_supported(const DedispShape &s);
-struct PatUnit {                   // building work: 64 positions x 16 patterns
+struct PatUnit {                   // building work: 128 or 64 positions x 16 patterns
   int64_t base;                    // byte offset of the group's first channel row
   int32_t x;                       // first position
   int32_t rel;                     // ... less the subgroup's first one
