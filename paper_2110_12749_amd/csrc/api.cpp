@@ -298,28 +298,31 @@ int gsp_single_pulse_search(gsp_ctx *ctx, const int32_t *dmt, const gsp_dmt_desc
     std::sort(w.begin(), w.end());
     w.erase(std::unique(w.begin(), w.end()), w.end());
     hipStream_t st = static_cast<hipStream_t>(stream);
-    ctx->widths.device = ctx->device;
-    ctx->widths.reserve(w.size() * sizeof(int32_t));
-    check_hip(hipMemcpyAsync(ctx->widths.ptr, w.data(), w.size() * sizeof(int32_t), hipMemcpyHostToDevice, st),
-              "copy widths");
-    ctx->counter.device = ctx->device;
-    ctx->counter.reserve(sizeof(unsigned long long));
     ctx->frags.device = ctx->device;
-    int64_t cap = std::max<int64_t>(1 << 16, (int64_t)(ctx->frags.bytes / sizeof(Frag)));
-    launch_stats(ctx, dmt, desc, st);
+    // the counter and the fragments behind it, of which the first come to the
+    // host with the counter
+    constexpr size_t kHead = 64, kFirst = 256;
+    int64_t cap = std::max<int64_t>(1 << 16, ((int64_t)ctx->frags.bytes - (int64_t)kHead) / (int64_t)sizeof(Frag));
     unsigned long long count = 0;
+    std::vector<unsigned char> head(kHead + kFirst * sizeof(Frag));
     for (int pass = 0; pass < 2; ++pass) {
-      ctx->frags.reserve((size_t)cap * sizeof(Frag));
-      launch_search(ctx, dmt, desc, ctx->widths.as<int32_t>(), (int32_t)w.size(), w.back(), threshold,
-                    ctx->frags.as<Frag>(), cap, ctx->counter.as<unsigned long long>(), st);
-      check_hip(hipMemcpyAsync(&count, ctx->counter.ptr, sizeof(count), hipMemcpyDeviceToHost, st), "copy count");
+      ctx->frags.reserve(kHead + (size_t)cap * sizeof(Frag));
+      unsigned char *base = ctx->frags.as<unsigned char>();
+      launch_search(ctx, dmt, desc, w, threshold, pass == 0, reinterpret_cast<Frag *>(base + kHead), cap,
+                    reinterpret_cast<unsigned long long *>(base), st);
+      check_hip(hipMemcpyAsync(head.data(), base, head.size(), hipMemcpyDeviceToHost, st), "copy count");
       check_hip(hipStreamSynchronize(st), "synchronise stream");
+      std::memcpy(&count, head.data(), sizeof(count));
       if ((int64_t)count <= cap) break;
       cap = (int64_t)count + 1024;  // rerun once with room for every fragment
     }
     std::vector<Frag> fr(count);
-    if (count)
-      check_hip(hipMemcpy(fr.data(), ctx->frags.ptr, count * sizeof(Frag), hipMemcpyDeviceToHost), "copy fragments");
+    const size_t first = std::min<size_t>(count, kFirst);
+    if (count) std::memcpy(fr.data(), head.data() + kHead, first * sizeof(Frag));
+    if (count > first)
+      check_hip(hipMemcpy(fr.data() + first, ctx->frags.as<unsigned char>() + kHead + first * sizeof(Frag),
+                          (count - first) * sizeof(Frag), hipMemcpyDeviceToHost),
+                "copy fragments");
     // join fragments split at tile edges: order them by (trial, first box
     // end) with a counting pass over the trials and a sort of each trial's
     // few fragments (a trial's runs are disjoint, so the order is unique)

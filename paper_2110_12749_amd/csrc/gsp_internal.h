@@ -172,8 +172,7 @@ struct gsp_ctx {
     const int32_t *dmt = nullptr;  // set when a gsp_dedisperse into dmt staged them last
   } staged_tag;
   gsp::DevBuf stats;       // per-trial moments / mu / sigma
-  gsp::DevBuf frags;       // search run fragments
-  gsp::DevBuf counter;     // fragment counter
+  gsp::DevBuf frags;       // search: fragment counter (64 bytes), run fragments
   gsp::DevBuf widths;      // device copy of the width set
   gsp::DevBuf jobs;        // device copy of the series-job table
   gsp::DevBuf ftsums;      // frequency-time band sums of batch cutouts
@@ -181,7 +180,6 @@ struct gsp_ctx {
   gsp::DevBuf rfi;         // RFI mitigation: spectrum sums, flags, block means
   gsp::DevBuf zbuf;        // sub-band series of sub-band dedispersion
   std::map<std::string, std::shared_ptr<gsp::SubbandPlan>> subband;
-  std::unique_ptr<gsp::SeriesTable> jobs_host = std::make_unique<gsp::SeriesTable>();
   std::vector<uint8_t> host_scratch;
   // tuned shapes keyed by row signature
   std::map<std::string, gsp::DedispShape> tuned;
@@ -341,7 +339,7 @@ void launch_stats_table(gsp_ctx *ctx, const SeriesTable *tb_dev, int64_t grid, d
 void launch_search_table(gsp_ctx *ctx, const SeriesTable *tb_dev, int64_t grid, const SearchTiling &tl,
                          const double *musig, const int32_t *widths_dev, int32_t n_widths, int32_t max_width,
                          float thr, Frag *frags, int64_t cap, unsigned long long *counter, double bytes,
-                         hipStream_t st);
+                         hipStream_t st, bool zeroed = false);
 
 void launch_stats(gsp_ctx *ctx, const int32_t *dmt, const gsp_dmt_desc *desc, hipStream_t st,
                   const uint32_t *need = nullptr);
@@ -366,9 +364,8 @@ void launch_cutouts_stream(const StreamCut *cuts_dev, int64_t n, uint16_t *out_d
 
 // Device pointer of per-trial mu/sigma (double[2*n_trials]) after launch_stats.
 const double *stats_musig(gsp_ctx *ctx, const gsp_dmt_desc *desc);
-void launch_search(gsp_ctx *ctx, const int32_t *dmt, const gsp_dmt_desc *desc, const int32_t *widths_dev,
-                   int32_t n_widths, int32_t max_width, float thr, Frag *frags, int64_t cap,
-                   unsigned long long *counter, hipStream_t st);
+void launch_search(gsp_ctx *ctx, const int32_t *dmt, const gsp_dmt_desc *desc, const std::vector<int32_t> &widths,
+                   float thr, bool stats, Frag *frags, int64_t cap, unsigned long long *counter, hipStream_t st);
 
 }  // namespace gsp
 

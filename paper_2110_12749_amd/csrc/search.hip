@@ -25,6 +25,7 @@
 //           where a box can pass, and run fragments appended with one atomic
 //           each (joined on the host).
 #include <algorithm>
+#include <cstring>
 #include <vector>
 
 #include "gsp_internal.h"
@@ -694,7 +695,8 @@ static SearchTiling batch_tiling(const gsp_dmt_desc *desc, int32_t max_width) {
   return t;
 }
 
-void finalize_table(SeriesTable &t, const SearchTiling &tl) {
+template <class Table>
+static void finalize_jobs(Table &t, const SearchTiling &tl) {
   int64_t nb = 0;
   int32_t trials = 0;
   for (int j = 0; j < t.n_jobs; ++j) {
@@ -708,6 +710,7 @@ void finalize_table(SeriesTable &t, const SearchTiling &tl) {
   t.n_items = nb;
   t.n_trials = trials;
 }
+void finalize_table(SeriesTable &t, const SearchTiling &tl) { finalize_jobs(t, tl); }
 
 void launch_stats_table(gsp_ctx *ctx, const SeriesTable *tb_dev, int64_t grid, double *musig, double bytes,
                         hipStream_t st, const uint32_t *need) {
@@ -720,7 +723,7 @@ void launch_stats_table(gsp_ctx *ctx, const SeriesTable *tb_dev, int64_t grid, d
 void launch_search_table(gsp_ctx *ctx, const SeriesTable *tb_dev, int64_t grid, const SearchTiling &tl,
                          const double *musig, const int32_t *widths_dev, int32_t n_widths, int32_t max_width,
                          float thr, Frag *frags, int64_t cap, unsigned long long *counter, double bytes,
-                         hipStream_t st) {
+                         hipStream_t st, bool zeroed) {
   SearchArgs a;
   a.tb = tb_dev;
   a.musig = musig;
@@ -732,7 +735,7 @@ void launch_search_table(gsp_ctx *ctx, const SeriesTable *tb_dev, int64_t grid, 
   a.frags = frags;
   a.cap = cap;
   a.counter = counter;
-  hipLaunchKernelGGL(k_zero_counter, dim3(1), dim3(1), 0, st, counter);
+  if (!zeroed) hipLaunchKernelGGL(k_zero_counter, dim3(1), dim3(1), 0, st, counter);
   if (grid <= 0) return;
   if (grid >= (1LL << 31)) fail(GSP_EOVERFLOW, "too many search workgroups");
   ProfScope prof(ctx, "search", st, bytes);
@@ -746,58 +749,85 @@ void launch_search_table(gsp_ctx *ctx, const SeriesTable *tb_dev, int64_t grid, 
   check_hip(hipGetLastError(), "launch search kernel");
 }
 
-// Batch: one job per plan row over the whole dedispersed output.
-static void batch_table(const gsp_dmt_desc *desc, const int32_t *dmt, SeriesTable &t) {
-  t.n_jobs = desc->n_seg;
-  for (int s = 0; s < desc->n_seg; ++s) {
-    SeriesJob &J = t.job[s];
-    J.x = dmt + desc->offset[s];
-    J.pitch = desc->n_out[s];
-    J.e_begin = 0;
-    J.n = desc->n_out[s];
-    J.look = 0;
-    J.abs0 = 0;
-    J.n_dm = desc->seg[s].n_dm;
+// Batch: one job per plan row over the whole dedispersed output.  The job table
+// and the widths go to the device as arguments of the kernel that puts them in
+// place (and clears the fragment counter): copies of the 80 KB table, twice, of
+// the widths and of the counter took some 40 us of a quick look's 140.
+struct BatchJobs {
+  SeriesJob job[GSP_MAX_SEG];
+  int32_t n_jobs, n_trials;
+  int64_t n_items;
+  int32_t widths[64];
+  int32_t n_widths;
+};
+static_assert(sizeof(BatchJobs) < 4000, "kernel argument size");
+
+__global__ __launch_bounds__(64) void k_put_batch(BatchJobs b, SeriesTable *t, int32_t *widths,
+                                                  unsigned long long *counter) {
+  const int j = threadIdx.x;
+  if (j < b.n_jobs) t->job[j] = b.job[j];
+  if (j < b.n_widths) widths[j] = b.widths[j];
+  if (j == 0) {
+    t->n_jobs = b.n_jobs;
+    t->n_trials = b.n_trials;
+    t->n_items = b.n_items;
+    if (counter) *counter = 0ull;
   }
 }
 
-static SeriesTable *upload_table(gsp_ctx *ctx, const SeriesTable &t, hipStream_t st) {
+static SeriesTable *put_batch(gsp_ctx *ctx, const gsp_dmt_desc *desc, const int32_t *dmt, const SearchTiling &tl,
+                              const std::vector<int32_t> &widths, unsigned long long *counter, BatchJobs &b,
+                              hipStream_t st) {
+  std::memset(&b, 0, sizeof(b));
+  b.n_jobs = desc->n_seg;
+  for (int s = 0; s < desc->n_seg; ++s) {
+    SeriesJob &J = b.job[s];
+    J.x = dmt + desc->offset[s];
+    J.pitch = desc->n_out[s];
+    J.n = desc->n_out[s];
+    J.n_dm = desc->seg[s].n_dm;
+  }
+  finalize_jobs(b, tl);
+  b.n_widths = (int32_t)widths.size();
+  std::copy(widths.begin(), widths.end(), b.widths);
   ctx->jobs.device = ctx->device;
   ctx->jobs.reserve(sizeof(SeriesTable));
-  *ctx->jobs_host = t;
-  check_hip(hipMemcpyAsync(ctx->jobs.ptr, ctx->jobs_host.get(), sizeof(SeriesTable), hipMemcpyHostToDevice, st),
-            "copy job table");
+  if (b.n_widths) {
+    ctx->widths.device = ctx->device;
+    ctx->widths.reserve(sizeof(b.widths));
+  }
+  hipLaunchKernelGGL(k_put_batch, dim3(1), dim3(64), 0, st, b, ctx->jobs.as<SeriesTable>(), ctx->widths.as<int32_t>(),
+                     counter);
+  check_hip(hipGetLastError(), "launch table setup");
+  ctx->stats.device = ctx->device;
+  ctx->stats.reserve((size_t)desc->n_trials * 2 * sizeof(double));
   return ctx->jobs.as<SeriesTable>();
 }
 
 void launch_stats(gsp_ctx *ctx, const int32_t *dmt, const gsp_dmt_desc *desc, hipStream_t st,
                   const uint32_t *need) {
-  ctx->stats.device = ctx->device;
-  ctx->stats.reserve((size_t)desc->n_trials * 2 * sizeof(double));
-  SeriesTable t;
-  batch_table(desc, dmt, t);
-  finalize_table(t, search_tiling(1));
-  SeriesTable *d = upload_table(ctx, t, st);
+  BatchJobs b;
+  SeriesTable *d = put_batch(ctx, desc, dmt, search_tiling(1), {}, nullptr, b, st);
   // bytes: the int32 DM-time array read once (the selected trials' rows only
   // when `need` is given; not known on the host then)
-  launch_stats_table(ctx, d, t.n_trials, ctx->stats.as<double>(), need ? 0.0 : 4.0 * (double)desc->total, st,
+  launch_stats_table(ctx, d, b.n_trials, ctx->stats.as<double>(), need ? 0.0 : 4.0 * (double)desc->total, st,
                      need);
 }
 
 const double *stats_musig(gsp_ctx *ctx, const gsp_dmt_desc *) { return ctx->stats.as<double>(); }
 
-void launch_search(gsp_ctx *ctx, const int32_t *dmt, const gsp_dmt_desc *desc, const int32_t *widths_dev,
-                   int32_t n_widths, int32_t max_width, float thr, Frag *frags, int64_t cap,
-                   unsigned long long *counter, hipStream_t st) {
-  const SearchTiling tl = batch_tiling(desc, max_width);
-  SeriesTable t;
-  batch_table(desc, dmt, t);
-  finalize_table(t, tl);
-  SeriesTable *d = upload_table(ctx, t, st);
-  set_search_attributes(tl);
+void launch_search(gsp_ctx *ctx, const int32_t *dmt, const gsp_dmt_desc *desc, const std::vector<int32_t> &widths,
+                   float thr, bool stats, Frag *frags, int64_t cap, unsigned long long *counter, hipStream_t st) {
+  const SearchTiling tl = batch_tiling(desc, widths.back());
+  BatchJobs b;
+  SeriesTable *d = put_batch(ctx, desc, dmt, tl, widths, counter, b, st);
   // bytes: the int32 DM-time array read once (look-back overlap not counted)
-  launch_search_table(ctx, d, (t.n_items + tl.waves - 1) / tl.waves, tl, stats_musig(ctx, desc), widths_dev, n_widths, max_width, thr, frags,
-                      cap, counter, 4.0 * (double)desc->total, st);
+  const double bytes = 4.0 * (double)desc->total;
+  if (stats) launch_stats_table(ctx, d, b.n_trials, ctx->stats.as<double>(), bytes, st, nullptr);
+  set_search_attributes(tl);
+  launch_search_table(ctx, d, (b.n_items + tl.waves - 1) / tl.waves, tl, stats_musig(ctx, desc),
+                      ctx->widths.as<int32_t>(), (int32_t)widths.size(), widths.back(), thr, frags, cap, counter, bytes,
+                      st, true);
 }
 
 }  // namespace gsp
