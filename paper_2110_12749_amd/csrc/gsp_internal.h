@@ -137,10 +137,10 @@ __device__ __forceinline__ T *as_global(T *p) {
 }
 static constexpr int kMaxJobs = 1024;
 struct SeriesTable {
-  SeriesJob job[kMaxJobs];
   int32_t n_jobs = 0;
   int32_t n_trials = 0;
   int64_t n_items = 0;
+  SeriesJob job[kMaxJobs];
 };
 struct SearchTiling {
   int ring = 1024;  // prefix sums kept per wave (power of two >= w_max + 512)

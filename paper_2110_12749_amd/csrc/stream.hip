@@ -29,7 +29,6 @@
 #include <chrono>
 #include <cmath>
 #include <condition_variable>
-#include <cstddef>
 #include <cstring>
 #include <deque>
 #include <mutex>
@@ -62,9 +61,9 @@ struct StageJob {
   int32_t t_tiles, c_tiles;
 };
 struct StageTable {
-  StageJob job[kMaxJobs];
-  int32_t n_jobs;
   int64_t n_items;
+  int32_t n_jobs;
+  StageJob job[kMaxJobs];  // last in every table: a step copies the used ones only
 };
 
 struct DedispJob {
@@ -72,9 +71,9 @@ struct DedispJob {
   int64_t item0;
 };
 struct DedispTable {
-  DedispJob job[kMaxJobs];
-  int32_t n_jobs;
   int64_t n_items;
+  int32_t n_jobs;
+  DedispJob job[kMaxJobs];
 };
 
 // A row's ring window as a linear copy in the pattern tile's form
@@ -105,9 +104,9 @@ struct TailJob {
   int32_t trial0;
 };
 struct TailTable {
-  TailJob job[kMaxJobs];
   int32_t n_jobs;
   int32_t n_trials;
+  TailJob job[kMaxJobs];
 };
 
 template <class Tab>
@@ -483,13 +482,16 @@ int64_t beam_bytes(const gsp_stream *s, const Beam &b) {
 
 // The pattern tile's tables of a row, where they fit and the tile is estimated
 // to be faster than k_dedisp_jobs's even after the window's copy (read as 16-bit
-// samples, written as NB bytes at 4.6 TB/s, 2.4 GHz).  4 beams of 4096 channels,
+// samples, written as NB bytes at 4.6 TB/s, 2.4 GHz) and 70000 clocks for the
+// launches and the tables it adds to a step and for rows that now run one after
+// the other (one beam of 256 channels with rows of 70, 120 and 45 trials: 0.65
+// ms a step without that margin, 0.64 before the pattern tile).  4 beams of 4096 channels,
 // 1175 trials and 20480 samples: 12.9 ms a step with k_dedisp_jobs, 4.6 with
 // the copies and the pattern tile.
 void plan_pattern(gsp_stream *s, StreamRow &row, int32_t nchan) {
   if (row.D > 8) return;  // the pattern tile's samples have 11 bits
   const int NB = row.D == 1 ? 1 : 2;
-  double best = plain_clocks(row.n_dm, row.Wcap, nchan) -
+  double best = plain_clocks(row.n_dm, row.Wcap, nchan) - 70e3 -
                 (double)nchan * (double)(row.Wcap + row.M) * (2 + NB) * 2.4e9 / 4.6e12;
   int best_tpw = 0;
   auto p = std::make_unique<RowTables>();
@@ -841,28 +843,27 @@ int64_t step_once(gsp_stream *s) {
   if (dd_lds == 0) dd_lds = 16;
   // upload the tables (pageable copies are staged, the host tables may be
   // rewritten after the calls return)
-  check_hip(hipMemcpyAsync(s->d_stage.ptr, &ts, sizeof(StageTable), hipMemcpyHostToDevice, st), "copy tables");
-  check_hip(hipMemcpyAsync(s->d_dedisp.ptr, &td, sizeof(DedispTable), hipMemcpyHostToDevice, st), "copy tables");
-  check_hip(hipMemcpyAsync(s->d_series.ptr, &tr, sizeof(SeriesTable), hipMemcpyHostToDevice, st), "copy tables");
-  check_hip(hipMemcpyAsync(s->d_tail.ptr, &tt, sizeof(TailTable), hipMemcpyHostToDevice, st), "copy tables");
-  bool regrid = false;  // more workgroups than the graph was captured with
-  auto upload = [&](DevBuf &dst, const void *src, size_t used, size_t all) {
+  auto upload = [&](DevBuf &dst, const auto &t) {
     dst.device = s->ctx->device;
-    dst.reserve(all);
-    check_hip(hipMemcpyAsync(dst.ptr, src, used, hipMemcpyHostToDevice, st), "copy tables");
+    dst.reserve(sizeof(t));
+    const size_t used = (size_t)(reinterpret_cast<const char *>(&t.job[t.n_jobs]) - reinterpret_cast<const char *>(&t));
+    check_hip(hipMemcpyAsync(dst.ptr, &t, used, hipMemcpyHostToDevice, st), "copy tables");
   };
+  upload(s->d_stage, ts);
+  upload(s->d_dedisp, td);
+  upload(s->d_series, tr);
+  upload(s->d_tail, tt);
+  bool regrid = false;  // more workgroups than the graph was captured with
   bool pattern = tu.n_jobs > 0;
   for (int k = 0; k < kPatForms; ++k) pattern |= s->pat_grid[k] > 0;
-  if (pattern)
-    upload(s->d_unring, &tu, offsetof(UnringTable, job) + sizeof(UnringJob) * (size_t)tu.n_jobs, sizeof(UnringTable));
+  if (pattern) upload(s->d_unring, tu);
   for (int k = 0; k < kPatForms; ++k) {
     const PatJobTable &tp = *s->h_pat[k];
     if (tp.n_items > s->pat_grid[k]) {
       s->pat_grid[k] = tp.n_items;
       regrid = true;
     }
-    if (s->pat_grid[k] > 0)
-      upload(s->d_pat[k], &tp, offsetof(PatJobTable, job) + sizeof(PatJob) * (size_t)tp.n_jobs, sizeof(PatJobTable));
+    if (s->pat_grid[k] > 0) upload(s->d_pat[k], tp);
   }
   // kernels: replay the captured graph (re-captured if the LDS need or the pattern tiles grew)
   const int64_t lds_need = std::max<int64_t>(dd_lds, 64 * 1024);
