@@ -242,3 +242,32 @@ def test_defaults_by_estimated_time(dev, nchan, nsamp, seg, kind, tpw):
     finally:
         torch.cuda.synchronize()
         ctx.close()
+
+
+@pytest.mark.parametrize("offset", [0, 1, 2, 3])
+@pytest.mark.parametrize("nchan", [1, 3, 15, 17, 127, 130, 259])
+def test_staging_of_any_alignment(dev, nchan, offset):
+    """Rows that start at any byte (channel counts that are no multiple of 16,
+    an input at any address): every downsampling's sums equal the oracle's, the
+    last bytes of the input included."""
+    import torch
+    from paper_2110_12749_amd import gsp
+    segs = [(0.0, 0.5, 3, 1), (2.0, 0.5, 2, 3), (4.0, 1.0, 2, 8), (6.0, 1.0, 1, 16)]
+    nsamp = 2309
+    freqs = 1400.0 + (np.arange(nchan) + 0.5) * 100.0 / nchan
+    X = np.random.default_rng(nchan).integers(0, 256, (nsamp, nchan), dtype=np.uint8)
+    X[-1] = 255
+    ref = oracle.dedisperse(X, freqs, 196.608e-6, segs)
+    desc = gsp.plan_shape(nsamp, freqs, 196.608e-6, segs)
+    say(f"[case] staging {nchan} channels, {offset} bytes off")
+    room = torch.zeros(X.size + offset, dtype=torch.uint8, device="cuda")
+    fb = room[offset:].view(nsamp, nchan)
+    fb.copy_(torch.from_numpy(X))
+    ctx = gsp.Context(0)
+    try:
+        dmt = ctx.dedisperse(fb, freqs, desc, out=torch.full((desc.total,), -1, dtype=torch.int32, device="cuda"))
+        for s, v in enumerate(gsp.segment_views(desc, dmt)):
+            assert np.array_equal(v.cpu().numpy(), ref[s]), s
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
