@@ -132,7 +132,8 @@ __global__ __launch_bounds__(kStatsThreads) void k_stats(const SeriesTable *__re
 // the ring's low halves, wherever no sample within a box's reach lies
 // 2^31 / w_max or more from c, so that every box's C difference fits): 8
 // differences and a maximum per lane.  Only blocks where one does, or that
-// hold a large sample, are looked at box end by box end (64 a step), and only
+// hold a large sample, are looked at box end by box end (64 a step, the widths
+// that passed), and only
 // ends that pass there get the exact double SNR.  Runs of flagged ends are
 // followed across steps and blocks inside the wave and written as fragments
 // (one atomic each).  Waves never wait for each other: there is no workgroup
@@ -259,7 +260,8 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
   __syncthreads();  // the only workgroup barrier
   // widths that are no multiple of 4 (a mask), and lane i: the i-th of the others
   const uint64_t unaligned = __ballot(lane < nw && (wsh[min(lane, nw - 1)] & 3) != 0);
-  const uint64_t aligned = (nw < 64 ? (1ull << nw) - 1 : ~0ull) & ~unaligned;
+  const uint64_t every = nw < 64 ? (1ull << nw) - 1 : ~0ull;
+  const uint64_t aligned = every & ~unaligned;
   const int n_al = __popcll(aligned), n4 = (n_al + 3) & ~3;
   int lane_qk = 0;
   for (uint64_t m = aligned, i = 0; m; m &= m - 1, ++i)
@@ -436,7 +438,7 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
       // to less than 2^31 in size about w c: C differences of the ring's low
       // halves are exact then ----
       const bool bits32 = full && blk - last_big > reach_blocks;
-      bool any = true;
+      uint64_t pass = every;  // widths of which a box may reach its bound in this block
       if (quads && bits32) {
         // does any box of the block reach its width's bound?  First the
         // largest of 4 ends less the smallest of their starts' quad (two
@@ -446,7 +448,8 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
         // exactly, for the widths left: per lane the 8 prefix sums w before
         // its own, two aligned quads, or two pairs of neighbouring ones.
         const int at0 = (r0 >> 2) + lane;
-        uint64_t need = nw < 64 ? (1ull << nw) - 1 : ~0ull, hit = 0;
+        uint64_t need = every;
+        pass = 0;
         if (blk - last_slow > reach_blocks) {
           need = 0;
           for (int k = 0; k < n4; k += 4) {
@@ -498,21 +501,21 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
             else
               best = max4(best, p32 + 4 * j, A.y, A.z, A.w, B.x);
           }
-          hit |= __ballot(best >= __builtin_amdgcn_readlane(lane_l32, k));
+          if (__ballot(best >= __builtin_amdgcn_readlane(lane_l32, k))) pass |= 1ull << k;
         }
-        any = hit != 0ull;
-        if (!any && !open) continue;
+        if (pass == 0ull && !open) continue;
       }
       // ---- box ends that may reach it, 64 a step; widths outer: per width the
       // 8 ring reads are issued together, each compare leaves a wave mask ----
       uint64_t mk[8];
 #pragma unroll
       for (int it = 0; it < 8; ++it) mk[it] = 0;
-      if (any && bits32) {
+      if (pass && bits32) {
         uint32_t pv[8];
 #pragma unroll
         for (int it = 0; it < 8; ++it) pv[it] = (uint32_t)W.ring_lo[(r0 + lane + 64 * it) & (RING - 1)];
-        for (int k = 0; k < nw; ++k) {
+        for (uint64_t ks = pass; ks; ks &= ks - 1) {
+          const int k = __builtin_ctzll(ks);
           const int w = __builtin_amdgcn_readlane(lane_w, k);
           const int32_t L = __builtin_amdgcn_readlane(lane_l32, k);
           const int bw = r0 + lane - w;
@@ -522,11 +525,12 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
           for (int it = 0; it < 8; ++it) mk[it] |= __ballot((int32_t)(pv[it] - qv[it]) >= L);
         }
-      } else if (any) {
+      } else if (pass) {
         int64_t pv[8];
 #pragma unroll
         for (int it = 0; it < 8; ++it) pv[it] = W.get((r0 + lane + 64 * it) & (RING - 1));
-        for (int k = 0; k < nw; ++k) {
+        for (uint64_t ks = pass; ks; ks &= ks - 1) {
+          const int k = __builtin_ctzll(ks);
           const int w = __builtin_amdgcn_readlane(lane_w, k);
           const int64_t L = readlane_i64(lane_lim, k);
           const int bw = r0 + lane - w;
@@ -562,17 +566,18 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
           // reach the threshold; when one does, the best width is among them
           // (a width below its bound has an SNR below the threshold), so the
           // others are skipped, for the whole wave when none of its lanes pass
-          for (int k = 0; k < nw; ++k) {
+          for (uint64_t ks = pass; ks; ks &= ks - 1) {
+            const int k = __builtin_ctzll(ks);
             const int w = __builtin_amdgcn_readlane(lane_w, k);
             if ((int64_t)w > e + look + 1) break;  // box would start before the first sample
             const int64_t d = q1 - W.get((re - w) & (RING - 1));  // C difference
-            const bool pass = d >= readlane_i64(lane_lim, k);
-            if (__ballot(pass) == 0ull) continue;
+            const bool over = d >= readlane_i64(lane_lim, k);
+            if (__ballot(over) == 0ull) continue;
             const double sum = (double)(d + cmean * (int64_t)w);
             const double wmu = __builtin_bit_cast(double, readlane_i64(__builtin_bit_cast(int64_t, lane_wmu), k));
             const double den = __builtin_bit_cast(double, readlane_i64(__builtin_bit_cast(int64_t, lane_den), k));
             const double snr = (sum - wmu) / den;
-            if (pass && (kb == 0 || snr > bs)) {
+            if (over && (kb == 0 || snr > bs)) {
               bs = snr;
               kb = k + 1;
             }
