@@ -595,17 +595,36 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
         __builtin_amdgcn_wave_barrier();
         const bool last_step = e0 + 63 >= s1 - 1;  // the segment's last box end is on this step
         const bool start = fl && (lane == 0 || !((m >> (lane - 1)) & 1ull));
-        if (start) {
-          int l = lane, pk = lane;
-          double ps = bs;
-          while (l + 1 < 64 && ((m >> (l + 1)) & 1ull)) {
-            ++l;
-            const double s = W.sb[l];
-            if (s > ps) {  // ties keep the earlier box end
+        // the run's last lane and, at its first lane, its peak (ties keep the
+        // earlier box end): lane by lane where runs are short, else all lanes
+        // together, each taking in twice as many of its run's lanes every time
+        const uint64_t above = ~(m >> lane);
+        const int l = lane + (above ? __builtin_ctzll(above) : 64) - 1;
+        int pk = lane;
+        double ps = bs;
+        uint64_t runs8 = m & (m >> 1);
+        runs8 &= runs8 >> 2;
+        runs8 &= runs8 >> 4;
+        if (runs8) {
+#pragma unroll
+          for (int d = 1; d < 64; d *= 2) {
+            const double s = __shfl_down(ps, d, 64);
+            const int p = __shfl_down(pk, d, 64);
+            if (lane + d <= l && s > ps) {
               ps = s;
-              pk = l;
+              pk = p;
             }
           }
+        }
+        if (start) {
+          if (!runs8)
+            for (int q = lane + 1; q <= l; ++q) {
+              const double s = W.sb[q];
+              if (s > ps) {
+                ps = s;
+                pk = q;
+              }
+            }
           int64_t f_first = e0 + lane, f_peak = e0 + pk;
           double f_snr = ps;
           int f_k = W.sk[pk];
