@@ -140,7 +140,7 @@ __global__ __launch_bounds__(kStatsThreads) void k_stats(const SeriesTable *__re
 // barrier after the widths are loaded.
 //
 // What bounds it: vector instructions, some 260 per block of a wave (10 widths;
-// 80% busy).  4.57 GB of a survey beam, widths 1 to 512: 1.44 ms (3.79 when each
+// 80% busy).  4.57 GB of a survey beam, widths 1 to 512: 1.36 ms (3.79 when each
 // step of 64 samples had its own scan and each box end its own LDS read and
 // compare; 1.84 with flat loads, which LDS waits include; 3 workgroups per CU
 // instead of 4, from 1 KB more LDS, 2.2).
@@ -706,7 +706,7 @@ SearchTiling search_tiling(int32_t max_width) {
 // Segments of a whole plan's search, whose fragment buffer grows with what is
 // found: halved, down to twice the look-back, while the plan gives fewer waves
 // than the chip holds (16 a CU).  A quick look's 200 trials of 16384 samples
-// are 400 waves of 8192 box ends, 43 us, or 3200 of 1024, 22 us.
+// are 400 waves of 8192 box ends, 43 us, or 3200 of 1024, 22 us (16 since).
 static SearchTiling batch_tiling(const gsp_dmt_desc *desc, int32_t max_width) {
   SearchTiling t = search_tiling(max_width);
   const int smallest = std::max(1, (max_width - 2 + kSearchBlock) / kSearchBlock) * kSearchBlock * 2;
