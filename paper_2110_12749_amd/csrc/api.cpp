@@ -91,20 +91,19 @@ RowTables &row_tables(gsp_ctx *ctx, const gsp_dmt_desc *desc, const double *freq
         }
         order.push_back(plain_shape(desc, s));
       }
-      DedispShape pair;  // the 16-bit tile's default (4, 4, 8, 32)
-      pair.kind = 0;
-      pair.groups = 4;
-      pair.tpw = 4;
-      pair.waves = 8;
-      pair.chunk = 32;
+      const DedispShape pair = pair_shape(desc, s, true), pair8 = pair_shape(desc, s, false);
       const bool pair_first = order.back().kind == 0;
+      if (pair_first && pair.tpw != pair8.tpw) order.push_back(pair8);
       if (pair_first && desc->seg[s].downsamp == 1 && desc->nchan % 4 == 0)  // where it does not fit
         order.push_back(quad_shape());
       if (order.back().kind == 2) {
         DedispShape split = order.back();
         split.kind = 3;
         order.push_back(split);
-        if (!pair_first) order.push_back(pair);
+        if (!pair_first) {
+          order.push_back(pair);
+          if (pair.tpw != pair8.tpw) order.push_back(pair8);
+        }
       }
     }
     std::unique_ptr<RowTables> rt;

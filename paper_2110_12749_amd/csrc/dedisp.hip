@@ -167,8 +167,14 @@ static double tile_clocks(int32_t n_dm, int64_t n_out, int32_t nchan, int trials
   return launch + (double)(tiles / 512) * (pair * work + round) +
          (rest ? (rest > 256 ? pair : alone) * work + round : 0.0);
 }
-double plain_clocks(int32_t n_dm, int64_t n_out, int32_t nchan) {
+// Tiles of 32 trials x 512 outputs a row has on the 16-bit tile
+static int64_t plain_tiles(int32_t n_dm, int64_t n_out) { return (int64_t)((n_dm + 31) / 32) * ((n_out + 511) / 512); }
+static double plain8_clocks(int32_t n_dm, int64_t n_out, int32_t nchan) {
   return tile_clocks(n_dm, n_out, nchan, 32, 512, 190.0, 115.0, 5e3, 18e3);
+}
+double plain_clocks(int32_t n_dm, int64_t n_out, int32_t nchan) {
+  if (plain_tiles(n_dm, n_out) > 256) return plain8_clocks(n_dm, n_out, nchan);
+  return tile_clocks(n_dm, n_out, nchan, 32, 512, 190.0, 98.0, 5e3, 18e3);  // pair_shape's 16 waves
 }
 double quad_clocks(int32_t n_dm, int64_t n_out, int32_t nchan) {
   return tile_clocks(n_dm, n_out, nchan, 96, 256, 90.0, 45.0, 39e3, 3e3);
@@ -184,22 +190,37 @@ DedispShape quad_shape() {  // byte-quad tile with staging waves: 12 summing wav
   return s;
 }
 
+// The 16-bit tile's two forms.  A tile to a CU at most: 16 waves of 2 trials and
+// nearly all of the LDS instead of 8 of 4 and half of it (128 channels, 200
+// trials, 14000 outputs: 0.036 -> 0.032 ms; 256 channels 0.063 -> 0.054; with
+// more tiles than CUs two workgroups a CU are faster: 300 channels, 640 tiles,
+// 0.166 against 0.173).
+DedispShape pair_shape(const gsp_dmt_desc *desc, int32_t seg, bool small) {
+  DedispShape s;
+  s.groups = 4;
+  if (small && plain_tiles(desc->seg[seg].n_dm, desc->n_out[seg]) <= 256) {
+    s.tpw = 2;
+    s.waves = 16;
+    s.chunk = 64;
+    return s;
+  }
+  s.tpw = 4;
+  s.waves = 8;
+  s.chunk = 32;
+  return s;
+}
+
 // The byte-quad tile takes D = 1 rows of whole quads, but for those of at least
 // 64 channels where the 16-bit tile is faster: rows of one or two rounds, in
 // which the byte-quad tile's 39000 clocks a round count (64 channels, 29 trials,
 // 134000 outputs: 0.047 against 0.031 ms; 39 trials, 177000: 0.059 against
-// 0.045 ms).
+// 0.045 ms; both in the 8-wave form, on which the line was drawn).
 DedispShape plain_shape(const gsp_dmt_desc *desc, int32_t seg) {
   const int32_t D = desc->seg[seg].downsamp, n_dm = desc->seg[seg].n_dm, nchan = desc->nchan;
   if (D == 1 && nchan % 4 == 0 &&
-      (nchan < 64 || quad_clocks(n_dm, desc->n_out[seg], nchan) <= plain_clocks(n_dm, desc->n_out[seg], nchan)))
+      (nchan < 64 || quad_clocks(n_dm, desc->n_out[seg], nchan) <= plain8_clocks(n_dm, desc->n_out[seg], nchan)))
     return quad_shape();
-  DedispShape s;
-  s.tpw = 4;
-  s.waves = 8;
-  s.groups = 4;
-  s.chunk = 32;
-  return s;
+  return pair_shape(desc, seg, true);
 }
 
 DedispShape default_shape(const gsp_dmt_desc *desc, int32_t s) {
@@ -223,6 +244,7 @@ bool shape_supported(const DedispShape &s) {
   if (s.kind >= 1 && s.kind <= 3) return quad_shape_supported(s);
   if (s.kind != 0) return false;
   const int kt = s.groups * 16 + s.tpw;
+  if (kt == 4 * 16 + 2) return s.waves == 16 && s.chunk >= 1;  // one workgroup per CU
   const bool inst = kt == 8 * 16 + 4 || kt == 4 * 16 + 8 || kt == 4 * 16 + 4 || kt == 2 * 16 + 8;
   return inst && s.waves >= 1 && s.waves <= 8 && s.chunk >= 1;
 }
@@ -283,7 +305,7 @@ void build_row_tables(gsp_ctx *ctx, const gsp_dmt_desc *desc, const double *freq
     return;
   }
   build_tables_from_delays(ctx, g.n_dm, desc->nchan, g.downsamp, desc->nsamp / g.downsamp, desc->n_out[s],
-                           desc->max_delay[s], shape, rt, units_per_thread);
+                           desc->max_delay[s], shape, rt, units_per_thread, shape.waves > 8 ? kLdsMax - 4096 : 0);
 }
 
 void build_tables_from_delays(gsp_ctx *ctx, int32_t n_dm, int32_t nchan_, int32_t D, int64_t N, int64_t n_out,
@@ -492,6 +514,7 @@ void launch_dedisp(gsp_ctx *ctx, const RowTables &rt, int32_t *out_row, hipStrea
     case 8 * 16 + 4: launch_k<8, 4>(a, sh.waves, rt.lds_bytes, rt.D, st); break;
     case 4 * 16 + 8: launch_k<4, 8>(a, sh.waves, rt.lds_bytes, rt.D, st); break;
     case 4 * 16 + 4: launch_k<4, 4>(a, sh.waves, rt.lds_bytes, rt.D, st); break;
+    case 4 * 16 + 2: launch_k<4, 2>(a, sh.waves, rt.lds_bytes, rt.D, st); break;
     case 2 * 16 + 8: launch_k<2, 8>(a, sh.waves, rt.lds_bytes, rt.D, st); break;
     default: fail(GSP_EINVAL, "unsupported dedispersion shape");
   }

@@ -85,7 +85,7 @@ struct Unit {
 // series of sub-band dedispersion); without it a.seg_ch is ignored.
 template <int K, int TPW, typename SrcT, typename OutT = int32_t, bool SEG = false>
 __device__ __forceinline__ void dedisp_tile(const DedispArgs &a, int dm_tile, int t_tile, uint32_t *lds) {
-  static_assert(TPW % 4 == 0, "offsets are read four trials at a time");
+  static_assert(TPW == 2 || TPW % 4 == 0, "offsets are read two or four trials at a time");
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -155,6 +155,11 @@ __device__ __forceinline__ void dedisp_tile(const DedispArgs &a, int dm_tile, in
     {
       // offsets of the wave's trials at channel cs + lane (clamped into the pass)
       const uint32_t *src = a.addr + (int64_t)(cs + min(lane, ce - cs - 1)) * a.n_dm_pad + i_wave;
+      if constexpr (TPW == 2) {
+        const uint2 q = *reinterpret_cast<const uint2 *>(src);
+        noff[0] = q.x;
+        noff[1] = q.y;
+      } else
 #pragma unroll
       for (int j = 0; j < TPW; j += 4) {
         const uint4 q = *reinterpret_cast<const uint4 *>(src + j);
@@ -335,7 +340,7 @@ __device__ __forceinline__ void dedisp_tile(const DedispArgs &a, int dm_tile, in
 
 // Batch launch: one tile per workgroup, XCD-aware tile order.
 template <int K, int TPW, typename SrcT>
-__global__ __launch_bounds__(512) void k_dedisp(DedispArgs a) {
+__global__ __launch_bounds__(TPW == 2 ? 1024 : 512) void k_dedisp(DedispArgs a) {
   extern __shared__ uint32_t lds[];
   const int G = a.n_dm_tiles * a.n_t_tiles;
   const int L = xcd_remap(blockIdx.x, G);

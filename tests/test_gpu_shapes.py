@@ -271,3 +271,29 @@ def test_staging_of_any_alignment(dev, nchan, offset):
     finally:
         torch.cuda.synchronize()
         ctx.close()
+
+
+@pytest.mark.parametrize("n_dm,nsamp,D", [(1, 1500, 1), (33, 9001, 1), (64, 2600, 3), (200, 16384, 1)])
+@pytest.mark.parametrize("nchan", [5, 130])
+def test_two_trials_a_wave(dev, nchan, n_dm, nsamp, D):
+    """The 16-bit tile's form for rows of up to 256 tiles (16 waves of 2
+    trials): ragged trials, outputs and passes, against the oracle."""
+    import torch
+    from paper_2110_12749_amd import gsp
+    seg = (0.0, 0.9, n_dm, D)
+    w = synth.small(nchan=nchan, nsamp=nsamp, segments=[seg], tsamp=196.608e-6, n_pulses=1, f_lo=1300.0)
+    X = w.generate()
+    ref = oracle.dedisperse(X, w.freqs, w.tsamp, w.segments)
+    desc = gsp.plan_shape(w.nsamp, w.freqs, w.tsamp, w.segments)
+    ctx = gsp.Context(0)
+    try:
+        fb = torch.from_numpy(X).to("cuda")
+        used = ctx.row_shape(w.freqs, desc, 0)
+        say(f"[case] {nchan} channels, {n_dm} trials, D {D}: default {used}")
+        ctx.set_row_shape(w.freqs, desc, 0, 4, 2, 16, 64, 0)
+        assert ctx.row_shape(w.freqs, desc, 0)[:3] == (4, 2, 16)
+        dmt = ctx.dedisperse(fb, w.freqs, desc, out=torch.full((desc.total,), -1, dtype=torch.int32, device="cuda"))
+        assert np.array_equal(gsp.segment_views(desc, dmt)[0].cpu().numpy(), ref[0])
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
