@@ -438,13 +438,14 @@ int gsp_stream_set_fragment_capacity(gsp_stream *s, int64_t cap);
  * sums do not fit the LDS (wide channels, trials far apart).  The default for
  * D <= 8 is kind 4 where its tables fit and promise to be faster than the
  * following; for D = 1 rows with a multiple of 4 channels kind 2 (4, 8, 12,
- * 64) where its copies fit, else kind 3 where it applies, else kind 0 (4, 4,
- * 8, 32); for other rows kind 0 (4, 4, 8, 32).  gsp_row_shape reports the
- * longest pass in `chunk` (of the byte-quad part for kind 3). */
+ * 64) where its copies fit and it is not estimated to be slower than kind 0,
+ * else kind 3 where it applies, else kind 0; for other rows kind 0, as (4, 2,
+ * 16, 64) on rows of up to 256 of its tiles and (4, 4, 8, 32) on others.
+ * gsp_row_shape reports the longest pass in `chunk` (of the byte-quad part for kind 3). */
 typedef struct gsp_shape {
   int32_t groups; /* kind 0: 2, 4 or 8; kind 1: 4, 8 or 16; kinds 2, 3: 4 or 8; kind 4: 4 */
-  int32_t tpw;    /* kind 0: 4 or 8; kind 1: 2, 4 or 8; kinds 2, 3: 8 (groups 4) or 4 (groups 8); kind 4: 8 or 12 */
-  int32_t waves;  /* kind 0: 1 .. 8; kind 1: 1 .. 16; kinds 2, 3: 1 .. 12 summing waves; kind 4: 8 summing waves */
+  int32_t tpw;    /* kind 0: 4 or 8, or 2 (groups 4); kind 1: 2, 4 or 8; kinds 2, 3: 8 (groups 4) or 4 (groups 8); kind 4: 8 or 12 */
+  int32_t waves;  /* kind 0: 1 .. 8, with tpw 2 16; kind 1: 1 .. 16; kinds 2, 3: 1 .. 12 summing waves; kind 4: 8 summing waves */
   int32_t chunk;  /* >= 1 */
   int32_t kind;   /* 0: 16-bit tile, 1: byte-quad tile, 2: with staging waves, 3: split row, 4: pattern tile */
 } gsp_shape;
