@@ -236,10 +236,13 @@ __global__ __launch_bounds__(256) void k_sum_parts(PartTable t) {
 // The partial sums of one backward pass: rows taken from a buffer, then summed.
 struct Parts {
   float *buf;
-  int64_t used = 0;
+  int64_t used = 0, room;  // floats
   PartTable t;
-  explicit Parts(float *b) : buf(b) { t.n_jobs = t.n_blocks = 0; }
+  explicit Parts(const DevBuf &b) : buf(b.as<float>()), room((int64_t)(b.bytes / sizeof(float))) {
+    t.n_jobs = t.n_blocks = 0;
+  }
   float *take(int64_t rows, int64_t stride) {
+    if (used + rows * stride > room) fail(GSP_EDEVICE, "partial sums larger than their buffer");
     float *p = buf + used;
     used += rows * stride;
     return p;
@@ -325,11 +328,17 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs g) {
   }
 }
 
-// p per workgroup: about 1024 workgroups, at least 256 p each
-static int64_t wgrad_slice(int64_t P, int M, int N) {
+// Slices of P at most: about 1024 workgroups, at least 256 p each.  Grows with
+// P, unlike the number of slices itself (a slice is rounded up to 32 p, so that
+// 252 images can have more than 256): what a buffer for any smaller P is sized by.
+static int64_t wgrad_max_rows(int64_t P, int M, int N) {
   const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
-  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(1024 / tiles, P / 256));
-  return ((P + want - 1) / want + 31) / 32 * 32;
+  return std::max<int64_t>(1, std::min<int64_t>(1024 / tiles, P / 256));
+}
+// p per workgroup
+static int64_t wgrad_slice(int64_t P, int M, int N) {
+  const int64_t rows = wgrad_max_rows(P, M, N);
+  return ((P + rows - 1) / rows + 31) / 32 * 32;
 }
 
 static void wgrad(const uint16_t *G, const uint16_t *X, int64_t P, int M, int N, int im_C, int im_H, float *dst,
@@ -1451,13 +1460,13 @@ void reserve_batch(gsp_cnn *c, int64_t n) {
   c->loss.reserve((size_t)n * 4);
   c->dh1.reserve((size_t)n * kHidden * 2);
   c->wt.reserve((size_t)kConv[3].cout * 9 * kConv[3].cin * 2);  // the largest convolution's weights
+  // partial sums: every term grows with the batch, so smaller ones fit too
   int64_t part = kConv1Parts * 288 + (n / kHeadRows + 1) * (kHidden + 1) +
-                 ((n + wgrad_slice(n, kHidden, kFlat) - 1) / wgrad_slice(n, kHidden, kFlat)) * kHidden * kFlat +
-                 colsum_rows(n, kHidden) * kHidden;
+                 wgrad_max_rows(n, kHidden, kFlat) * kHidden * kFlat + colsum_rows(n, kHidden) * kHidden;
   for (int l = 0; l < 4; ++l) {
     const ConvSpec &cs = kConv[l];
-    const int64_t px = n * cs.h * cs.h, slice = wgrad_slice(px, cs.cout, 9 * cs.cin);
-    part += (px + slice - 1) / slice * cs.cout * 9 * cs.cin + colsum_rows(px, cs.cout) * cs.cout;
+    const int64_t px = n * cs.h * cs.h;
+    part += wgrad_max_rows(px, cs.cout, 9 * cs.cin) * cs.cout * 9 * cs.cin + colsum_rows(px, cs.cout) * cs.cout;
   }
   c->part.reserve((size_t)part * 4);
   c->dpre.reserve((size_t)n * 64 * 64 * 16 * 2);
@@ -1539,7 +1548,7 @@ void forward(gsp_cnn *c, const uint16_t *x, int64_t n, hipStream_t st) {
 void backward(gsp_cnn *c, const uint16_t *x, const float *labels, int64_t n, hipStream_t st) {
   const uint16_t *wb = c->pbf.as<uint16_t>();
   float *g = c->g32.as<float>();
-  Parts parts(c->part.as<float>());
+  Parts parts(c->part);
   // loss head: fp32 dz, fc2's gradients from it, bf16 gradient of fc1's pre-activation
   hipLaunchKernelGGL(k_head_bwd, dim3(grid_for(n * kHidden)), dim3(256), 0, st, c->z.as<float>(), labels,
                      c->h1.as<uint16_t>(), wb + c->L.w[5], (int)n, c->loss.as<float>(), c->dz.as<float>(),

@@ -449,3 +449,22 @@ def test_cutouts_invalid_candidates_give_zero_images(env):
     bad["width"] = [4, 4, 1, 4]
     out = gsp.cutouts(ctx, fb, w.freqs, dmt, desc, bad).cpu().numpy()
     assert (out == 0).all()
+
+
+@pytest.mark.parametrize("first,n", [(256, 252), (205, 204)])
+def test_gradients_of_a_smaller_batch_after_a_larger_one(env, first, n):
+    """Batches whose gradients are summed in more slices than those of the
+    larger batch that the network's buffers were sized for: the same bits as
+    from a network that has seen no other batch."""
+    gsp, ctx, torch = env
+    say(f"[case] gradients of {n} images after {first}")
+    x, y = inputs(first, 900 + n)
+    xd, yd = to_dev(torch, x), torch.from_numpy(y.astype(np.float32)).cuda()
+    out = []
+    for batches in ((first, n), (n,)):
+        net = gsp.Cnn(ctx, seed=6)
+        for b in batches:
+            g, loss = net.gradients(xd[:b].contiguous(), yd[:b].contiguous())
+        out.append((g, loss))
+        net.close()
+    assert np.array_equal(out[0][0].view(np.uint32), out[1][0].view(np.uint32)) and out[0][1] == out[1][1]

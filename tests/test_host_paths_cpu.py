@@ -1,0 +1,16 @@
+"""The library's host side without a GPU: sizes of workspaces, fall-backs when
+memory runs out, memory budgets and graph captures, on a HIP runtime in host
+memory whose kernels are logged and not run."""
+import pytest
+
+from tests import host_hip
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    so = host_hip.build(tmp_path_factory.mktemp("host_hip"))
+    return lambda case, **kw: host_hip.run(so, "tests.host_cases", case, **kw)
+
+
+def test_gradient_partial_sums_fit_what_larger_batches_reserved(host):
+    host("gradient_parts")
