@@ -427,7 +427,9 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
           W.put((r0 + 64 * it + lane) & (RING - 1), P);
         }
         if (blk_big) last_big = blk;
-        last_slow = blk;
+        // box starts lie one position further back than box samples: in one
+        // block more than reach_blocks where w_max is 1 above a multiple of 512
+        last_slow = blk + ((a.wmax - 1) % kSearchBlock == 0 ? 1 : 0);
       }
       __builtin_amdgcn_wave_barrier();
       if (eb + kSearchBlock - 1 < s0) continue;  // look-back block: sums only

@@ -105,3 +105,28 @@ def test_search_segments_and_far_samples(env, n_tr, n, widths):
             x[i + 3, at] = 1000 + np.array([min(2 ** 21, big) - 300, min(2 ** 21, big) + 300, 2 ** 21])
     say(f"[case] search segments {n_tr} x {n} widths {widths}")
     run_case(env, np.clip(x, -2 ** 31, 2 ** 31 - 1).astype(np.int32), [w for w in widths if w <= n] or [1], 4.0)
+
+
+@pytest.mark.parametrize("widths", [[513], [4, 30, 513], [1025], [2, 1025]])
+def test_search_first_end_after_a_far_sample(env, widths):
+    """The widest box that ends on the first sample of a block starts behind
+    the last sample of another: where that block is summed in 64 bits (a
+    sample 2.2 million below the mean) it has no minima for the bound over
+    groups of box starts.  A box just after that sample, over one 2 million
+    above the mean, is the only one of its length that reaches the threshold."""
+    gsp, ctx, torch = env
+    n, w = 60007, widths[-1]
+    rng = np.random.default_rng(w)
+    at = 512 * np.array([1, 3, 6, 10, 16, 17, 32, 61, 99, 110])
+    x = np.rint(rng.normal(1000.0, 50.0, size=(len(at), n))).astype(np.int32)
+    x[np.arange(len(at)), at - 1] -= 2200000
+    x[np.arange(len(at)), at] += 2000000
+    say(f"[case] search after a far sample, widths {widths}")
+    c = run_case(env, x, widths, 4.0)
+    for i, k in enumerate(at):
+        end = k + w - 1
+        hit = (c["dm_index"] == i) & (c["t_first"] <= end) & (c["t_last"] >= end) & (c["width"] == w)
+        assert hit.sum() == 1, (i, k)
+    desc = gsp.plan_shape(n, [1400.0], 1e-4, [(0.0, 1.0, len(at), 1)])
+    dmt = torch.from_numpy(x.reshape(-1)).cuda()
+    assert np.array_equal(ctx.single_pulse_search_noalloc(dmt, desc, widths, 4.0), c)
