@@ -402,7 +402,7 @@ struct gsp_stream {
   std::unique_ptr<UnringTable> h_unring = std::make_unique<UnringTable>();
   std::unique_ptr<PatJobTable> h_pat[kPatForms] = {std::make_unique<PatJobTable>(), std::make_unique<PatJobTable>(),
                                                    std::make_unique<PatJobTable>()};
-  int64_t pat_grid[kPatForms] = {0, 0, 0};  // workgroups the graph was captured with
+  int64_t pat_grid[kPatForms] = {0, 0, 0};  // workgroups of each form, the most tiles of a step so far
   int64_t frag_cap = 1 << 16;
   int64_t regrown = 0;  // steps whose search ran again with a grown fragment buffer
   int64_t musig_cap = 0;
@@ -410,6 +410,7 @@ struct gsp_stream {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   int64_t graph_lds = -1;  // dedispersion LDS the graph was captured with
+  int64_t graph_grid[kPatForms] = {0, 0, 0};  // and pat_grid
   bool use_graph = true;
   // learned triage (optional): cutouts of each step's candidates scored by a network
   gsp_cnn *cnn = nullptr;
@@ -853,21 +854,19 @@ int64_t step_once(gsp_stream *s) {
   upload(s->d_dedisp, td);
   upload(s->d_series, tr);
   upload(s->d_tail, tt);
-  bool regrid = false;  // more workgroups than the graph was captured with
   bool pattern = tu.n_jobs > 0;
   for (int k = 0; k < kPatForms; ++k) pattern |= s->pat_grid[k] > 0;
   if (pattern) upload(s->d_unring, tu);
   for (int k = 0; k < kPatForms; ++k) {
     const PatJobTable &tp = *s->h_pat[k];
-    if (tp.n_items > s->pat_grid[k]) {
-      s->pat_grid[k] = tp.n_items;
-      regrid = true;
-    }
+    s->pat_grid[k] = std::max(s->pat_grid[k], tp.n_items);
     if (s->pat_grid[k] > 0) upload(s->d_pat[k], tp);
   }
   // kernels: replay the captured graph (re-captured if the LDS need or the pattern tiles grew)
   const int64_t lds_need = std::max<int64_t>(dd_lds, 64 * 1024);
   if (s->use_graph) {
+    // (compared with what was captured: steps without the graph, or that failed, raise pat_grid too)
+    const bool regrid = !std::equal(s->pat_grid, s->pat_grid + kPatForms, s->graph_grid);
     if (!s->exec || lds_need > s->graph_lds || regrid) {
       if (s->exec) (void)hipGraphExecDestroy(s->exec);
       if (s->graph) (void)hipGraphDestroy(s->graph);
@@ -886,6 +885,7 @@ int64_t step_once(gsp_stream *s) {
       check_hip(hipStreamEndCapture(st, &s->graph), "end capture");
       check_hip(hipGraphInstantiate(&s->exec, s->graph, nullptr, nullptr, 0), "instantiate graph");
       s->graph_lds = lds_need;
+      std::copy(s->pat_grid, s->pat_grid + kPatForms, s->graph_grid);
     }
     check_hip(hipGraphLaunch(s->exec, st), "launch graph");
   } else {

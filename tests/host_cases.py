@@ -44,3 +44,43 @@ def gradient_parts(hh, gsp):
         room = hh.room(base)
         assert room >= need[:r + 1].max(), f"{r} images reserve {room} bytes, {need[:r + 1].argmax()} take {need[:r + 1].max()}"
         net.close()
+
+
+# rows large enough for the pattern tile, and one for the other tile
+STREAM_ROWS = [(0.0, 0.05, 400, 1), (20.0, 0.1, 330, 2), (53.0, 0.2, 300, 4), (113.0, 30.0, 3, 4)]
+STREAM_TSAMP = 49.152e-6
+
+
+def _stream_freqs(nchan):
+    return 1400.0 + (np.arange(nchan) + 0.5) * 100.0 / nchan
+
+
+def _pattern_tiles(hh):
+    """(tiles listed, workgroups launched) of every pattern launch of the log."""
+    return [(C.c_int64.from_address(struct.unpack_from("<Q", bytes(l.arg))[0]).value, l.grid[0])
+            for l in hh.launches("k_dedisp_pat_jobs")]
+
+
+def stream_graph_switched_on_and_off(hh, gsp):
+    """The captured step holds a workgroup for every pattern tile, also where
+    the tiles grew in steps that were launched without the graph."""
+    ctx = gsp.Context(0)
+    nchan, block = 1024, 2064
+    s = gsp.Stream(ctx, 1 << 34, block, [1, 2, 4], 50.0)
+    bid, ok = s.open_beam(nchan, _stream_freqs(nchan), STREAM_TSAMP, STREAM_ROWS)
+    assert ok
+    data = np.zeros((block, nchan), np.uint8)
+    seen = []
+    for k, graph in enumerate([True, False, False, True, True]):
+        s.set_graph(graph)
+        s.push(bid, data)
+        hh.clear()
+        assert s.step() == 1
+        tiles = _pattern_tiles(hh)
+        print(k, graph, tiles)
+        assert all(l.replayed == int(graph) for l in hh.launches("k_dedisp_pat_jobs"))
+        assert all(n <= grid for n, grid in tiles), (k, tiles)
+        seen.append(sorted(n for n, _ in tiles if n))
+    assert seen[1] and all(n == seen[1] for n in seen[1:]), seen  # full windows: the same tiles every step
+    assert seen[0] != seen[1]  # the first window is a shorter one
+    s.close()

@@ -444,3 +444,40 @@ def test_pattern_rows_equal_batch(env, nchan, block, graph):
     s.push(ids[0], X[0][(n_blk - 1) * block:])  # a short last block: the beam ends
     assert s.step() == 1
     s.close()
+
+
+def test_pattern_rows_with_the_graph_switched_on_and_off(env):
+    """Windows grow while the step graph is off: switched on again, its replays
+    compute every tile (each window against the batch dedispersion)."""
+    gsp, ctx, torch = env
+    nchan, block = 1024, 2064
+    segs = [(0.0, 0.05, 400, 1), (20.0, 0.1, 330, 2), (53.0, 0.2, 300, 4)]
+    freqs = 1400.0 + (np.arange(nchan) + 0.5) * 100.0 / nchan
+    ts = 49.152e-6
+    graphs = [True, False, False, True, True, False, True]
+    nsamp = len(graphs) * block
+    X = np.random.default_rng(5).integers(0, 256, (nsamp, nchan), dtype=np.uint8)
+    desc = gsp.plan_shape(nsamp, freqs, ts, segs)
+    c = gsp.Context(0)
+    for r in range(len(segs)):
+        c.set_row_shape(freqs, desc, r, 4, 4, 8, 32, 0)
+    ref = [v.cpu().numpy() for v in gsp.segment_views(desc, c.dedisperse(torch.from_numpy(X).cuda(), freqs, desc))]
+    c.close()
+    s = gsp.Stream(ctx, 1 << 34, block, WIDTHS, 50.0)
+    bid, ok = s.open_beam(nchan, freqs, ts, segs)
+    assert ok
+    say("[case] stream graph switched on and off")
+    checked = 0
+    for k, graph in enumerate(graphs):
+        s.set_graph(graph)
+        s.push(bid, X[k * block:(k + 1) * block])
+        assert s.step() == 1
+        for r, seg in enumerate(segs):
+            M = nsamp // seg[3] - int(desc.n_out[r])
+            a, b = max(0, k * block // seg[3] - M), max(0, (k + 1) * block // seg[3] - M)
+            t0, arr = s.window(bid, r, seg[2])
+            assert (t0, arr.shape[1]) == (a, b - a), (k, r)
+            assert np.array_equal(arr, ref[r][:, a:b]), (k, r)
+            checked += b - a
+    assert checked == int(sum(desc.n_out[r] for r in range(len(segs))))
+    s.close()

@@ -14,3 +14,7 @@ def host(tmp_path_factory):
 
 def test_gradient_partial_sums_fit_what_larger_batches_reserved(host):
     host("gradient_parts")
+
+
+def test_stream_graph_holds_every_tile_after_steps_without_it(host):
+    host("stream_graph_switched_on_and_off")
