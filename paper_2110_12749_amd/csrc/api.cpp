@@ -71,8 +71,10 @@ RowTables &row_tables(gsp_ctx *ctx, const gsp_dmt_desc *desc, const double *freq
   auto &slot = it->second->rows[s];
   const DedispShape want = shape_for_row(ctx, desc, s);
   const DedispShape had = slot ? slot->req : want;
+  // (a default may stand for another tile than the same shape does when it is asked for)
+  const bool tuned = ctx->tuned.count(row_signature(desc, s)) > 0;
   if (slot && (had.groups != want.groups || had.tpw != want.tpw || had.waves != want.waves || had.kind != want.kind ||
-               had.chunk != want.chunk))
+               had.chunk != want.chunk || slot->forced != tuned))
     slot.reset();  // the tuned shape changed since the tables were built
   if (!slot) {
     // a default does not suit every row: the pattern tile's partial sums may
@@ -82,7 +84,6 @@ RowTables &row_tables(gsp_ctx *ctx, const gsp_dmt_desc *desc, const double *freq
     // lie at one end of it, else keep the 16-bit tile).  A tuned shape is not
     // replaced.
     std::vector<DedispShape> order{want};
-    const bool tuned = ctx->tuned.count(row_signature(desc, s)) > 0;
     if (!tuned) {
       if (want.kind == 4) {
         if (want.tpw != 8) {  // fewer trials per tile, fewer patterns per group
@@ -120,6 +121,7 @@ RowTables &row_tables(gsp_ctx *ctx, const gsp_dmt_desc *desc, const double *freq
       }
     }
     rt->req = want;
+    rt->forced = tuned;
     slot = std::move(rt);
   }
   return *slot;

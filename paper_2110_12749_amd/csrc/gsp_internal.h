@@ -58,7 +58,8 @@ struct RowTables {
   int64_t n_out = 0;
   int64_t max_delay = 0;
   DedispShape shape;
-  DedispShape req;           // shape requested (before LDS limits, or the byte-quad default that did not fit)
+  DedispShape req;           // shape requested (before LDS limits, or the default that did not fit or pay)
+  bool forced = false;       // req was tuned or set, not a default: built as it is or refused
   int64_t lds_bytes = 0;     // dynamic LDS per block
   int32_t row_dwords = 0;    // LDS dwords per staged copy of the widest channel
   DevBuf passes;             // int32 pairs (first channel, dwords per staged copy) per staging pass + end

@@ -84,3 +84,44 @@ def stream_graph_switched_on_and_off(hh, gsp):
     assert seen[1] and all(n == seen[1] for n in seen[1:]), seen  # full windows: the same tiles every step
     assert seen[0] != seen[1]  # the first window is a shorter one
     s.close()
+
+
+def forced_shape_after_default(hh, gsp, how):
+    """A shape that is asked for is built (or refused) also where the row's
+    default asked for the same one and settled for another."""
+    freqs = 1000.0 + (np.arange(64) + 0.5) * 500.0 / 64
+    desc = gsp.plan_shape(20000, freqs, 1e-4, [(0.0, 1.0, 40, 1), (0.0, 1.0, 40, 2)])
+    wide = np.linspace(300.0, 1500.0, 64)  # a group's patterns do not fit the LDS
+    far = gsp.plan_shape(1 << 20, wide, 1e-4, [(0.0, 1.0, 96, 1)])
+    for plan, f, rows in ((desc, freqs, [(0, 12), (1, 8)]), (far, wide, [(0, 12)])):
+        for r, tpw in rows:
+            fresh = gsp.Context(0)  # what the shape gives without a default before it
+            try:
+                fresh.set_row_shape(f, plan, r, 4, tpw, 8, 16, 4)
+                want = fresh.row_shape(f, plan, r)
+            except gsp.GspError as e:
+                assert e.status == gsp.GSP_EINVAL
+                want = None
+            ctx = gsp.Context(0)
+            before = ctx.row_shape(f, plan, r)
+            assert before[4] != 4, before
+            got = None
+            try:
+                if how == "set":
+                    ctx.set_row_shape(f, plan, r, 4, tpw, 8, 16, 4)
+                else:
+                    fresh_file = f"{how}/{r}"
+                    donor = gsp.Context(0)
+                    try:
+                        donor.set_row_shape(f, plan, r, 4, tpw, 8, 16, 4)
+                    except gsp.GspError:
+                        continue
+                    donor.tuning_save(fresh_file)
+                    ctx.tuning_load(fresh_file)
+                got = ctx.row_shape(f, plan, r)
+            except gsp.GspError as e:
+                assert e.status == gsp.GSP_EINVAL
+            print(r, before, "->", got, "wanted", want)
+            assert got == want
+            if want is None:  # refused: the default stands
+                assert ctx.row_shape(f, plan, r) == before

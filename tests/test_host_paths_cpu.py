@@ -18,3 +18,8 @@ def test_gradient_partial_sums_fit_what_larger_batches_reserved(host):
 
 def test_stream_graph_holds_every_tile_after_steps_without_it(host):
     host("stream_graph_switched_on_and_off")
+
+
+@pytest.mark.parametrize("how", ["set", "load"])
+def test_forced_row_shape_after_the_default(host, how, tmp_path):
+    host("forced_shape_after_default", how=how if how == "set" else str(tmp_path))
