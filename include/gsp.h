@@ -332,7 +332,10 @@ int gsp_store_load(gsp_store *s, const char *dir);
  * sequence of kernels captured once as a hipGraph and replayed.  Beams are
  * admitted against the device-memory budget; a beam that does not fit is
  * queued (GSP_EAGAIN, the id stays valid and its blocks are held on the host)
- * and admitted, in order, when finished beams release memory. */
+ * and admitted, in order, when finished beams release memory.  What the beams
+ * leave of the budget may hold tables and copies that make their steps faster;
+ * it is given up when a beam needs it (opening or closing a beam then waits for
+ * the step that runs, if one does). */
 typedef struct gsp_stream gsp_stream;
 
 typedef struct gsp_stream_candidate {
@@ -347,7 +350,7 @@ typedef struct gsp_stream_stats {
   double lat_p50_s, lat_p99_s, lat_max_s; /* push -> results on the host, per block */
   int64_t blocks, steps;
   double busy_s;                          /* wall time inside steps */
-  int64_t mem_used, mem_budget;           /* device bytes held by admitted beams */
+  int64_t mem_used, mem_budget;           /* device bytes held of the budget, with what would be given up for a beam */
   int32_t beams_active, beams_queued;
   int64_t blocks_pending;
   int64_t triage_scored, triage_rejected; /* candidates scored / dropped by the network */

@@ -35,6 +35,12 @@ void DevBuf::reserve(size_t n) {
   bytes = n;
 }
 
+void DevBuf::release() {
+  if (ptr) (void)hipFree(ptr);
+  ptr = nullptr;
+  bytes = 0;
+}
+
 static hipEvent_t pool_event(gsp_ctx *ctx) {
   if (!ctx->prof_pool.empty()) {
     hipEvent_t e = ctx->prof_pool.back();

@@ -801,6 +801,15 @@ void build_pat_tables(gsp_ctx *ctx, RowTables &rt, bool must) {
   if (!must && rt.shape.tpw == 12 && fewer_trials_faster(rt, H))
     fail(GSP_EINVAL, "fewer trials per pattern tile are faster on this row");
   if (!must && !pat_tables_pay(rt, H)) fail(GSP_EINVAL, "the pattern tile does not pay on this row");
+  upload_pat_tables(ctx, rt, H);
+}
+
+int64_t pat_table_bytes(const PatHost &H) {
+  return (int64_t)((H.tile_pass.size() + H.passes.size() + H.chan.size() + H.pats.size() + H.addr.size()) * 4 +
+                   H.units.size() * sizeof(PatUnit));
+}
+
+void upload_pat_tables(gsp_ctx *ctx, RowTables &rt, const PatHost &H) {
   rt.q_pitch = H.pitch;
   rt.lds_bytes = 2 * kPatLdsDw * 4;
   rt.q_staged_dw = H.built;

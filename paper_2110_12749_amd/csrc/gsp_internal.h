@@ -32,6 +32,7 @@ struct DevBuf {
   DevBuf &operator=(const DevBuf &) = delete;
   ~DevBuf();
   void reserve(size_t n);  // grow to at least n bytes; contents not preserved
+  void release();
   template <class T> T *as() const { return static_cast<T *>(ptr); }
 };
 
@@ -320,6 +321,8 @@ void pat_tables_host(const RowTables &rt, PatHost &H);
 double pat_clocks(const RowTables &rt, const PatHost &H);  // estimated clocks of the row
 bool pat_tables_pay(const RowTables &rt, const PatHost &H);
 void build_pat_tables(gsp_ctx *ctx, RowTables &rt, bool must);  // must: also where another tile is faster
+int64_t pat_table_bytes(const PatHost &H);                     // device memory of the tables
+void upload_pat_tables(gsp_ctx *ctx, RowTables &rt, const PatHost &H);
 void launch_dedisp_pat(gsp_ctx *ctx, const RowTables &rt, int32_t *out_row, hipStream_t st);
 // Arguments of outputs [t_lo, n_out) of a row staged at Y, written to out[i * out_pitch + t]
 PatArgs pat_args(const RowTables &rt, const uint8_t *Y, int32_t *out, int64_t out_pitch, int32_t t_lo, int64_t n_out);

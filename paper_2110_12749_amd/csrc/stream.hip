@@ -334,8 +334,12 @@ struct StreamRow {
   int32_t D = 1, n_dm = 0;
   int64_t M = 0;          // maximum delay (row samples)
   RowTables tables;       // LDS offsets and staging bases for the stream shape
-  std::unique_ptr<RowTables> pat;  // the pattern tile's tables, where it is faster
-  int64_t lin_bytes = 0;  // of its linear copy
+  // the pattern tile's tables where it is faster and the budget has room: on the
+  // host until the beam is admitted (pat_host), then on the device
+  std::unique_ptr<RowTables> pat;
+  std::unique_ptr<PatHost> pat_host;
+  int64_t pat_bytes = 0;  // of the tables on the device
+  int64_t lin_bytes = 0;  // of the row's linear copy
   DevBuf ring;            // uint16 [nchan][R + kGuard]
   int64_t R = 0;
   DevBuf win;             // int32 [n_dm][look + Wcap]
@@ -378,7 +382,11 @@ struct gsp_stream {
   hipStream_t st = nullptr;
   hipStream_t cst = nullptr;  // copies of the next step's blocks
   int32_t B = 0;
-  int64_t budget = 0, used = 0;
+  int64_t budget = 0;
+  int64_t used = 0;      // admitted beams
+  int64_t used_pat = 0;  // their pattern tables, in what the beams leave of the budget, as is `lin`
+  bool in_step = false;  // a step uses the tables and lin
+  int room_waits = 0;    // openings that wait for the step to end, to take their memory
   std::vector<int32_t> widths;
   int32_t wmax = 1;
   float thr = 6.f;
@@ -489,11 +497,12 @@ int64_t beam_bytes(const gsp_stream *s, const Beam &b) {
 // ms a step without that margin, 0.64 before the pattern tile).  4 beams of 4096 channels,
 // 1175 trials and 20480 samples: 12.9 ms a step with k_dedisp_jobs, 4.6 with
 // the copies and the pattern tile.
-void plan_pattern(gsp_stream *s, StreamRow &row, int32_t nchan) {
+void plan_pattern(StreamRow &row, int32_t nchan) {
   if (row.D > 8) return;  // the pattern tile's samples have 11 bits
   const int NB = row.D == 1 ? 1 : 2;
   double best = plain_clocks(row.n_dm, row.Wcap, nchan) - 70e3 -
                 (double)nchan * (double)(row.Wcap + row.M) * (2 + NB) * 2.4e9 / 4.6e12;
+  std::unique_ptr<PatHost> tables;
   int best_tpw = 0;
   auto p = std::make_unique<RowTables>();
   p->n_dm = row.n_dm;
@@ -510,42 +519,111 @@ void plan_pattern(gsp_stream *s, StreamRow &row, int32_t nchan) {
   for (int tpw : {12, 8}) {
     if (tpw == 12 && row.D > 1) continue;
     p->shape.tpw = tpw;
-    p->shape.chunk = 16;
     try {
-      PatHost H;
-      pat_tables_host(*p, H);
-      const double t = pat_clocks(*p, H);
+      auto H = std::make_unique<PatHost>();
+      pat_tables_host(*p, *H);
+      const double t = pat_clocks(*p, *H);
       if (t < best) {
         best = t;
         best_tpw = tpw;
+        tables = std::move(H);
       }
     } catch (const Error &e) {
       if (e.status != GSP_EINVAL) throw;  // its partial sums do not fit the LDS
+    } catch (const std::bad_alloc &) {
+      return;  // the row has another tile
     }
   }
   if (!best_tpw) return;
   p->shape.tpw = best_tpw;
-  build_pat_tables(s->ctx, *p, true);
   p->delays_host = std::vector<int32_t>();
-  row.lin_bytes = (p->q_pitch * nchan * NB + 256 + 255) / 256 * 256;
+  row.pat_bytes = pat_table_bytes(*tables);
+  row.lin_bytes = (tables->pitch * nchan * NB + 256 + 255) / 256 * 256;
+  row.pat_host = std::move(tables);
   row.pat = std::move(p);
 }
 
-// Room for `want` bytes of linear copies, as far as memory that later
-// admissions may need is left alone; rows without room keep k_dedisp_jobs.
+void drop_pattern(StreamRow &row) {
+  row.pat.reset();
+  row.pat_host.reset();
+  row.pat_bytes = row.lin_bytes = 0;
+}
+
+// The tables of an admitted beam's rows go to the device, as far as the budget
+// and the device have room; the other rows keep k_dedisp_jobs.
+void admit_pattern(gsp_stream *s, Beam &b) {
+  for (auto &r : b.rows) {
+    if (!r->pat) continue;
+    if (s->used + s->used_pat + (int64_t)s->lin.bytes + r->pat_bytes > s->budget) {
+      drop_pattern(*r);
+      continue;
+    }
+    try {
+      upload_pat_tables(s->ctx, *r->pat, *r->pat_host);
+      r->pat_host.reset();
+      s->used_pat += r->pat_bytes;
+    } catch (const Error &) {
+      (void)hipGetLastError();
+      drop_pattern(*r);
+    }
+  }
+}
+
+// Waits for the end of the step that runs, which the next one lets it do first.
+void wait_for_step(gsp_stream *s, std::unique_lock<std::mutex> &lk) {
+  ++s->room_waits;
+  s->cv.wait(lk, [s] { return !s->in_step; });
+  --s->room_waits;
+  s->cv.notify_all();
+}
+
+// Makes room in the budget for `need` bytes of a beam that it holds beside the
+// other beams: the linear copies go first, then pattern tables.  A step may be
+// using them: with `lk` waits for its end, without returns false.
+bool make_room(gsp_stream *s, int64_t need, std::unique_lock<std::mutex> *lk) {
+  auto over = [&] { return s->used + need + s->used_pat + (int64_t)s->lin.bytes > s->budget; };
+  if (!over()) return true;
+  if (s->in_step) {
+    if (!lk) return false;
+    wait_for_step(s, *lk);
+  }
+  if (over()) s->lin.release();
+  for (auto &kv : s->beams)
+    for (auto &r : kv.second->rows)
+      if (over() && kv.second->admitted && r->pat) {
+        s->used_pat -= r->pat_bytes;
+        drop_pattern(*r);
+      }
+  return true;
+}
+
+// Room for `want` bytes of linear copies, as far as the budget has it and
+// memory that later admissions may need is left alone; rows without room keep
+// k_dedisp_jobs.
 static constexpr int64_t kLinMax = int64_t(8) << 30;
 void reserve_copies(gsp_stream *s, int64_t want) {
-  want = std::min(want, kLinMax);
+  std::lock_guard<std::mutex> lk(s->mu);
+  const int64_t room = s->budget - s->used - s->used_pat;
+  want = std::min({want, kLinMax, room});
   if (want <= (int64_t)s->lin.bytes) return;
   size_t free_b = 0, total_b = 0;
   if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return;
-  if ((int64_t)free_b + (int64_t)s->lin.bytes < want + (s->budget - s->used) + (int64_t(1) << 30)) return;
+  if ((int64_t)free_b + (int64_t)s->lin.bytes < room + (int64_t(1) << 30)) return;
   s->lin.device = s->ctx->device;
   try {
     s->lin.reserve((size_t)want);
   } catch (const Error &) {
     (void)hipGetLastError();  // no room after all
   }
+}
+
+// The linear copies are given back with the last beam that has rows on the pattern tile.
+void trim_copies(gsp_stream *s) {
+  if (s->in_step) return;
+  for (auto &kv : s->beams)
+    for (auto &r : kv.second->rows)
+      if (kv.second->admitted && r->pat) return;
+  s->lin.release();
 }
 
 // Build the per-row state of a beam (host tables; device memory allocated at admission).
@@ -573,7 +651,7 @@ void plan_beam(gsp_stream *s, Beam &b) {
     row->tables.dmin.device = s->ctx->device;
     // the staged rows are uint16 for every D in a stream (one kernel instance)
     build_row_tables(s->ctx, &d, b.freqs.data(), r, sh, row->tables, unit_max<uint16_t>());  // rings are uint16
-    plan_pattern(s, *row, b.nchan);
+    plan_pattern(*row, b.nchan);
     b.rows.push_back(std::move(row));
   }
 }
@@ -597,6 +675,7 @@ void admit(gsp_stream *s, Beam &b) {
   }
   b.admitted = true;
   s->used += b.mem;
+  admit_pattern(s, b);
 }
 
 void release(gsp_stream *s, Beam &b) {
@@ -605,10 +684,15 @@ void release(gsp_stream *s, Beam &b) {
   b.pf_src = nullptr;
   for (auto &in : b.in) in.reserve(0);
   s->used -= b.mem;
+  for (auto &r : b.rows) {
+    if (r->pat) s->used_pat -= r->pat_bytes;
+    drop_pattern(*r);
+  }
   b.admitted = false;
 }
 
-void admit_queued(gsp_stream *s) {
+// Returns false where the next beam has to wait for the end of the step that runs.
+bool admit_queued(gsp_stream *s) {
   while (!s->queue.empty()) {
     auto it = s->beams.find(s->queue.front());
     if (it == s->beams.end()) {
@@ -617,9 +701,11 @@ void admit_queued(gsp_stream *s) {
     }
     Beam &b = *it->second;
     if (s->used + b.mem > s->budget) break;  // FIFO: later beams wait too
+    if (!make_room(s, b.mem, nullptr)) return false;
     admit(s, b);
     s->queue.pop_front();
   }
+  return true;
 }
 
 void set_attributes(gsp_stream *s, int64_t dd_lds) {
@@ -662,8 +748,18 @@ int64_t step_once(gsp_stream *s) {
     PendingBlock blk;
   };
   std::vector<Work> work;
+  struct InStep {
+    gsp_stream *s = nullptr;
+    ~InStep() {
+      if (!s) return;
+      std::lock_guard<std::mutex> lk(s->mu);
+      s->in_step = false;
+      s->cv.notify_all();
+    }
+  } in_step;
   {
-    std::lock_guard<std::mutex> lk(s->mu);
+    std::unique_lock<std::mutex> lk(s->mu);
+    s->cv.wait(lk, [s] { return s->room_waits == 0; });  // openings that waited for the last step come first
     int64_t rows = 0;  // one staging, dedispersion, series and shift job per (beam, row) at most
     for (auto &kv : s->beams) {
       Beam &b = *kv.second;
@@ -675,8 +771,10 @@ int64_t step_once(gsp_stream *s) {
         b.inflight = true;
       }
     }
+    if (work.empty()) return 0;
+    s->in_step = true;
+    in_step.s = s;
   }
-  if (work.empty()) return 0;
   const auto t_start = Clock::now();
   hipStream_t st = s->st;
   // blocks copied ahead during the previous step have arrived; from here on
@@ -1037,6 +1135,8 @@ int64_t step_once(gsp_stream *s) {
   s->blocks += (int64_t)work.size();
   s->busy_s += std::chrono::duration<double>(t_done - t_start).count();
   // finished beams release their memory; queued beams may now fit
+  s->in_step = false;
+  in_step.s = nullptr;
   for (auto it = s->beams.begin(); it != s->beams.end();) {
     Beam &b = *it->second;
     if ((b.closing || b.ended) && b.pending.empty() && b.admitted) {
@@ -1046,6 +1146,7 @@ int64_t step_once(gsp_stream *s) {
       ++it;
     }
   }
+  trim_copies(s);
   admit_queued(s);
   s->cv.notify_all();
   return (int64_t)work.size();
@@ -1147,11 +1248,12 @@ int gsp_stream_open_beam(gsp_stream *s, int32_t nchan, const double *freqs, doub
     plan_beam(s, *b);
     b->mem = beam_bytes(s, *b);
     if (b->mem > s->budget) fail(GSP_ENOMEM, "beam larger than the stream's memory budget");
-    std::lock_guard<std::mutex> lk(s->mu);
+    std::unique_lock<std::mutex> lk(s->mu);
+    auto room = [&] { return s->queue.empty() && s->used + b->mem <= s->budget; };
+    const bool fits = room() && make_room(s, b->mem, &lk) && room();
     b->id = s->next_id++;
     *beam_id = b->id;
     const int32_t id = b->id;
-    const bool fits = s->queue.empty() && s->used + b->mem <= s->budget;
     Beam &ref = *b;
     s->beams.emplace(id, std::move(b));
     if (fits)
@@ -1207,7 +1309,7 @@ int gsp_stream_push(gsp_stream *s, int32_t beam_id, const uint8_t *block, int64_
 
 int gsp_stream_close_beam(gsp_stream *s, int32_t beam_id) {
   return sguard(s, [&] {
-    std::lock_guard<std::mutex> lk(s->mu);
+    std::unique_lock<std::mutex> lk(s->mu);
     auto it = s->beams.find(beam_id);
     if (it == s->beams.end()) fail(GSP_EINVAL, "unknown beam");
     Beam &b = *it->second;
@@ -1216,7 +1318,11 @@ int gsp_stream_close_beam(gsp_stream *s, int32_t beam_id) {
       release(s, b);
       s->queue.erase(std::remove(s->queue.begin(), s->queue.end(), beam_id), s->queue.end());
       s->beams.erase(it);
-      admit_queued(s);
+      trim_copies(s);
+      if (!admit_queued(s)) {
+        wait_for_step(s, lk);
+        admit_queued(s);
+      }
     }
   });
 }
@@ -1340,7 +1446,7 @@ int gsp_stream_report(gsp_stream *s, gsp_stream_stats *r) {
     r->blocks = s->blocks;
     r->steps = s->steps;
     r->busy_s = s->busy_s;
-    r->mem_used = s->used;
+    r->mem_used = s->used + s->used_pat + (int64_t)s->lin.bytes;
     r->mem_budget = s->budget;
     r->triage_scored = s->scored;
     r->triage_rejected = s->rejected;

@@ -125,3 +125,108 @@ def forced_shape_after_default(hh, gsp, how):
             assert got == want
             if want is None:  # refused: the default stands
                 assert ctx.row_shape(f, plan, r) == before
+
+
+def _least_budget(gsp, ctx, nchan, block, rows):
+    """Smallest budget a beam is accepted under: what the beam itself takes."""
+    lo, hi = 1, 1 << 34
+    while lo < hi:
+        mid = (lo + hi) // 2
+        s = gsp.Stream(ctx, mid, block, [1, 2, 4], 50.0)
+        try:
+            s.open_beam(nchan, _stream_freqs(nchan), STREAM_TSAMP, rows)
+            hi = mid
+        except gsp.GspError as e:
+            assert e.status == gsp.GSP_ENOMEM
+            lo = mid + 1
+        s.close()
+    return lo
+
+
+# job tables and search scratch that a stream holds beside its beams
+STREAM_FIXED = 8 << 20
+
+
+def stream_budget(hh, gsp):
+    """Linear copies and pattern tables are held in what the beams leave of
+    the budget, and given up for a beam that fits without them."""
+    ctx = gsp.Context(0)
+    nchan, block = 1024, 2064
+    one = _least_budget(gsp, ctx, nchan, block, STREAM_ROWS)
+    freqs = _stream_freqs(nchan)
+    data = np.zeros((block, nchan), np.uint8)
+
+    def steps(s, ids, n=3):
+        hh.clear()
+        for _ in range(n):
+            for b in ids:
+                s.push(b, data)
+            assert s.step() == len(ids)
+        return sum(n for n, _ in _pattern_tiles(hh))
+
+    for beams, spare, pattern in ((1, 0, False), (1, 64 << 20, True), (3, 64 << 20, True), (2, 0, False)):
+        base = hh.used()
+        s = gsp.Stream(ctx, beams * one + spare, block, [1, 2, 4], 50.0)
+        ids = []
+        for k in range(beams):
+            bid, ok = s.open_beam(nchan, freqs, STREAM_TSAMP, STREAM_ROWS)
+            assert ok, (beams, k)
+            ids.append(bid)
+            tiles = steps(s, ids)
+            rep = s.report()
+            print(f"{k + 1} of {beams} beams, {spare} bytes to spare: {tiles} pattern tiles, {rep['mem_used']} held")
+            assert rep["mem_used"] <= rep["mem_budget"]
+            assert hh.used() - base <= rep["mem_used"] + STREAM_FIXED
+            if k + 1 < beams:
+                assert tiles > 0  # the room of the beams to come
+        assert (tiles > 0) == pattern
+        assert not s.open_beam(nchan, freqs, STREAM_TSAMP, STREAM_ROWS)[1] or spare >= one
+        for b in ids:
+            s.close_beam(b)
+        s.close()
+        assert hh.used() - base <= STREAM_FIXED
+
+
+def stream_budget_with_worker(hh, gsp):
+    """The same while a worker thread steps: openings wait for its steps."""
+    ctx = gsp.Context(0)
+    nchan, block = 1024, 2064
+    one = _least_budget(gsp, ctx, nchan, block, STREAM_ROWS)
+    s = gsp.Stream(ctx, 3 * one + (1 << 20), block, [1, 2, 4], 50.0)
+    data = np.zeros((block, nchan), np.uint8)
+    s.start()
+    live = []
+    for k in range(40):
+        if len(live) == 3:
+            s.close_beam(live.pop(0))
+        bid, ok = s.open_beam(nchan, _stream_freqs(nchan), STREAM_TSAMP, STREAM_ROWS)
+        live.append(bid)
+        for b in live:
+            for _ in range(3):
+                s.push(b, data)
+        rep = s.report()
+        assert rep["mem_used"] <= rep["mem_budget"], (k, rep)
+    s.flush()
+    s.stop()
+    rep = s.report()
+    print(rep)
+    assert rep["beams_queued"] == 0 and rep["blocks_pending"] == 0 and rep["mem_used"] <= rep["mem_budget"]
+    s.close()
+
+
+def stream_without_room_for_tables(hh, gsp):
+    """A beam whose pattern tables get no device memory runs on the other tile."""
+    ctx = gsp.Context(0)
+    nchan, block = 1024, 2064
+    freqs = _stream_freqs(nchan)
+    one = _least_budget(gsp, ctx, nchan, block, STREAM_ROWS)
+    s = gsp.Stream(ctx, 1 << 34, block, [1, 2, 4], 50.0)
+    hh.limit(hh.used() + one + (256 << 10))  # the beam, and a part of the tables
+    bid, ok = s.open_beam(nchan, freqs, STREAM_TSAMP, STREAM_ROWS)
+    assert ok
+    hh.clear()
+    for _ in range(3):
+        s.push(bid, np.zeros((block, nchan), np.uint8))
+        assert s.step() == 1
+    assert not _pattern_tiles(hh) and hh.launches("k_dedisp_jobs")
+    s.close()

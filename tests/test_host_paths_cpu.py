@@ -23,3 +23,8 @@ def test_stream_graph_holds_every_tile_after_steps_without_it(host):
 @pytest.mark.parametrize("how", ["set", "load"])
 def test_forced_row_shape_after_the_default(host, how, tmp_path):
     host("forced_shape_after_default", how=how if how == "set" else str(tmp_path))
+
+
+@pytest.mark.parametrize("case", ["stream_budget", "stream_budget_with_worker", "stream_without_room_for_tables"])
+def test_stream_keeps_its_memory_budget(host, case):
+    host(case)
