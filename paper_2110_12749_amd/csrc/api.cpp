@@ -87,8 +87,9 @@ RowTables &row_tables(gsp_ctx *ctx, const gsp_dmt_desc *desc, const double *freq
     // not fit the LDS or its smaller tile be faster (next: that one) or not
     // pay (then plain_shape); the byte-quad tile's copies may not fit (such
     // rows split their band between two tiles where the quads that do not fit
-    // lie at one end of it, else keep the 16-bit tile).  A tuned shape is not
-    // replaced.
+    // lie at one end of it, else keep the 16-bit tile).  The same where a
+    // shape's tables get no memory: another's may be smaller.  A tuned shape is
+    // not replaced.
     std::vector<DedispShape> order{want};
     if (!tuned) {
       if (want.kind == 4) {
@@ -122,7 +123,8 @@ RowTables &row_tables(gsp_ctx *ctx, const gsp_dmt_desc *desc, const double *freq
         build_row_tables(ctx, desc, freqs, s, order[k], *rt, 0, tuned);
         break;
       } catch (const Error &e) {
-        if (e.status != GSP_EINVAL || k + 1 == order.size()) throw;
+        if ((e.status != GSP_EINVAL && e.status != GSP_ENOMEM) || k + 1 == order.size()) throw;
+        if (e.status == GSP_ENOMEM) (void)hipGetLastError();
         delays = std::move(rt->delays_host);
       }
     }

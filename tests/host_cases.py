@@ -230,3 +230,25 @@ def stream_without_room_for_tables(hh, gsp):
         assert s.step() == 1
     assert not _pattern_tiles(hh) and hh.launches("k_dedisp_jobs")
     s.close()
+
+
+def row_tables_without_room(hh, gsp):
+    """A default row shape whose tables get no device memory gives way to one
+    with smaller tables; a shape that was asked for is refused."""
+    freqs = 1000.0 + (np.arange(1024) + 0.5) * 500.0 / 1024
+    for row, room, kind in (((0.0, 0.1, 400, 1), 500000, 2), ((100.0, 0.4, 400, 2), 1800000, 0)):
+        desc = gsp.plan_shape(1 << 19, freqs, 49.152e-6, [row])
+        ctx = gsp.Context(0)
+        assert ctx.row_shape(freqs, desc, 0)[4] == 4
+        ctx = gsp.Context(0)
+        hh.limit(hh.used() + room)
+        shape = ctx.row_shape(freqs, desc, 0)
+        print(row, "with", room, "bytes:", shape)
+        assert shape[4] == kind
+        other = gsp.Context(0)
+        try:
+            other.set_row_shape(freqs, desc, 0, 4, 8, 8, 16, 4)
+            assert False
+        except gsp.GspError as e:
+            assert e.status == gsp.GSP_ENOMEM
+        hh.limit(1 << 36)

@@ -28,3 +28,7 @@ def test_forced_row_shape_after_the_default(host, how, tmp_path):
 @pytest.mark.parametrize("case", ["stream_budget", "stream_budget_with_worker", "stream_without_room_for_tables"])
 def test_stream_keeps_its_memory_budget(host, case):
     host(case)
+
+
+def test_default_row_shape_without_room_for_its_tables(host):
+    host("row_tables_without_room")
