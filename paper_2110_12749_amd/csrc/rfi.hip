@@ -195,7 +195,8 @@ __global__ __launch_bounds__(kRfiThreads) void k_rfi_sums(const uint8_t *__restr
 // Channel means over the unflagged spectra of blocks that replace some:
 // thread = channel, workgroup = (channel tile, blocks y, y + gridDim.y, ...).
 // csum: the sums (k_rfi_sums); null for blocks of at most kRfiSlice spectra,
-// which are summed here (their sums would take more memory than their bytes).
+// which are summed here (their sums would take more memory than their bytes),
+// and where there is no memory for them.
 __global__ __launch_bounds__(kRfiThreads) void k_rfi_means(const uint8_t *__restrict__ x, int64_t nsamp,
                                                           int32_t nchan, int64_t block, int64_t n_blocks,
                                                           const uint8_t *__restrict__ flag,
@@ -307,11 +308,17 @@ extern "C" int gsp_rfi_clean(gsp_ctx *ctx, const uint8_t *fb_dev, int64_t nsamp,
     const size_t o_mean = (o_nu + (size_t)nb * 4 + 255) / 256 * 256;
     const size_t o_msum = (o_mean + (size_t)nb * nchan + 255) / 256 * 256;
     const size_t o_cnt = (o_msum + (size_t)nb * 8 + 255) / 256 * 256;
-    const bool split = clip && block > kRfiSlice && nsamp > kRfiSlice;  // channel sums of their own
+    bool split = clip && block > kRfiSlice && nsamp > kRfiSlice;  // channel sums of their own
     const size_t o_csum = o_cnt + 256;
-    const size_t bytes = o_csum + (split ? (size_t)nb * nchan * 4 : 0);
     ctx->rfi.device = ctx->device;
-    ctx->rfi.reserve(bytes);
+    try {
+      ctx->rfi.reserve(o_csum + (split ? (size_t)nb * nchan * 4 : 0));
+    } catch (const Error &e) {  // up to a 32nd of the input: k_rfi_means does without
+      if (!split || e.status != GSP_ENOMEM) throw;
+      (void)hipGetLastError();
+      split = false;
+      ctx->rfi.reserve(o_csum);
+    }
     unsigned char *base = ctx->rfi.as<unsigned char>();
     int32_t *s = reinterpret_cast<int32_t *>(base + o_s);
     uint8_t *flag = base + o_flag;

@@ -252,3 +252,18 @@ def row_tables_without_room(hh, gsp):
         except gsp.GspError as e:
             assert e.status == gsp.GSP_ENOMEM
         hh.limit(1 << 36)
+
+
+def rfi_without_room_for_sums(hh, gsp):
+    """Mitigation that gets no memory for its split channel sums runs without them."""
+    nsamp, nchan, block = 8256, 4096, 129
+    fb, out = hh.malloc(nsamp * nchan), hh.malloc(nsamp * nchan)
+    n = C.c_int64()
+    for room, split in ((1 << 24, True), (600 << 10, False)):
+        ctx = gsp.Context(0)
+        hh.limit(hh.used() + room)
+        hh.clear()
+        rc = gsp.lib().gsp_rfi_clean(ctx.h, fb, nsamp, nchan, 3.0, block, 1, out, C.byref(n), None)
+        assert rc == gsp.GSP_OK, rc
+        assert len(hh.launches("k_rfi_means")) == 1 and bool(hh.launches("k_rfi_sums")) == split
+        hh.limit(1 << 36)

@@ -32,3 +32,7 @@ def test_stream_keeps_its_memory_budget(host, case):
 
 def test_default_row_shape_without_room_for_its_tables(host):
     host("row_tables_without_room")
+
+
+def test_mitigation_without_room_for_split_sums(host):
+    host("rfi_without_room_for_sums")
