@@ -1443,6 +1443,7 @@ namespace {
 
 void reserve_batch(gsp_cnn *c, int64_t n) {
   if (n <= c->cap) return;
+  c->cap = c->last_n = c->last_bwd_n = 0;  // what fails half way leaves buffers without memory
   const int dev = c->ctx->device;
   for (int l = 0; l < 4; ++l) {
     const int64_t px = n * kConv[l].h * kConv[l].h;

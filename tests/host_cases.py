@@ -267,3 +267,30 @@ def rfi_without_room_for_sums(hh, gsp):
         assert rc == gsp.GSP_OK, rc
         assert len(hh.launches("k_rfi_means")) == 1 and bool(hh.launches("k_rfi_sums")) == split
         hh.limit(1 << 36)
+
+
+def network_after_a_batch_without_room(hh, gsp):
+    """A batch whose buffers got no memory leaves the network usable."""
+    ctx = gsp.Context(0)
+    net = gsp.Cnn(ctx, seed=1)
+    logits = np.zeros(4096, np.float32)
+    x = hh.malloc(1 << 20)
+
+    def forward(n):
+        return gsp.lib().gsp_cnn_forward(net.h, x, n, logits.ctypes.data_as(C.c_void_p), None)
+
+    assert forward(64) == gsp.GSP_OK
+    held = hh.used()
+    hh.limit(held + (64 << 20))
+    assert forward(4096) == gsp.GSP_ENOMEM
+    hh.limit(1 << 36)
+    try:  # the activations of the batch before are gone with their buffers
+        net.activation(0, 64)
+        assert False
+    except gsp.GspError as e:
+        assert e.status == gsp.GSP_EINVAL
+    assert forward(64) == gsp.GSP_OK
+    print(held, hh.used())
+    assert hh.used() >= held  # every buffer is there again
+    for l in hh.launches("k_conv_pool"):
+        assert hh.room(struct.unpack_from("<Q", bytes(l.arg))[0]) > 0

@@ -36,3 +36,7 @@ def test_default_row_shape_without_room_for_its_tables(host):
 
 def test_mitigation_without_room_for_split_sums(host):
     host("rfi_without_room_for_sums")
+
+
+def test_network_after_a_batch_without_room(host):
+    host("network_after_a_batch_without_room")
