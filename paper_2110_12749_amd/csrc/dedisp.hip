@@ -169,7 +169,7 @@ static double tile_clocks(int32_t n_dm, int64_t n_out, int32_t nchan, int trials
 }
 // Tiles of 32 trials x 512 outputs a row has on the 16-bit tile
 static int64_t plain_tiles(int32_t n_dm, int64_t n_out) { return (int64_t)((n_dm + 31) / 32) * ((n_out + 511) / 512); }
-static double plain8_clocks(int32_t n_dm, int64_t n_out, int32_t nchan) {
+double plain8_clocks(int32_t n_dm, int64_t n_out, int32_t nchan) {
   return tile_clocks(n_dm, n_out, nchan, 32, 512, 190.0, 115.0, 5e3, 18e3);
 }
 double plain_clocks(int32_t n_dm, int64_t n_out, int32_t nchan) {

@@ -222,8 +222,10 @@ DedispShape default_shape(const gsp_dmt_desc *desc, int32_t s);
 DedispShape plain_shape(const gsp_dmt_desc *desc, int32_t s);
 DedispShape quad_shape();  // the byte-quad tile's default
 DedispShape pair_shape(const gsp_dmt_desc *desc, int32_t s, bool small);  // the 16-bit tile's; small: with its form for few tiles
-// estimated clocks of a row on the 16-bit and on the byte-quad tile
+// estimated clocks of a row on the 16-bit tile (in the form that batches take, or
+// always with 8 waves, as in streams) and on the byte-quad tile
 double plain_clocks(int32_t n_dm, int64_t n_out, int32_t nchan);
+double plain8_clocks(int32_t n_dm, int64_t n_out, int32_t nchan);
 double quad_clocks(int32_t n_dm, int64_t n_out, int32_t nchan);
 bool shape_supported(const DedispShape &s);
 std::string row_signature(const gsp_dmt_desc *desc, int32_t s);

@@ -494,13 +494,16 @@ int64_t beam_bytes(const gsp_stream *s, const Beam &b) {
 // samples, written as NB bytes at 4.6 TB/s, 2.4 GHz) and 70000 clocks for the
 // launches and the tables it adds to a step and for rows that now run one after
 // the other (one beam of 256 channels with rows of 70, 120 and 45 trials: 0.65
-// ms a step without that margin, 0.64 before the pattern tile).  4 beams of 4096 channels,
-// 1175 trials and 20480 samples: 12.9 ms a step with k_dedisp_jobs, 4.6 with
-// the copies and the pattern tile.
+// ms a step without that margin, 0.64 before the pattern tile).  4 beams of 4096
+// channels, 1175 trials and 20480 samples: 12.9 ms a step with k_dedisp_jobs, 4.6
+// with the copies and the pattern tile.  k_dedisp_jobs has 8 waves for any number
+// of tiles: with the clocks of the batch's 16 waves, for up to 256 tiles, one beam
+// of 1024 channels, rows of 96 and 96 trials and 4096 samples took 0.474 ms a step
+// and one of 256 channels, 250 trials and 16384 samples 0.264, now 0.419 and 0.214.
 void plan_pattern(StreamRow &row, int32_t nchan) {
   if (row.D > 8) return;  // the pattern tile's samples have 11 bits
   const int NB = row.D == 1 ? 1 : 2;
-  double best = plain_clocks(row.n_dm, row.Wcap, nchan) - 70e3 -
+  double best = plain8_clocks(row.n_dm, row.Wcap, nchan) - 70e3 -
                 (double)nchan * (double)(row.Wcap + row.M) * (2 + NB) * 2.4e9 / 4.6e12;
   std::unique_ptr<PatHost> tables;
   int best_tpw = 0;

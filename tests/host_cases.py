@@ -294,3 +294,21 @@ def network_after_a_batch_without_room(hh, gsp):
     assert hh.used() >= held  # every buffer is there again
     for l in hh.launches("k_conv_pool"):
         assert hh.room(struct.unpack_from("<Q", bytes(l.arg))[0]) > 0
+
+
+def stream_rows_of_one_round(hh, gsp):
+    """Rows of at most a tile to a CU: the estimate that the pattern tile is
+    compared with is that of the streaming kernel (8 waves a workgroup), which
+    takes longer there than the batch kernel's form for so few tiles."""
+    ctx = gsp.Context(0)
+    nchan, block = 256, 8192
+    s = gsp.Stream(ctx, 1 << 34, block, [1, 2, 4], 50.0)
+    bid, ok = s.open_beam(nchan, _stream_freqs(nchan), STREAM_TSAMP, STREAM_ROWS)
+    assert ok
+    hh.clear()
+    for _ in range(3):
+        s.push(bid, np.zeros((block, nchan), np.uint8))
+        s.step()
+    print(_pattern_tiles(hh))
+    assert sum(n for n, _ in _pattern_tiles(hh)) > 0
+    s.close()

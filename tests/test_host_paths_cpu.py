@@ -40,3 +40,7 @@ def test_mitigation_without_room_for_split_sums(host):
 
 def test_network_after_a_batch_without_room(host):
     host("network_after_a_batch_without_room")
+
+
+def test_stream_rows_of_one_round_take_the_pattern_tile(host):
+    host("stream_rows_of_one_round")
