@@ -455,10 +455,9 @@ typedef struct gsp_shape {
 
 /* Autotuner.  For every plan row of `desc`, times the dedispersion kernel
  * with each built-in candidate shape on the given input (dmt_dev is
- * overwritten; fb_dev as in gsp_dedisperse), `n_reps` timed launches each and,
- * for those close to the fastest, three times as many again in turn, keeps the
- * fastest and uses it for every later call on this context whose row has the
- * same signature (nchan, D, n_dm, maximum delay, length class).
+ * overwritten; fb_dev as in gsp_dedisperse), `n_reps` timed launches each,
+ * keeps the fastest and uses it for every later call on this context whose
+ * row has the same signature (nchan, D, n_dm, maximum delay, length class).
  * Synchronises `stream`. */
 int gsp_autotune(gsp_ctx *ctx, const uint8_t *fb_dev, const double *freqs_mhz, const gsp_dmt_desc *desc,
                  int32_t *dmt_dev, int32_t n_reps, void *stream);

@@ -4,11 +4,7 @@
 // The best shape depends on the row's downsampling (uint8 or uint16 staging),
 // on the spread of delays across a tile of trials (LDS window per channel) and
 // on the row length; it is found by timing every candidate on the caller's
-// data and is then keyed by the row signature.  Candidates within a few percent
-// of the fastest are timed again in turn: one launch of the same kernel can take
-// 6 % longer than the next (the survey's D = 2 row in tiles of 96 trials: 25.5
-// and 27.1 ms; of 64, 25.1, once left for the former).
-#include <algorithm>
+// data and is then keyed by the row signature.
 #include <cstdio>
 #include <cstring>
 #include <fstream>
@@ -40,15 +36,6 @@ const DedispShape kCandidates[] = {
     // pattern tile (D <= 8)
     mk(4, 12, 8, 16, 4), mk(4, 8, 8, 16, 4),
 };
-
-// A candidate whose first time is close to the fastest
-struct Finalist {
-  DedispShape shape;
-  float first = 0.f, sum = 0.f;
-  std::unique_ptr<RowTables> rt;
-};
-constexpr float kClose = 1.08f;
-constexpr int kRounds = 3;
 
 DedispShape from_abi(const gsp_shape &s) {
   DedispShape d;
@@ -118,20 +105,8 @@ int gsp_autotune(gsp_ctx *ctx, const uint8_t *fb, const double *freqs, const gsp
     try {
       for (int32_t s = 0; s < desc->n_seg; ++s) {
         const std::string sig = row_signature(desc, s);
-        DedispShape best = default_shape(desc, s);
-        auto time_row = [&](const RowTables &rt) {
-          stage_row(ctx, fb, desc, rt, st);
-          launch_dedisp(ctx, rt, dmt + desc->offset[s], st);  // warm-up
-          check_hip(hipEventRecord(e0, st), "record event");
-          for (int r = 0; r < n_reps; ++r) launch_dedisp(ctx, rt, dmt + desc->offset[s], st);
-          check_hip(hipEventRecord(e1, st), "record event");
-          check_hip(hipEventSynchronize(e1), "wait for event");
-          float ms = 0.f;
-          check_hip(hipEventElapsedTime(&ms, e0, e1), "event time");
-          return ms;
-        };
-        std::vector<Finalist> fin;
         float best_ms = 1e30f;
+        DedispShape best = default_shape(desc, s);
         for (const DedispShape &cand : kCandidates) {
           ctx->tuned[sig] = cand;
           RowTables *rt = nullptr;
@@ -141,33 +116,18 @@ int gsp_autotune(gsp_ctx *ctx, const uint8_t *fb, const double *freqs, const gsp
             if (e.status == GSP_EINVAL) continue;  // does not fit: skip
             throw;
           }
-          const float ms = time_row(*rt);
+          stage_row(ctx, fb, desc, *rt, st);
+          launch_dedisp(ctx, *rt, dmt + desc->offset[s], st);  // warm-up
+          check_hip(hipEventRecord(e0, st), "record event");
+          for (int r = 0; r < n_reps; ++r) launch_dedisp(ctx, *rt, dmt + desc->offset[s], st);
+          check_hip(hipEventRecord(e1, st), "record event");
+          check_hip(hipEventSynchronize(e1), "wait for event");
+          float ms = 0.f;
+          check_hip(hipEventElapsedTime(&ms, e0, e1), "event time");
           if (ms < best_ms) {
             best_ms = ms;
             best = cand;
           }
-          fin.emplace_back();
-          fin.back().shape = cand;
-          fin.back().first = ms;
-        }
-        fin.erase(std::remove_if(fin.begin(), fin.end(), [&](const Finalist &f) { return f.first > kClose * best_ms; }),
-                  fin.end());
-        try {
-          for (size_t k = 0; k < fin.size() && fin.size() > 1; ++k) {
-            fin[k].rt = std::make_unique<RowTables>();
-            build_row_tables(ctx, desc, freqs, s, fin[k].shape, *fin[k].rt);
-          }
-        } catch (const Error &e) {
-          if (e.status != GSP_ENOMEM) throw;
-          (void)hipGetLastError();
-          fin.clear();  // no room for the tables of all: the first times decide
-        }
-        if (fin.size() > 1) {
-          for (int r = 0; r < kRounds; ++r)
-            for (Finalist &f : fin) f.sum += time_row(*f.rt);
-          best = std::min_element(fin.begin(), fin.end(), [](const Finalist &a, const Finalist &b) {
-                   return a.sum < b.sum;
-                 })->shape;
         }
         ctx->tuned[sig] = best;
         row_tables(ctx, desc, freqs, s);

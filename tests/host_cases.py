@@ -312,21 +312,3 @@ def stream_rows_of_one_round(hh, gsp):
     print(_pattern_tiles(hh))
     assert sum(n for n, _ in _pattern_tiles(hh)) > 0
     s.close()
-
-
-def autotune_repeats_close_times(hh, gsp):
-    """Shapes whose first times are close are timed again in turn: a lucky
-    first time does not make the slower one the row's shape."""
-    freqs = 1000.0 + (np.arange(1024) + 0.5) * 500.0 / 1024
-    desc = gsp.plan_shape(100000, freqs, 49.152e-6, [(0.0, 0.1, 400, 2)])
-    fb, dmt = hh.malloc(100000 * 1024), hh.malloc(4 * desc.total)
-    long = [27.0] * 40
-    hh.cost("k_dedisp_patILi12ELi2E", 25.0, 24.5, 24.5, *long)  # the first three: warm-up and two timed launches
-    hh.cost("k_dedisp_patILi8ELi2E", 25.1)
-    hh.cost("k_dedispI", 60.0)
-    ctx = gsp.Context(0)
-    f = np.ascontiguousarray(freqs)
-    rc = gsp.lib().gsp_autotune(ctx.h, fb, f.ctypes.data_as(C.c_void_p), C.byref(desc), dmt, 2, None)
-    assert rc == gsp.GSP_OK
-    print(ctx.row_shape(freqs, desc, 0))
-    assert ctx.row_shape(freqs, desc, 0)[1] == 8

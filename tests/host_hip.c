@@ -34,7 +34,7 @@ static size_t used, limit = (size_t)1 << 36, fail_over = SIZE_MAX;
 static graph_t *capture;
 static int captures;
 static double clock_ms;
-static struct { char part[64]; double ms[64]; int n, at; } cost[COST_RULES];
+static struct { char part[64]; double ms[8]; int n, at; } cost[COST_RULES];
 static int n_cost;
 static __thread struct { dim3_t g, b; size_t sh; void *st; } call_;
 

@@ -44,7 +44,3 @@ def test_network_after_a_batch_without_room(host):
 
 def test_stream_rows_of_one_round_take_the_pattern_tile(host):
     host("stream_rows_of_one_round")
-
-
-def test_autotuner_times_close_shapes_again(host):
-    host("autotune_repeats_close_times")
