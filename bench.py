@@ -40,6 +40,11 @@ PEAK_NOTE = {"dedisperse": "two 16-bit sample additions per packed 32-bit VALU a
                                 "2.4 GHz",
              "dedisperse_pattern": "two dwords of two 8-channel sums per v_add3_u32: 32 x 256 CUs x 64 lanes x "
                                    "2.4 GHz"}
+# What bounds each (counters in profiles/)
+BOUND_NOTE = {"dedisperse": "the kernel is bound by its LDS reads (see 'lds') and the VALU work of staging them",
+              "dedisperse_quad": "the kernel is bound by its LDS reads (see 'lds') and the VALU work of staging them",
+              "dedisperse_pattern": "building the 8-channel sums is not in this peak, and no single unit bounds the "
+                                    "kernel (vector units 58 to 60 % busy, LDS reads 32 to 59 %)"}
 # LDS bytes the kernels read per sample addition (a dword holds two 16-bit
 # samples, four channels' bytes, or two outputs' 8-channel sums)
 LDS_BYTES_PER_ADD = {"dedisperse": 2.0, "dedisperse_quad": 1.0, "dedisperse_pattern": 0.25}
@@ -533,8 +538,7 @@ def main():
                      "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-scaled)",
                      "kernel": kname, "launches_per_step": n / args.steps,
                      "work": "integer sample additions (n_dm * n_out * nchan per launch)",
-                     "peak_note": PEAK_NOTE[dom] + "; the kernel is bound by its LDS reads (see 'lds') and the VALU "
-                                                   "work of staging them",
+                     "peak_note": PEAK_NOTE[dom] + "; " + BOUND_NOTE[dom],
                      "all_dedispersion": {"adds_per_s": all_adds / (all_ms / 1e3), "ms_per_step": all_ms / args.steps,
                                           "what": "every dedispersion launch of the step (all tiles)"},
                      "int32_reference": {"peak": PEAK_INT32_OPS / 1e12, "frac": achieved / PEAK_INT32_OPS,

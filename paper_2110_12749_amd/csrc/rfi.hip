@@ -11,12 +11,13 @@
 //   zero-DM filter (zero_dm != 0), after clipping: z_j = floor((2 s'_j +
 //     nchan) / (2 nchan)) of the (clipped) spectrum's sum s'_j is
 //     subtracted and 128 added back, clamped to 0..255.
-// Design: four HBM-bound passes.  One wave per spectrum forms s_j (16-byte
-// loads, byte sums by v_sad_u8, DPP reduction); one workgroup per block
-// takes the moments (int64 / 128-bit sums) and flags; channel means are
-// read only for blocks that replace something, each block's spectra split over
-// many workgroups; a last pass writes the replaced spectra and applies the
-// filter, in place if out == in.
+// Design: three HBM-bound passes over spectra and two small ones.  One wave
+// per spectrum forms s_j (16-byte loads, byte sums by v_sad_u8, wave
+// reduction); one workgroup per block takes the moments (int64 / 128-bit sums)
+// and flags; the spectra of blocks that replace something are read for their
+// channel sums, each block split over many workgroups, and the means are taken
+// from these; a last pass writes the replaced spectra and applies the filter,
+// in place if out == in.
 #include <algorithm>
 #include <cmath>
 

@@ -28,8 +28,7 @@ class HostHip:
         lib.hh_room.restype = C.c_int64
         lib.hh_room.argtypes = [C.c_uint64]
         lib.hh_used.restype = C.c_uint64
-        lib.hh_limit.argtypes = lib.hh_fail_over.argtypes = [C.c_uint64]
-        lib.hh_cost.argtypes = [C.c_char_p, C.POINTER(C.c_double), C.c_int]
+        lib.hh_limit.argtypes = [C.c_uint64]
 
     def launches(self, part=""):
         """The log's launches whose kernel name holds `part`."""
@@ -46,17 +45,11 @@ class HostHip:
     def limit(self, nbytes):
         self.lib.hh_limit(nbytes)
 
-    def fail_over(self, nbytes):
-        self.lib.hh_fail_over(nbytes)
-
     def used(self):
         return int(self.lib.hh_used())
 
     def room(self, p):
         return int(self.lib.hh_room(p))
-
-    def cost(self, part, *ms):
-        self.lib.hh_cost(part.encode(), (C.c_double * len(ms))(*ms), len(ms))
 
     def malloc(self, nbytes):
         p = C.c_void_p()
